@@ -64,3 +64,31 @@ def test_spectrum_argument_errors(gpu_lib):
         gpu_lib.spectrum(torch.zeros((10, 2, 1), dtype=torch.float64, device="cuda"), 0.05, np.linspace(0.1, 1.0, 5))
     with pytest.raises(ValueError):
         gpu_lib.spectrum(sig, 0.05, np.array([0.1, 0.2, 0.4]), kappa=1.0)
+
+
+@pytest.mark.parametrize("n_t,nsig,n_w", [(1, 1, 1), (2, 2, 3), (255, 3, 4), (257, 4, 5), (8193, 7, 9)])
+def test_spectrum_edges(gpu_lib, n_t, nsig, n_w):
+    """Sample counts around the block's 256 lanes and its 8192-sample phase refresh, signal counts
+    around the groups of three and frequency counts around the groups of four, both kinds.  The
+    phases reach w t = 655 rad, so each sine is good to about 655 x 1.1e-16 on either side: 1e-12 of
+    the windowed sum of |y| leaves a factor of ten."""
+    import torch
+
+    rng = np.random.default_rng(5)
+    dt, kappa = 0.05, 1e-3
+    omega = 0.2 + 0.175 * np.arange(n_w)
+    y = rng.standard_normal((n_t, nsig))
+    z = rng.standard_normal((n_t, nsig, 2))
+    S = gpu_lib.spectrum(torch.from_numpy(y).cuda(), dt, omega, kappa=kappa).cpu().numpy()
+    Sa = gpu_lib.spectrum(torch.from_numpy(y).cuda(), dt, omega, kappa=kappa, average=True).cpu().numpy()
+    C = gpu_lib.spectrum(torch.from_numpy(z).cuda(), dt, omega).cpu().numpy()
+    n = np.arange(n_t)
+    h = 0.5 * (1.0 + np.cos(np.pi * n / (n_t - 1))) if n_t > 1 else np.ones(1)
+    for j, w in enumerate(omega):
+        sn, cs = np.sin(w * (n * dt)), np.cos(w * (n * dt))
+        ref = w * dt / kappa * ((h * sn) @ (y - y[0]))
+        bar = 1e-12 * w * dt / kappa * (h @ np.abs(y - y[0]) + 1.0)
+        assert np.all(np.abs(S[:, j] - ref) <= bar)
+        assert abs(Sa[j] - ref.mean()) <= bar.max()
+        refc = w * dt * ((h * cs) @ z[:, :, 0] - (h * sn) @ z[:, :, 1])
+        assert np.all(np.abs(C[:, j] - refc) <= 1e-12 * w * dt * (h @ np.abs(z).sum(axis=2) + 1.0))
