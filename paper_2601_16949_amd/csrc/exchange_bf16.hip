@@ -49,9 +49,13 @@ __device__ __forceinline__ bf8 cat(bf4 a, bf4 b) {
   return bf8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
-// 8 consecutive bf16 from global, zero beyond `lim` elements
-__device__ __forceinline__ us8 fetch8(const __bf16 *src, int lim, bool vec) {
-  if (vec && lim >= 8) return *reinterpret_cast<const us8 *>(src);
+// 8 consecutive bf16 from global, zero beyond `lim` elements.  A whole group is one 16-byte load at
+// whatever address the row gives it (2-byte aligned where v is odd; global memory takes any).  At
+// o37 v277 N_Q743, two RHS, an exchange launch takes 320 us; with eight 2-byte loads for the rows of
+// an odd v, whose issue bound it, it took 1380 us.
+typedef us8 us8_unaligned __attribute__((aligned(2)));
+__device__ __forceinline__ us8 fetch8(const __bf16 *src, int lim) {
+  if (lim >= 8) return *reinterpret_cast<const us8_unaligned *>(src);
   const unsigned short *s = reinterpret_cast<const unsigned short *>(src);
   us8 val = us8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -96,7 +100,6 @@ __global__ __launch_bounds__(256, 1) void k_exchange_bf16(const __bf16 *__restri
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, m = lane & 31;
   const int ws = wave >> 1, wc = wave & 1;
-  const bool vec = (v & 7) == 0;
   const bool ovec = (o & 3) == 0;
   const int nkc = (v + KC - 1) / KC;
   const int NC = (qb - qa) * nkc;
@@ -126,8 +129,8 @@ __global__ __launch_bounds__(256, 1) void k_exchange_bf16(const __bf16 *__restri
         const int sl = s_base + row / O32, j = row % O32, a = a0 + k8;
         if (sl < ns && j < o && a < v) {
           const size_t off = ((size_t)sl * o + j) * v + a;
-          vh = fetch8(Xh + off, v - a, vec);
-          vl = fetch8(Xl + off, v - a, vec);
+          vh = fetch8(Xh + off, v - a);
+          vl = fetch8(Xl + off, v - a);
         }
       }
       xhr[r] = vh;
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(256, 1) void k_exchange_bf16(const __bf16 *__restri
       if (e < C::BT) {
         const int cl = e / (KC / 8), k8 = (e - cl * (KC / 8)) * 8;
         const int cc = c_base + cl, a = a0 + k8;
-        if (cc < v && a < v) val = fetch8(Vq + (size_t)cc * v + a, v - a, vec);  // row cc of symmetric B_vv^Q
+        if (cc < v && a < v) val = fetch8(Vq + (size_t)cc * v + a, v - a);  // row cc of symmetric B_vv^Q
       }
       brr[r] = val;
     }
@@ -409,7 +412,6 @@ __global__ __launch_bounds__(64 * NW, 1) void k_exchange_bf16w(const __bf16 *__r
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, m = lane & 31;
-  const bool vec = (v & 7) == 0;
   const bool ovec = (o & 3) == 0;
   const int nkc = (v + KC - 1) / KC;
   const int NC = (qb - qa) * nkc;
@@ -428,8 +430,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_exchange_bf16w(const __bf16 *__r
         const int j = e / (KC / 8), k8 = (e - j * (KC / 8)) * 8, a = a0 + k8;
         if (j < o && a < v) {
           const size_t off = ((size_t)sl * o + j) * v + a;
-          vh = fetch8(Xh + off, v - a, vec);
-          vl = fetch8(Xl + off, v - a, vec);
+          vh = fetch8(Xh + off, v - a);
+          vl = fetch8(Xl + off, v - a);
         }
       }
       RR.xh[r] = vh;
@@ -443,7 +445,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_exchange_bf16w(const __bf16 *__r
       if (e < C::BT) {
         const int cl = e / (KC / 8), k8 = (e - cl * (KC / 8)) * 8;
         const int cc = c_base + cl, a = a0 + k8;
-        if (cc < v && a < v) val = fetch8(Vq + (size_t)cc * v + a, v - a, vec);
+        if (cc < v && a < v) val = fetch8(Vq + (size_t)cc * v + a, v - a);
       }
       RR.b[r] = val;
     }

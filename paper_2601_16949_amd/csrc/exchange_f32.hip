@@ -25,6 +25,7 @@ namespace rttda {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4_unaligned __attribute__((aligned(4)));  // rows start at any float where v % 4 != 0
 
 template <int O16, int WS, int WC, int KC>
 struct Cfg {
@@ -68,7 +69,6 @@ __global__ __launch_bounds__(256, 1) void k_exchange_f32(const float *__restrict
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, n = lane & 15;
   const int ws = wave >> 1, wc = wave & 1;
-  const bool vec = (v & 3) == 0;
   const int nkc = (v + KC - 1) / KC;
   const int NC = (qb - qa) * nkc;
   // column blocks entirely beyond v (last column tile) skip their MFMAs (wave-uniform)
@@ -96,8 +96,8 @@ __global__ __launch_bounds__(256, 1) void k_exchange_f32(const float *__restrict
         const int sl = s_base + row / O16, j = row % O16, a = a0 + k4;
         if (sl < ns && j < o && a < v) {
           const float *src = X + ((size_t)sl * o + j) * v + a;
-          if (vec) {
-            val = *reinterpret_cast<const f4 *>(src);
+          if (a + 3 < v) {
+            val = *reinterpret_cast<const f4_unaligned *>(src);
           } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t) val[t] = (a + t < v) ? src[t] : 0.f;
@@ -116,8 +116,8 @@ __global__ __launch_bounds__(256, 1) void k_exchange_f32(const float *__restrict
         const int cc = c_base + cl, a = a0 + k4;
         if (cc < v && a < v) {
           const float *src = Vq + (size_t)cc * v + a;  // row cc of the symmetric B_vv^Q
-          if (vec) {
-            val = *reinterpret_cast<const f4 *>(src);
+          if (a + 3 < v) {
+            val = *reinterpret_cast<const f4_unaligned *>(src);
           } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t) val[t] = (a + t < v) ? src[t] : 0.f;
