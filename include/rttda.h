@@ -321,7 +321,8 @@ typedef struct rttda_tuning {
   int32_t overlap;          /* 1 = the Coulomb pair runs on a second stream alongside the
                                exchange, 2 = both in order on the context's stream; the
                                default is 1 when the exchange has at least 5e10 flops per
-                               stage at max_rhs, else 2                                     */
+                               stage at max_rhs and its kernel shares the CUs (not the
+                               X-resident variants), else 2                                 */
   int32_t small_path;       /* 1 = small-problem path: per RK4 stage one launch for the
                                Coulomb and exchange partial sums and one single-workgroup
                                launch for the whole stage epilogue (o*v <= 2048,

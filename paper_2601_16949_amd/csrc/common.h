@@ -198,6 +198,13 @@ hipError_t launch_corr(hipStream_t s, int R, size_t ov, const double *X, const d
 // XGEMM_SCRATCH_MAX bytes' worth of Q values.
 constexpr int XGEMM_O_MIN = 128;
 constexpr size_t XGEMM_SCRATCH_MAX = size_t(2048) << 20;
+constexpr size_t XGEMM_SCRATCH_MID = size_t(256) << 20;  // below o = 128, where 256 MiB hold hundreds of Q
+
+// work of an X-resident exchange workgroup (see shape_xres)
+struct ResShape {
+  int tiles, qs;
+  double q_cycles, start_cycles;
+};
 
 struct ExchangeVariant {
   int precision;  // RTTDA_PREC_*
@@ -216,8 +223,10 @@ struct ExchangeVariant {
   int o_min = 1;
   bool scratch = false;  // needs the W scratch region of the workspace
   int rank = 0;          // preference among variants of equal tile waste (higher first)
+  int v_max = 1 << 30;
+  void (*res)(int v, int ns, struct ResShape *) = nullptr;  // X resident in LDS (one workgroup fills a CU)
   bool applies(int o, int v) const {
-    return o <= o16 && o >= o_min && v >= v_min && v % v_mod == 0 && o % o_mod == 0;
+    return o <= o16 && o >= o_min && v >= v_min && v <= v_max && v % v_mod == 0 && o % o_mod == 0;
   }
 };
 

@@ -1,0 +1,543 @@
+// Exchange contraction with X resident in LDS (both precisions):
+//   P[split][s][i][c] = scale * sum_{Q in split} (B_oo^Q X_s B_vv^Q)[i][c]
+//
+// Same two products per Q as the other exchange kernels (W = X_s B_vv^Q in matrix-core accumulators,
+// then K += B_oo^Q W with the accumulators as the second operand), for shapes where the padded X of
+// one or a few slices fits the LDS of a CU.  X is then staged once per workgroup, already in operand
+// order, and only the factors move: every wave owns 16-column blocks of the output and a range of
+// Q and reads its own rows of the symmetric B_vv^Q straight into registers, `D` K steps ahead.  No
+// barrier and no LDS write separates the staging from the last Q, so the waves of a SIMD drift apart
+// and one's matrix work covers the other's waits; the kernels that stage both operands through LDS
+// stop all waves at every K chunk for that.
+//
+// Operands travel as 16-byte groups (eight BF16 or four FP32 values).  A K step is four groups: lane
+// (g, n) = (lane / 16, lane % 16) holds one group of row n, which for BF16 is one
+// v_mfma_f32_16x16x32_bf16 and for FP32 four v_mfma_f32_16x16x4_f32.  Which group of the row a lane
+// group g takes is free (X is laid out to match): two K steps (a double step, eight groups, 128 bytes
+// of a row) are loaded as pairs of rows, lanes 2a and 2a + 1 taking 32 contiguous bytes of row 2a in
+// one load and of row 2a + 1 in the other, and the lanes of a pair exchange halves.  (A load with 16
+// bytes per row and lane costs the L1 a lookup per lane: with it the lookups, one a cycle, set the
+// time.)  The last group of a row is the row's last eight (four) values; X's copy of it holds zeros
+// where the group before it has those values already, and zeros in the groups past it.  So any v works,
+// nothing is read outside a row, and no lane is masked (global memory takes rows of any alignment).
+// The K product does the same with rows: the accumulators of lane (g, n) are the W rows it must supply,
+// and X's rows are laid out so that they are consecutive j (eight per pair of 16-row blocks in BF16,
+// four per block in FP32); the last group of j is o's last eight (four) rows with the repeated ones
+// zero.  B_oo^Q fragments are then one load per lane too.
+//
+// What bounds it: in FP32 the matrix cores (busy about 89 % of the time at o60 v400 N_Q1500, 3 RHS: 1660
+// us per launch, where the best LDS-staged tile takes 1870).  In split BF16, whose products are eight
+// times shorter, the L1's lookups of B_vv and B_oo rows and the waits of two waves per SIMD (matrix
+// cores busy about 48 %: 386 us against 536-600).  The Q ranges of a workgroup are long (42 slabs there
+// against 220-357), which the stage epilogue feels: 18 us for 38-51.
+// Odd sizes run like even ones: o37 v277 N_Q743, 2 RHS, split BF16: 86 us (320 for the register-staged
+// tile); o27 v203 N_Q541, 3 RHS, FP32: 124 us (192).
+//
+// Split BF16 as in exchange_bf16.hip: X = X_hi + X_lo (two planes), W likewise, FP32 accumulators.
+#include <algorithm>
+#include <type_traits>
+
+#include "common.h"
+
+namespace rttda {
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef u4 u4_unaligned __attribute__((aligned(2)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef u2 u2_unaligned __attribute__((aligned(2)));
+
+constexpr int NWAVE = 8;                      // waves per workgroup, two per SIMD
+constexpr size_t LDS_MAX = (size_t)160 << 10;  // a CU's LDS
+
+// BF: split BF16 (else FP32); JB 16-row blocks per slice, KS slices per workgroup, at most NCBM column
+// blocks per wave
+template <bool BF, int JB, int KS, int NCBM>
+struct CfgR {
+  static constexpr int RB = JB * KS;
+  static constexpr int PL = BF ? 2 : 1;           // planes of X
+  static constexpr int GV = BF ? 8 : 4;           // values per 16-byte group
+  static constexpr int SZ = BF ? 2 : 4;           // bytes per factor value
+  static constexpr int STEP_LDS = RB * PL * 1024;  // bytes of X per K step
+  static constexpr int VMAX = (int)(LDS_MAX / STEP_LDS) * 4 * GV;
+};
+
+// How a workgroup's waves share the columns and its Q range.  Its column tile's blocks go to ncg groups
+// of waves, the first `wide` of them one block wider, and each group's Q range to qs waves.  rem: the
+// last rem blocks of the tile are left to a second phase, in which all eight waves take an eighth of
+// the Q range each.
+struct Split {
+  int nct, ncg, qs, rem;
+};
+
+// first block and width of column group cg in a tile of nb blocks (rem of them left out)
+__host__ __device__ inline void group_blocks(int nb, int rem, int ncg, int cg, int &b0, int &w) {
+  const int base = (nb - rem) / ncg, wide = (nb - rem) % ncg;
+  b0 = cg * base + (cg < wide ? cg : wide);
+  w = base + (cg < wide ? 1 : 0);
+}
+__host__ __device__ inline int tile_block(int nblk, int nct, int ct) { return (int)((long long)ct * nblk / nct); }
+
+// The split with the least matrix work per Q on the fullest SIMD (waves w and w + 4 share one).  A
+// wave's X reads are spread over its width, so narrow groups cost more than their matrix work: a
+// single block per wave is bound by the LDS at about twice its matrix time, two at about 1.1 times.
+// Depends on v alone, so that a batch and a single right-hand side sum alike.
+inline Split choose_split(int v, int ncbm) {
+  const int nblk = (v + 15) / 16;
+  auto cost = [](int w) { return w == 1 ? 2.0 : w == 2 ? 2.2 : (double)w; };
+  Split s{0, 0, 0, 0};
+  double best = 1e300;
+  for (int nct = 1; nct <= nblk; ++nct) {
+    const int nb = nblk - tile_block(nblk, nct, nct - 1);  // the last tile is the widest
+    for (int ncg = 1; ncg <= NWAVE; ++ncg) {
+      const int qs = NWAVE / ncg;
+      for (int rem = 0; rem <= (qs == 1 ? std::min(ncbm, nb - 1) : 0); ++rem) {
+        double load[4] = {0, 0, 0, 0};
+        int wmax = 0;
+        for (int w = 0; w < ncg * qs; ++w) {
+          int b0, width;
+          group_blocks(nb, rem, ncg, w % ncg, b0, width);
+          load[w % 4] += width ? cost(width) : 0.0;
+          wmax = std::max(wmax, width);
+        }
+        if (wmax > ncbm) continue;
+        const double c = nct * (std::max(std::max(load[0], load[1]), std::max(load[2], load[3])) / qs +
+                                (rem ? 2.0 * cost(rem) / NWAVE + 0.05 : 0.0));
+        if (c < best - 1e-12) {
+          best = c;
+          s = Split{nct, ncg, qs, rem};
+        }
+      }
+    }
+    if (s.nct > 0 && nct > s.nct) break;  // more tiles than the first count that fits only if they cost less
+  }
+  return s;
+}
+
+// source row of X row slot rs (0 .. 16 JB - 1), or -1 for a row of zeros
+template <bool BF, int JB>
+__device__ __forceinline__ int slot_row(int rs, int o) {
+  const int blk = rs >> 4, gg = (rs >> 2) & 3, t = rs & 3;
+  const bool pair = BF && (blk | 1) < JB;
+  const int w = pair ? 8 : 4;
+  const int j0 = pair ? 32 * (blk >> 1) + 8 * gg : 16 * blk + 4 * gg, e = pair ? t + 4 * (blk & 1) : t;
+  if (j0 + w <= o) return j0 + e;
+  const int j = o - w + e;
+  return j0 < o && j >= j0 ? j : -1;
+}
+
+template <bool BF, int JB, int KS, int NCBM>
+__global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__restrict__ Boo,
+                                                                const char *__restrict__ Bvv,
+                                                                const char *__restrict__ X,
+                                                                const char *__restrict__ Xlo, int o, int v, int nq,
+                                                                int ns, int n_sg, int nct, int ncg, int qs, int rem,
+                                                                int nsplit, float scale, float *__restrict__ P) {
+  using C = CfgR<BF, JB, KS, NCBM>;
+  constexpr int RB = C::RB, PL = C::PL, GV = C::GV, SZ = C::SZ;
+  constexpr int D = 2;                       // double steps of B_vv in flight (three measure the same)
+  constexpr int HA = (RB + 1) / 2;           // row blocks of the first half of a step
+  constexpr int NP = BF ? (JB + 1) / 2 : JB;  // K-product steps: pairs of row blocks (the last may be a single one)
+  extern __shared__ __attribute__((aligned(16))) char ldsr[];
+
+  // XCD-aware logical block id (hardware deals workgroups to the 8 XCDs round robin): slice groups
+  // fastest, so that the workgroups that read the same rows of B_vv^Q run together on one XCD
+  const int total = n_sg * nct * nsplit;
+  const int per_xcd = (int)gridDim.x / 8;
+  const int lb = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if (lb >= total) return;
+  const int sg = lb % n_sg, ct = (lb / n_sg) % nct, sp = lb / (n_sg * nct);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int s_base = sg * KS;
+  const int ng = (v + GV - 1) / GV, nds = (ng + 7) / 8;  // groups per row, double steps
+  const bool odd_k = ng - 8 * (nds - 1) <= 4;             // the last double step is a single one
+  const int nst = 2 * nds - (odd_k ? 1 : 0);              // K steps
+
+  // ---- X of this workgroup's slices into LDS, in operand order (1 KiB per K step, row block, plane)
+  {
+    const int nfrag = nst * RB;
+    const int row = lane >> 2, gl = lane & 3;  // four groups of 16 rows: 64 contiguous bytes per row
+    for (int f = wave; f < nfrag; f += NWAVE) {
+      const int st = f / RB, rb = f - st * RB;
+      const int sl = s_base + rb / JB, j = slot_row<BF, JB>((rb % JB) * 16 + row, o);
+      const int grp = odd_k && st == nst - 1 ? 4 * st + gl : 8 * (st >> 1) + 2 * gl + (st & 1);
+      const bool live = sl < ns && j >= 0 && grp < ng;
+      const int a0 = grp == ng - 1 ? v - GV : GV * grp;  // first value of the group's load
+      const int dup = GV * grp - a0;                     // its leading values the previous group has
+      const size_t off = ((size_t)(live ? sl : 0) * o + (live ? j : 0)) * v + (live ? a0 : 0);
+#pragma unroll
+      for (int p = 0; p < PL; ++p) {
+        u4 x = *reinterpret_cast<const u4_unaligned *>((p ? Xlo : X) + off * SZ);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (BF) {
+            const unsigned lo = live && 2 * e >= dup ? x[e] & 0xffffu : 0u;
+            const unsigned hi = live && 2 * e + 1 >= dup ? x[e] & 0xffff0000u : 0u;
+            x[e] = lo | hi;
+          } else {
+            x[e] = live && e >= dup ? x[e] : 0u;
+          }
+        }
+        *reinterpret_cast<u4 *>(ldsr + ((size_t)f * PL + p) * 1024 + (gl * 16 + row) * 16) = x;
+      }
+    }
+  }
+  __syncthreads();
+
+  const int nblk = (v + 15) / 16;
+  const int t0 = tile_block(nblk, nct, ct), t1 = tile_block(nblk, nct, ct + 1);
+  const int qa0 = (int)((long long)sp * nq / nsplit), qb0 = (int)((long long)(sp + 1) * nq / nsplit);
+
+  // byte offset of this lane's load in the last double step of a row: the row's last group ends at v
+  const int odd = n & 1;
+  const int glast = 8 * (nds - 1) + (odd_k ? (odd ? 8 : g) : 2 * g + odd);
+  const unsigned klast = glast < ng - 1 ? 16u * glast : glast == ng - 1 ? (unsigned)(v - GV) * SZ : 0u;
+
+  // blocks [b0, b0 + NCB) over Q in [qa, qb): part `part` of nparts, whose waves are grp, grp + pstride, ...
+  auto run = [&](auto ncb_tag, int b0, int qa, int qb, int part, int nparts, int grp, int pstride)
+                 __attribute__((always_inline)) {
+    constexpr int NCB = decltype(ncb_tag)::value;
+    f4 K[RB][NCB], W[RB][NCB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) K[a][c] = W[a][c] = f4{0.f, 0.f, 0.f, 0.f};
+    // byte offset of the first of the two rows (columns of the output) this lane loads; the second is
+    // the row after it, or the last one
+    unsigned roff[NCB];
+    const unsigned row_bytes = (unsigned)(v * SZ), row_last = (unsigned)(v - 1) * row_bytes;
+#pragma unroll
+    for (int c = 0; c < NCB; ++c) roff[c] = (unsigned)min((b0 + c) * 16 + (n & ~1), v - 1) * row_bytes;
+    if (qa < qb) {
+      const size_t qstride = (size_t)v * v * SZ;
+      const char *ql = Bvv + (size_t)qa * qstride;  // Q and double step of the next load
+      int lq = qa, lds_ = 0;
+      u4 ring[D][2][NCB];
+      auto load = [&](u4(&B)[2][NCB]) __attribute__((always_inline)) {
+        const unsigned ko = lds_ == nds - 1 ? klast : 128u * lds_ + 32u * g + 16u * odd;
+#pragma unroll
+        for (int c = 0; c < NCB; ++c)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            B[u][c] = *reinterpret_cast<const u4_unaligned *>(
+                ql + (size_t)((u ? min(roff[c] + row_bytes, row_last) : roff[c]) + ko));
+        if (++lds_ == nds) {  // (past the last Q: its rows once more)
+          lds_ = 0;
+          if (++lq < qb) ql += qstride;
+        }
+      };
+      // the pair's exchange: the even lane keeps its half of row 2a and takes the odd lane's, and the
+      // other way round for row 2a + 1; then B[u] holds each lane's own row, step u
+      auto exchange = [&](u4 &B0, u4 &B1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const unsigned send = odd ? B0[e] : B1[e];
+          const unsigned got = __builtin_amdgcn_update_dpp(0u, send, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+          B0[e] = odd ? got : B0[e];
+          B1[e] = odd ? B1[e] : got;
+        }
+      };
+      u4 xa[HA][PL], xb[HA][PL];
+      auto read_x = [&](u4(&F)[HA][PL], int st, int r0, int r1) __attribute__((always_inline)) {
+        const char *b = ldsr + (size_t)st * C::STEP_LDS + lane * 16;
+#pragma unroll
+        for (int r = 0; r < HA; ++r)
+          if (r0 + r < r1)
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+              F[r][p] = *reinterpret_cast<const u4 *>(b + ((r0 + r) * PL + p) * 1024);
+      };
+      auto mfma_w = [&](const u4(&F)[HA][PL], const u4 &B, int c, int r0, int r1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < (BF ? PL : 4); ++p)
+#pragma unroll
+          for (int r = 0; r < HA; ++r)
+            if (r0 + r < r1) {
+              if constexpr (BF)
+                W[r0 + r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf8, F[r][p]), __builtin_bit_cast(bf8, B), W[r0 + r][c], 0, 0, 0);
+              else
+                W[r0 + r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    __builtin_bit_cast(f4, F[r][0])[p], __builtin_bit_cast(f4, B)[p], W[r0 + r][c], 0, 0, 0);
+            }
+      };
+      auto mfma_all = [&](const u4(&F)[HA][PL], const u4(&B)[NCB], int r0, int r1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) mfma_w(F, B[c], c, r0, r1);
+      };
+      // B_oo^Q fragments of K-product step p: row ib 16 + n, the j of this lane's accumulators
+      auto load_o = [&](u4(&F)[JB], int q, int p) __attribute__((always_inline)) {
+        const bool pair = BF && 2 * p + 1 < JB;
+        const int w = pair ? 8 : 4;
+        int ln = lane;  // (once per Q: offsets recomputed rather than held in registers)
+        asm volatile("" : "+v"(ln));
+        const int g = ln >> 4, n = ln & 15;
+        const int j0 = pair ? 32 * p + 8 * g : (BF ? 32 : 16) * p + 4 * g;
+        const int j = j0 + w <= o ? j0 : j0 < o ? o - w : 0;
+        const char *Oq = Boo + (size_t)q * o * o * SZ;
+#pragma unroll
+        for (int ib = 0; ib < JB; ++ib) {
+          const char *src = Oq + (unsigned)((min(ib * 16 + n, o - 1) * o + j) * SZ);
+          if (BF && !pair) {
+            const u2 t = *reinterpret_cast<const u2_unaligned *>(src);
+            F[ib] = u4{t[0], t[1], 0u, 0u};
+          } else {
+            F[ib] = *reinterpret_cast<const u4_unaligned *>(src);
+          }
+        }
+      };
+      // K += B_oo^Q W for K-product step p
+      auto mfma_k = [&](const u4(&F)[JB], int p) __attribute__((always_inline)) {
+        if constexpr (BF) {
+          const bool pair = 2 * p + 1 < JB;
+          u4 w[KS][NCB][2];
+#pragma unroll
+          for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) {
+              bf8 hi, lo;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                if (e >= 4 && !pair) {
+                  hi[e] = lo[e] = (__bf16)0.f;
+                  continue;
+                }
+                const float x = W[s * JB + (pair ? 2 * p + (e >> 2) : 2 * p)][c][e & 3];
+                hi[e] = (__bf16)x;
+                lo[e] = (__bf16)(x - (float)hi[e]);
+              }
+              w[s][c][0] = __builtin_bit_cast(u4, hi);
+              w[s][c][1] = __builtin_bit_cast(u4, lo);
+            }
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int ib = 0; ib < JB; ++ib)
+#pragma unroll
+              for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int c = 0; c < NCB; ++c) {
+                  f4 &k = K[s * JB + ib][c];
+                  if (pair)
+                    k = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, F[ib]),
+                                                                __builtin_bit_cast(bf8, w[s][c][h]), k, 0, 0, 0);
+                  else
+                    k = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                        __builtin_bit_cast(s4v, u2{F[ib][0], F[ib][1]}),
+                        __builtin_bit_cast(s4v, u2{w[s][c][h][0], w[s][c][h][1]}), k, 0, 0, 0);
+                }
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int ib = 0; ib < JB; ++ib)
+#pragma unroll
+              for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int c = 0; c < NCB; ++c)
+                  K[s * JB + ib][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                      __builtin_bit_cast(f4, F[ib])[t], W[s * JB + p][c][t], K[s * JB + ib][c], 0, 0, 0);
+        }
+      };
+
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        load(ring[d]);
+        __builtin_amdgcn_sched_barrier(0);  // (in ring order: the loop's waits count on it)
+      }
+      read_x(xa, 0, 0, HA);
+      int q = qa, ds = 0;
+      u4 of0[JB], of1[JB];
+      // one double step: each half step's X is read behind the other half's products; the ring slot is
+      // refilled D double steps ahead.  A Q's first B_oo^Q fragments are requested before its last
+      // double step's products.
+      auto step = [&](u4(&B)[2][NCB]) __attribute__((always_inline)) {
+        const bool last = ds == nds - 1, two = !(last && odd_k);
+        if (last) load_o(of0, q, 0);
+        if constexpr (HA < RB) read_x(xb, 2 * ds, HA, RB);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) {
+          exchange(B[0][c], B[1][c]);
+          mfma_w(xa, B[0][c], c, 0, HA);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        read_x(xa, two ? 2 * ds + 1 : 0, 0, HA);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (HA < RB) mfma_all(xb, B[0], HA, RB);
+        if (two) {
+          if constexpr (HA < RB) read_x(xb, 2 * ds + 1, HA, RB);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma_all(xa, B[1], 0, HA);
+          __builtin_amdgcn_sched_barrier(0);
+          read_x(xa, last ? 0 : 2 * ds + 2, 0, HA);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (HA < RB) mfma_all(xb, B[1], HA, RB);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load(B);
+        __builtin_amdgcn_sched_barrier(0);
+        ++ds;
+        if (last) {
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            if (p + 1 < NP) load_o(p & 1 ? of0 : of1, q, p + 1);
+            mfma_k(p & 1 ? of1 : of0, p);
+          }
+#pragma unroll
+          for (int a = 0; a < RB; ++a)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) W[a][c] = f4{0.f, 0.f, 0.f, 0.f};
+          ds = 0;
+          ++q;
+          // the two waves of a SIMD take turns at issue priority: the older one, favoured by default,
+          // would finish a quarter earlier and leave the other alone
+          if ((q ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+        }
+      };
+      // (the exits between the slots leave the loop at once: a path on which a slot is skipped would
+      // make the compiler wait for every load in flight)
+      for (;;) {
+        step(ring[0]);
+        if (q >= qb) break;
+        step(ring[1]);
+        if (q >= qb) break;
+      }
+    }
+    int ln = lane;  // (opaque here: addresses made from it would be held in registers through the loop)
+    asm volatile("" : "+v"(ln));
+    auto store = [&](int a, int c, f4 k) __attribute__((always_inline)) {
+      const int sl = s_base + a / JB, col = (b0 + c) * 16 + (ln & 15);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int i = (a % JB) * 16 + 4 * (ln >> 4) + t;
+        if (sl < ns && i < o && col < v) P[(((size_t)sp * ns + sl) * o + i) * v + col] = scale * k[t];
+      }
+    };
+    if (nparts == 1) {
+#pragma unroll
+      for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) store(a, c, K[a][c]);
+      return;
+    }
+    // the parts' sums meet in LDS (X is no longer needed), added in order, the blocks dealt to the parts
+    constexpr int SLOT = RB * NCBM * 1024;
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+      for (int c = 0; c < NCB; ++c)
+        *reinterpret_cast<f4 *>(ldsr + (size_t)wave * SLOT + (a * NCB + c) * 1024 + lane * 16) = K[a][c];
+    __syncthreads();
+    for (int f = part; f < RB * NCB; f += nparts) {
+      f4 k = f4{0.f, 0.f, 0.f, 0.f};
+      for (int p = 0; p < nparts; ++p)
+        k += *reinterpret_cast<const f4 *>(ldsr + (size_t)(p * pstride + grp) * SLOT + f * 1024 + lane * 16);
+      store(f / NCB, f % NCB, k);
+    }
+  };
+  auto go = [&](int w, int b0, int qa, int qb, int part, int nparts, int grp, int pstride)
+                __attribute__((always_inline)) {
+    switch (w) {
+      case 1: run(std::integral_constant<int, 1>{}, b0, qa, qb, part, nparts, grp, pstride); break;
+      case 2: if constexpr (NCBM >= 2) run(std::integral_constant<int, 2>{}, b0, qa, qb, part, nparts, grp, pstride); break;
+      case 3: if constexpr (NCBM >= 3) run(std::integral_constant<int, 3>{}, b0, qa, qb, part, nparts, grp, pstride); break;
+      case 4: if constexpr (NCBM >= 4) run(std::integral_constant<int, 4>{}, b0, qa, qb, part, nparts, grp, pstride); break;
+      case 5: if constexpr (NCBM >= 5) run(std::integral_constant<int, 5>{}, b0, qa, qb, part, nparts, grp, pstride); break;
+      default:  // no columns for this wave: it keeps the barriers
+        if (nparts > 1) {
+          __syncthreads();
+          __syncthreads();
+        }
+        break;
+    }
+  };
+  for (int phase = 0; phase < (rem ? 2 : 1); ++phase) {
+    int cg = wave % ncg, part = wave / ncg, nparts = qs, pstride = ncg, b0 = 0, w = 0;
+    if (phase == 0) {
+      if (part < qs) group_blocks(t1 - t0, rem, ncg, cg, b0, w);
+    } else {
+      cg = 0, part = wave, nparts = NWAVE, pstride = 1, b0 = t1 - t0 - rem, w = rem;
+    }
+    const int qa = qa0 + (int)((long long)part * (qb0 - qa0) / nparts);
+    const int qb = qa0 + (int)((long long)(part + 1) * (qb0 - qa0) / nparts);
+    go(w, t0 + b0, qa, qb, part, nparts, cg, pstride);
+  }
+}
+
+template <bool BF, int JB, int KS, int NCBM>
+hipError_t launch_xres(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o, int v,
+                       int nq, int ns, int nsplit, float scale, float *P, void *, size_t) {
+  using C = CfgR<BF, JB, KS, NCBM>;
+  if (o > 16 * JB || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || nsplit > nq)
+    return hipErrorInvalidValue;
+  const Split sp = choose_split(v, NCBM);
+  const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;  // K steps
+  const size_t lds = std::max((size_t)nst * C::STEP_LDS, sp.qs > 1 || sp.rem ? (size_t)NWAVE * C::RB * NCBM * 1024 : (size_t)0);
+  if (lds > LDS_MAX) return hipErrorInvalidValue;
+  const int n_sg = (ns + KS - 1) / KS;
+  const int total = n_sg * sp.nct * nsplit;
+  const dim3 grid((total + 7) / 8 * 8);
+  hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM>), grid, dim3(64 * NWAVE), lds, s,
+                     static_cast<const char *>(Boo), static_cast<const char *>(Bvv), static_cast<const char *>(X),
+                     static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, nsplit,
+                     scale, P);
+  return hipGetLastError();
+}
+
+template <bool BF, int JB, int KS, int NCBM>
+hipError_t prepare_xres() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+}
+
+// What auto_splits needs of a shape: workgroups per Q split, Q subranges per workgroup, and the cycles
+// of a workgroup per Q (of one subrange) and before its first.
+template <bool BF, int JB, int KS, int NCBM>
+void shape_xres(int v, int ns, ResShape *r) {
+  using C = CfgR<BF, JB, KS, NCBM>;
+  const Split sp = choose_split(v, NCBM);
+  const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;
+  const double per_block = (double)nst * C::RB * (BF ? 2 * 16 : 4 * 32) +
+                           (BF ? 2 * 16 * ((JB + 1) / 2) : 4 * 32 * JB) * (double)C::RB;  // matrix cycles per Q
+  const int nb = ((v + 15) / 16 + sp.nct - 1) / sp.nct;
+  r->tiles = (ns + KS - 1) / KS * sp.nct;
+  r->qs = sp.qs;
+  // (a wave of two row blocks waits longer for its operands per product than one of three or four)
+  r->q_cycles = per_block * ((nb + sp.ncg - 1) / sp.ncg) * 2 / (BF ? (C::RB > 2 ? 0.45 : 0.35) : 0.85);
+  r->start_cycles = 5000.0 + nst * C::STEP_LDS / 40.0;
+}
+
+// Column blocks per wave: as many as keep the accumulators, the ring and two halves of a step's X
+// within (about) the 256 registers of two waves per SIMD.
+#define XRES(BF, JB, KS, NCBM, NAME)                                                                               \
+  ExchangeVariant {                                                                                                \
+    BF ? RTTDA_PREC_MIXED_BF16 : RTTDA_PREC_FP32, 16 * JB, KS, 16 * NWAVE * NCBM, NAME, &launch_xres<BF, JB, KS, NCBM>, \
+        LDS_MAX, &prepare_xres<BF, JB, KS, NCBM>, CfgR<BF, JB, KS, NCBM>::GV, 1, 1, JB > 1 ? 8 : 4, false, 3,      \
+        CfgR<BF, JB, KS, NCBM>::VMAX, &shape_xres<BF, JB, KS, NCBM>                                                \
+  }
+
+const ExchangeVariant kResF32[] = {
+    XRES(false, 4, 1, 4, "f32r_o64"), XRES(false, 3, 1, 4, "f32r_o48"), XRES(false, 2, 2, 4, "f32r_o32_s2"),
+    XRES(false, 2, 1, 5, "f32r_o32_s1"), XRES(false, 1, 2, 5, "f32r_o16_s2"),
+};
+const ExchangeVariant kResBf16[] = {
+    XRES(true, 4, 1, 4, "bf16x2r_o64"), XRES(true, 3, 1, 4, "bf16x2r_o48"), XRES(true, 2, 2, 4, "bf16x2r_o32_s2"),
+    XRES(true, 2, 1, 5, "bf16x2r_o32_s1"), XRES(true, 1, 2, 5, "bf16x2r_o16_s2"),
+};
+
+}  // namespace
+
+int exchange_res_variant_count(int prec) {
+  return prec == RTTDA_PREC_FP32 ? (int)(sizeof(kResF32) / sizeof(kResF32[0])) : (int)(sizeof(kResBf16) / sizeof(kResBf16[0]));
+}
+const ExchangeVariant *exchange_res_variant(int prec, int k) {
+  return prec == RTTDA_PREC_FP32 ? &kResF32[k] : &kResBf16[k];
+}
+
+}  // namespace rttda

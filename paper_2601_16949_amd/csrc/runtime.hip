@@ -22,6 +22,8 @@ int exchange_bf16dl_variant_count();
 const ExchangeVariant *exchange_bf16dl_variant(int k);
 int exchange_gemm_variant_count();
 const ExchangeVariant *exchange_gemm_variant(int k);
+int exchange_res_variant_count(int prec);
+const ExchangeVariant *exchange_res_variant(int prec, int k);
 }  // namespace rttda
 
 using namespace rttda;
@@ -118,7 +120,7 @@ Layout make_layout(int o, int v, int nq, int R, int prec, size_t slab_bytes = SK
   if (gemm_scratch && prec == RTTDA_PREC_MIXED_BF16 && nq > 0 && o >= XGEMM_O_MIN && o <= 256 && o % 8 == 0 &&
       v % 8 == 0) {
     const size_t per_q = (size_t)v * ns * o * 4;  // W hi + lo for one Q at the largest RHS count
-    L.scratch_bytes = std::min((size_t)nq * per_q, std::max(per_q, XGEMM_SCRATCH_MAX));
+    L.scratch_bytes = std::min((size_t)nq * per_q, std::max(per_q, o >= 128 ? XGEMM_SCRATCH_MAX : XGEMM_SCRATCH_MID));
   }
   L.scratch = take(L.scratch_bytes);
   L.lz = take(3 * ov * 8);
@@ -199,14 +201,16 @@ struct GraphEntry {
   hipGraphExec_t exec = nullptr;
 };
 
-// Variant tables: register-staged variants first, then direct-to-LDS variants
+// Variant tables: register-staged variants first, then direct-to-LDS, GEMM and X-resident variants
 const ExchangeVariant *variant_of(int prec, int k) {
   if (k < 0) return nullptr;
   if (prec == RTTDA_PREC_FP32) {
     const int n1 = exchange_f32_variant_count();
     if (k < n1) return exchange_f32_variant(k);
     k -= n1;
-    return k < exchange_f32dl_variant_count() ? exchange_f32dl_variant(k) : nullptr;
+    if (k < exchange_f32dl_variant_count()) return exchange_f32dl_variant(k);
+    k -= exchange_f32dl_variant_count();
+    return k < exchange_res_variant_count(prec) ? exchange_res_variant(prec, k) : nullptr;
   }
   const int n2 = exchange_bf16_variant_count();
   if (k < n2) return exchange_bf16_variant(k);
@@ -214,12 +218,15 @@ const ExchangeVariant *variant_of(int prec, int k) {
   const int n3 = exchange_bf16dl_variant_count();
   if (k < n3) return exchange_bf16dl_variant(k);
   k -= n3;
-  return k < exchange_gemm_variant_count() ? exchange_gemm_variant(k) : nullptr;
+  if (k < exchange_gemm_variant_count()) return exchange_gemm_variant(k);
+  k -= exchange_gemm_variant_count();
+  return k < exchange_res_variant_count(prec) ? exchange_res_variant(prec, k) : nullptr;
 }
 int variant_count(int prec) {
   return prec == RTTDA_PREC_FP32
-             ? exchange_f32_variant_count() + exchange_f32dl_variant_count()
-             : exchange_bf16_variant_count() + exchange_bf16dl_variant_count() + exchange_gemm_variant_count();
+             ? exchange_f32_variant_count() + exchange_f32dl_variant_count() + exchange_res_variant_count(prec)
+             : exchange_bf16_variant_count() + exchange_bf16dl_variant_count() + exchange_gemm_variant_count() +
+                   exchange_res_variant_count(prec);
 }
 // a variant runs on a context when it holds the shape and, if it needs one, the workspace has scratch
 bool usable(const ExchangeVariant *x, int o, int v, const Layout &L) {
@@ -238,6 +245,10 @@ struct rttda_ctx {
   // launch configuration
   int xvar = -1;  // 0-based exchange variant
   int sk = 0, sj = 0;
+  // exchange splits of launches on one plane per RHS (split operator) and on one slice (Lanczos): an
+  // X-resident variant's workgroups fill the CUs in whole rounds, so fewer slices take more splits.
+  // Equal to sk for the other variants and once a tile or split count has been chosen by the caller.
+  int sk_real = 0, sk_one = 0;
   int use_graph = 1, steps_per_graph = 8;
   int qchunk = 0;  // Q per chunk of the GEMM exchange path, 0 = as many as the scratch holds
   // second stream for the Coulomb pair, which then runs alongside the exchange (HBM-bound next to
@@ -245,6 +256,7 @@ struct rttda_ctx {
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   int overlap = 2;  // 1: Coulomb pair on the second stream, 2: in order on the context's stream
+  bool overlap_set = false;  // chosen by the caller (else it follows the exchange variant)
   // small problems: the stage's Coulomb + exchange slabs in one launch (small_splits slabs) and the
   // RK4 stage epilogue in one single-workgroup launch
   int small = 0, small_splits = 0;
@@ -332,13 +344,50 @@ rttda_status validate_desc(const rttda_desc *d, bool need_ptrs) {
   return RTTDA_OK;
 }
 
-int auto_variant(int prec, int o, int ns, int v, const Layout &L) {
+// Split count of an X-resident variant (one workgroup per CU at a time): the least time in whole
+// rounds of workgroups, plus the epilogue's read of the slabs (about 1900 bytes a cycle over the chip,
+// and 60 cycles a slab for the chain of its loads).  *cycles receives that time.
+int resident_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap, double *cycles) {
+  ResShape r;
+  x->res(v, ns, &r);
+  int best = 1;
+  *cycles = 1e300;
+  for (int s = 1; s <= std::min(cap, nq); ++s) {
+    const double rounds = std::ceil((double)r.tiles * s / 256.0);
+    const double q = std::ceil(std::ceil((double)nq / s) / r.qs);
+    const double t = rounds * (q * r.q_cycles + r.start_cycles) + s * (60.0 + 2.0 * 4 * ns * o * v / 1900.0);
+    if (t < *cycles) {
+      *cycles = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
+int auto_variant(int prec, int o, int ns, int v, int nq, const Layout &L) {
   const int n = variant_count(prec);
   // the large-o GEMM path first whenever the workspace carries its scratch
   for (int k = 0; k < n; ++k) {
     const ExchangeVariant *x = variant_of(prec, k);
     if (x->scratch && usable(x, o, v, L)) return k;
   }
+  // then X resident in LDS wherever it fits: on every shape tried (o 12..64, v 56..800, 1..64 RHS, both
+  // precisions) as fast as the best of the others or faster, e.g. o60 v400 N_Q1500, 3 RHS: 386 against
+  // 536 us (split BF16) and 1660 against 1870 us (FP32) per launch; o40 v300 N_Q1000, 32 RHS: 1.21
+  // against 6.67 ms and 5.21 against 6.57 ms; among its tiles the one with the least estimated time
+  int res = -1;
+  double res_cycles = 1e300;
+  for (int k = 0; k < n; ++k) {
+    const ExchangeVariant *x = variant_of(prec, k);
+    if (!x->res || !x->applies(o, v)) continue;
+    double t;
+    resident_splits(x, o, ns, v, nq, L.sk_max, &t);
+    if (t < res_cycles) {
+      res_cycles = t;
+      res = k;
+    }
+  }
+  if (res >= 0) return res;
   // else the smallest padded occupied size that holds o; among those prefer the variant whose
   // tile wastes the least of the (slices x columns) space, then the larger tile, then the
   // variant's rank (the pipelined direct-to-LDS kernels over the plain ones over the register ones).
@@ -374,6 +423,10 @@ int auto_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap,
     const int tiles_b = ns * ((v + 127) / 128);
     int s = (512 + tiles_b - 1) / tiles_b;
     return std::max(1, std::min({s, std::max(1, qc / 2), cap}));
+  }
+  if (x->res) {
+    double t;
+    return resident_splits(x, o, ns, v, nq, cap, &t);
   }
   const int tiles = ((ns + x->ks - 1) / x->ks) * ((v + x->nt - 1) / x->nt);
   const int cus = 256;
@@ -414,9 +467,34 @@ size_t scratch_for(const rttda_ctx *ctx, int ns) {
   return qc * (size_t)ctx->v * ns * ctx->o * 4;
 }
 
+// What a launch's slices are: both planes of every RHS (RK4, sigma, Davidson batches), one plane per
+// RHS (split operator) or a single vector (Lanczos).  The split count goes by this and the context's
+// largest RHS count, not by the call's, so that a batch and a single RHS sum alike.
+enum Slices { SL_COMPLEX, SL_REAL, SL_ONE };
+
+int exchange_splits(const rttda_ctx *ctx, Slices k) {
+  return k == SL_COMPLEX ? ctx->sk : k == SL_REAL ? ctx->sk_real : ctx->sk_one;
+}
+
+// Default splits of the current variant, and whether the Coulomb pair runs alongside it: only where
+// the exchange is long enough to cover the cost of the fork and join (small problems and many
+// concurrent contexts lose), and not next to an X-resident variant, whose workgroups leave no
+// registers for others on their CU.
+void default_launch(rttda_ctx *ctx) {
+  const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  const int cap = ctx->L.sk_max;
+  ctx->sk = auto_splits(x, ctx->o, 2 * ctx->R, ctx->v, ctx->nq, cap, ctx->L);
+  ctx->sk_real = x->res ? auto_splits(x, ctx->o, ctx->R, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
+  ctx->sk_one = x->res ? auto_splits(x, ctx->o, 1, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
+}
+void default_overlap(rttda_ctx *ctx) {
+  const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  const double flops = 4.0 * ctx->nq * (double)ctx->ov * (ctx->o + ctx->v) * ctx->R;
+  ctx->overlap = !x->res && flops >= OVERLAP_MIN_FLOPS ? 1 : 2;
+}
+
 // Coulomb + exchange partials for the current stage input (x32 or xhi/xlo), `ns` real slices
-// (2 per RHS for the complex RK4 stages, 1 per RHS for the split-operator half steps).
-rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns) {
+rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPLEX) {
   if (ctx->nq == 0) return RTTDA_OK;
   const int ov = (int)ctx->ov;
   hipStream_t s = ctx->stream;
@@ -451,14 +529,16 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns) {
   const void *X = ctx->prec == RTTDA_PREC_FP32 ? (const void *)ctx->x32() : (const void *)ctx->xhi();
   const void *Xlo = ctx->prec == RTTDA_PREC_FP32 ? nullptr : (const void *)ctx->xlo();
   if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
-  HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, ctx->sk, (float)(-ctx->d.cx),
-                    Pk, ctx->scratch(), scratch_for(ctx, ns)));
+  HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, exchange_splits(ctx, kind),
+                    (float)(-ctx->d.cx), Pk, ctx->scratch(), scratch_for(ctx, ns)));
   if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
   if (fork) HIP_TRY(hipStreamWaitEvent(s, ctx->ev_join, 0));  // join before any reader of the slabs
   return RTTDA_OK;
 }
 
-int nslab(const rttda_ctx *ctx) { return ctx->nq > 0 ? (ctx->small ? ctx->small_splits : ctx->sj + ctx->sk) : 0; }
+int nslab(const rttda_ctx *ctx, Slices kind = SL_COMPLEX) {
+  return ctx->nq > 0 ? (ctx->small ? ctx->small_splits : ctx->sj + exchange_splits(ctx, kind)) : 0;
+}
 
 // the small path applies to the shape (o v and the RHS count within its single-workgroup limits)
 bool small_fits(int o, int v, int R) { return small_shape_ok(o, v) && R <= SMALL_R_MAX; }
@@ -533,7 +613,7 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
   if (pops) HIP_TRY(launch_pop(s, nrhs, ctx->ov, c, ctx->state()));
   if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
   for (int half = 0; half < 2; ++half) {  // 0: drift (stage node 1/2), 1: kick (node 1)
-    if ((st = enqueue_two_electron(ctx, nrhs)) != RTTDA_OK) return st;
+    if ((st = enqueue_two_electron(ctx, nrhs, SL_REAL)) != RTTDA_OK) return st;
     if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
     if (has_field)
       HIP_TRY(launch_field(s, W, W0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
@@ -541,7 +621,7 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
       HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, half == 0 ? 1 : 3,
                             (has_field ? SM_EFIELD : 0) | (half == 1 ? SM_INC : 0), dt, ctx->pulses(), ctx->state(),
                             ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
-    HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, o, v, nslab(ctx), half == 0 ? SSO_DRIFT : SSO_KICK,
+    HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, o, v, nslab(ctx, SL_REAL), half == 0 ? SSO_DRIFT : SSO_KICK,
                               has_field ? 1 : 0, dt, ctx->D(), ctx->P(), ctx->F(), ctx->sc(), c, c0, W, W0, ctx->x32(),
                               ctx->xhi(), ctx->xlo()));
     if (pr) HIP_TRY(ctx->prof.end(PC_EPILOGUE, s));
@@ -553,13 +633,13 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
 rttda_status enqueue_sso_start(rttda_ctx *ctx, int nrhs, double dt, bool has_field, double *c0, double *c) {
   hipStream_t s = ctx->stream;
   HIP_TRY(launch_plane_copy(s, ctx->prec, nrhs, ctx->ov, 0, c, ctx->x32(), ctx->xhi(), ctx->xlo()));
-  rttda_status st = enqueue_two_electron(ctx, nrhs);
+  rttda_status st = enqueue_two_electron(ctx, nrhs, SL_REAL);
   if (st != RTTDA_OK) return st;
   if (has_field)
     HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part()));
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, has_field ? SM_EFIELD : 0, dt, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
-  HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
+  HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx, SL_REAL), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
                             ctx->D(), ctx->P(), ctx->F(), ctx->sc(), c, c0, ctx->xs64(), ctx->xs0(), ctx->x32(),
                             ctx->xhi(), ctx->xlo()));
   return RTTDA_OK;
@@ -779,7 +859,7 @@ rttda_status rttda_create(const rttda_desc *desc, rttda_ctx **out) {
   const int ns_max = 2 * desc->max_rhs;
   int xv = -1;
   if (desc->n_aux > 0) {
-    xv = auto_variant(desc->precision, desc->n_occ, ns_max, desc->n_virt, L);
+    xv = auto_variant(desc->precision, desc->n_occ, ns_max, desc->n_virt, desc->n_aux, L);
     if (xv < 0)
       return fail(RTTDA_E_UNSUPPORTED, "no exchange kernel for o=%d in precision %d", desc->n_occ, desc->precision);
   }
@@ -798,11 +878,9 @@ rttda_status rttda_create(const rttda_desc *desc, rttda_ctx **out) {
   ctx->ws = static_cast<char *>(desc->workspace);
   ctx->xvar = xv;
   if (desc->n_aux > 0) {
-    ctx->sk = auto_splits(variant_of(ctx->prec, xv), ctx->o, ns_max, ctx->v, ctx->nq, L.sk_max, L);
+    default_launch(ctx);
     ctx->sj = L.sj_max;
-    // the Coulomb pair runs alongside the exchange only where the exchange is long enough to
-    // cover the cost of the fork and join (small problems and many concurrent contexts lose)
-    ctx->overlap = 4.0 * ctx->nq * (double)ctx->ov * (ctx->o + ctx->v) * ctx->R >= OVERLAP_MIN_FLOPS ? 1 : 2;
+    default_overlap(ctx);
     // the small path: at most 2e9 exchange flops per stage (a few tens of microseconds of FP32 FMA);
     // up to SMALL_SPLITS Q ranges (the epilogue adds one slab per range)
     ctx->small_splits = std::max(1, std::min({SMALL_SPLITS, ctx->nq, L.sj_max + L.sk_max}));
@@ -902,14 +980,16 @@ rttda_status rttda_set_tuning(rttda_ctx *ctx, const rttda_tuning *t) {
   if (t->exchange_chunk < -1) return fail(RTTDA_E_INVAL, "exchange_chunk must be -1, 0 or positive");
   if (ctx->nq > 0) {
     ctx->xvar = xv;
-    ctx->sk = sk;
+    if (t->exchange_variant || t->exchange_splits) ctx->sk = ctx->sk_real = ctx->sk_one = sk;
     ctx->sj = sj;
+    if (!ctx->overlap_set) default_overlap(ctx);
   }
   if (t->exchange_chunk) ctx->qchunk = t->exchange_chunk < 0 ? 0 : t->exchange_chunk;
   if (t->use_graph) ctx->use_graph = t->use_graph;
   if (t->overlap) {
     if (t->overlap != 1 && t->overlap != 2) return fail(RTTDA_E_INVAL, "overlap must be 0, 1 or 2");
     ctx->overlap = t->overlap;
+    ctx->overlap_set = true;
   }
   // an explicit exchange tile or split count asks for the general kernels
   if ((t->exchange_variant || t->exchange_splits) && !t->small_path) ctx->small = 0;
@@ -1307,9 +1387,9 @@ rttda_status rttda_spectral_radius(rttda_ctx *ctx, int32_t n_iter, double *rho, 
   double bj = 0.0, blast = 0.0;
   const int kmax = (int)std::min<long long>(n_iter, n);
   for (int j = 0; j < kmax; ++j) {
-    if (ctx->nq > 0 && (st = enqueue_two_electron(ctx, 1)) != RTTDA_OK) return st;
+    if (ctx->nq > 0 && (st = enqueue_two_electron(ctx, 1, SL_ONE)) != RTTDA_OK) return st;
     double aj = 0.0, b2 = 0.0;
-    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx), ctx->D(), ctx->P(), v, vprev, bj, w, part));
+    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx, SL_ONE), ctx->D(), ctx->P(), v, vprev, bj, w, part));
     if ((st = host_sum(aj)) != RTTDA_OK) return st;
     HIP_TRY(launch_lz_orth(hs, n, v, aj, w, part));
     if ((st = host_sum(b2)) != RTTDA_OK) return st;
@@ -1765,7 +1845,7 @@ extern "C" rttda_status rttda_sigma_noalloc(const rttda_desc *desc, int32_t nrhs
                 o, v, nq, nrhs, L.total, NOALLOC_BYTES);
   int xv = -1;
   if (nq > 0) {
-    xv = auto_variant(prec, o, 2 * nrhs, v, L);  // no W scratch here, so never the large-o GEMM path
+    xv = auto_variant(prec, o, 2 * nrhs, v, nq, L);  // no W scratch here, so never the large-o GEMM path
     if (xv < 0) return fail(RTTDA_E_UNSUPPORTED, "no exchange kernel for o=%d in precision %d", o, prec);
   }
   void *base = nullptr;
@@ -1787,7 +1867,7 @@ extern "C" rttda_status rttda_sigma_noalloc(const rttda_desc *desc, int32_t nrhs
   ctx.xvar = xv;
   ctx.overlap = 2;
   if (nq > 0) {
-    ctx.sk = auto_splits(variant_of(prec, xv), o, 2 * nrhs, v, nq, L.sk_max, L);
+    default_launch(&ctx);
     ctx.sj = L.sj_max;
   }
   // directions and field strengths: host arrays copied into the scratch, waited for before they
