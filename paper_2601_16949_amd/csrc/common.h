@@ -22,6 +22,8 @@ struct DevPulse {
 // Device-resident propagation scalars.
 struct DevState {
   long long step;      // absolute step index of the current state c
+  long long pend;      // 1: the step's last epilogue has run and `step` is still the old one (the next
+                       // field product adds it: the epilogue's own blocks read `step`)
   long long step0;     // step index at the start of the current propagate call
   long long bad_step;  // first step at which the norm guard tripped, -1 if none
   long long keep_ref;  // 1: the call resumes a run (the guard's reference norm and first bad step
@@ -72,7 +74,7 @@ inline int field_blocks_i(int o) { return (o + FT_I - 1) / FT_I; }
 enum : int {
   SM_TRACE = 1,     // write trace/norm samples at index step - step0, update the guard
   SM_C0 = 2,        // RK4 stage update of c0 with k0 = i E g
-  SM_INC = 4,       // step += 1 once the stage is done
+  SM_INC = 4,       // the step is done: `pend`
   SM_EFIELD = 8,    // E = pulse field at (step + node) dt (else E = 0 unless SM_KEEP_E)
   SM_SIGMA0 = 16,   // s0 = -E g with E preset by the host
   SM_OUT = 32,      // out[r] = <X|M|X>  (dipole_trace entry point)
@@ -119,13 +121,13 @@ hipError_t launch_gaps(hipStream_t s, const double *e_occ, const double *e_virt,
 hipError_t launch_to_f32(hipStream_t s, const double *c, long long n, float *x32);
 hipError_t launch_to_bf16x2(hipStream_t s, const double *c, long long n, float *x32, __hip_bfloat16 *hi,
                             __hip_bfloat16 *lo);
-// Coulomb first product in `nes` ia chunks (partials dpart[nes][nq][ns], summed into slot 0 when
-// nes > 1, which is d for the second product); gemv1_chunks picks nes (at most GEMV1_CHUNKS_MAX).
+// Coulomb first product in `nes` ia chunks (partials dpart[nes][nq][ns], which the second product
+// adds); gemv1_chunks picks nes (at most GEMV1_CHUNKS_MAX).
 constexpr int GEMV1_CHUNKS_MAX = 16;
 int gemv1_chunks(int nq, int ov);
 hipError_t launch_gemv1(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns, int nes,
                         float *dpart);
-hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *dvec, int nq, int ov, int ns,
+hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *dpart, int nes, int nq, int ov, int ns,
                         int nsplit, float *P);
 // The same pair on the FP32 matrix cores for batches of many slices (the context's 2 max_rhs >= 32):
 // d in nes ia chunks (coulomb_mfma_chunks, at most GEMV1_CHUNKS_MAX) summed into chunk slot 0 of
@@ -134,15 +136,24 @@ int coulomb_mfma_chunks(int nq, int ov);
 hipError_t launch_coulomb_mfma(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns,
                                int nes, int nsplit, float *dpart, float *P);
 hipError_t launch_field(hipStream_t s, const double *X, const double *X0, const double *moo, const double *mov,
-                        const double *mvv, int o, int v, int R, double *F, double *part);
+                        const double *mvv, int o, int v, int R, double *F, double *part, DevState *st);
 hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, double dt, const DevPulse *pulses,
                          DevState *st, const double *part, double *sc, double *c0, double *acc0, double *xs0,
                          double *out, double *normref, double *s0);
+// The stage scalars an RK4 epilogue carries (mode: SM_TRACE, SM_C0, SM_INC, SM_EFIELD, SM_ENERGY; 0 for none)
+struct StageScalars {
+  int mode, nbf;
+  const DevPulse *pulses;
+  DevState *st;
+  const double *part;
+  double *c0, *acc0, *xs0, *normref;
+};
 // epart != NULL: also the per-block partial sums of <X, A X> per RHS ([R][epilogue_blocks(ov)])
 hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, int nslab, int stage, int mode,
-                           int use_field, double dt, const double *D, const float *P, const double *F,
-                           const double *sc, const double *Xin, double *c, double *acc, double *xs64, float *x32,
-                           __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, double *s_out, double *epart = nullptr);
+                           int use_field, double dt, const double *D, const float *P, const double *F, double *sc,
+                           const double *Xin, double *c, double *acc, double *xs64, float *x32, __hip_bfloat16 *xhi,
+                           __hip_bfloat16 *xlo, double *s_out, double *epart = nullptr,
+                           const StageScalars *scalars = nullptr);
 hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, int nslab, int mode, int use_field,
                              double dt, const double *D, const float *P, const double *F, const double *sc, double *c,
                              double *c0, double *W, double *W0, float *x32, __hip_bfloat16 *xhi,

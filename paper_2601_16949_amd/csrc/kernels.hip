@@ -73,17 +73,13 @@ __global__ void k_to_bf16x2(const double *__restrict__ c, long long n, float *__
 // ------------------------------------------------------------------------------------------------
 // Coulomb, first product: d[Q][s] = sum_ia B_ov[Q][ia] X[s][ia]   (B streamed once from HBM)
 // Block = QT rows of B x ST slices x one ia chunk; the chunk partials dpart[chunk][Q][s] are summed
-// in a fixed order by the second product.  Vector path: 4 consecutive ia per lane and load (needs
-// ov % 4 == 0 so that every B row starts 16/8-byte aligned); scalar path otherwise.
+// in a fixed order by the second product.  Each lane takes EPL consecutive ia per load (16 bytes of B
+// where ov is a multiple of those values, so that every row starts aligned); rows of other lengths are
+// read one value per lane and load, four loads per row in flight (o27 v203 N_Q541 FP32, 3 RHS: 7.7 us;
+// with one in flight 30.5 us).
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ float4 load_b4(const float *p, size_t i) {
-  return *reinterpret_cast<const float4 *>(p + i);
-}
-__device__ __forceinline__ float4 load_b4(const __hip_bfloat16 *p, size_t i) {
-  const uint2 u = *reinterpret_cast<const uint2 *>(p + i);  // element 2k in the low half of word k
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
-                     __uint_as_float(u.y & 0xffff0000u));
-}
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u4u __attribute__((ext_vector_type(4), aligned(2)));
 
 // Sum 64 per-lane values over the wave with 63 exchanges: at each halving step a lane keeps the
 // half of its values selected by its lane bit and adds the partner's copy of that half.  On exit
@@ -105,34 +101,37 @@ __device__ __forceinline__ float wave_transpose_sum64(float (&v)[64], int lane) 
   return v[0];
 }
 
-// One 16-byte load of a B row: EPL values widened to FP32 (FP32: four; BF16: four from an 8-byte load,
-// or eight)
+// One 16-byte load of a B row: EPL values widened to FP32
 template <int EPL>
 __device__ __forceinline__ void load_row(const float *p, size_t i, float (&x)[EPL]) {
   static_assert(EPL == 4, "FP32 rows: four values per 16-byte load");
-  const float4 t = *reinterpret_cast<const float4 *>(p + i);
-  x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
+  const f4u t = *reinterpret_cast<const f4u *>(p + i);
+  x[0] = t[0], x[1] = t[1], x[2] = t[2], x[3] = t[3];
 }
 template <int EPL>
 __device__ __forceinline__ void load_row(const __hip_bfloat16 *p, size_t i, float (&x)[EPL]) {
   static_assert(EPL == 4 || EPL == 8, "BF16 rows: four or eight values per load");
-  if constexpr (EPL == 4) {
-    const float4 t = load_b4(p, i);
-    x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
+  typedef unsigned u2u __attribute__((ext_vector_type(2), aligned(2)));
+  unsigned w[EPL / 2];  // element 2k in the low half of word k
+  if constexpr (EPL == 8) {
+    const u4u u = *reinterpret_cast<const u4u *>(p + i);
+    w[0] = u[0], w[1] = u[1], w[2] = u[2], w[3] = u[3];
   } else {
-    const uint4 u = *reinterpret_cast<const uint4 *>(p + i);  // element 2k in the low half of word k
-    const unsigned w[4] = {u.x, u.y, u.z, u.w};
+    const u2u u = *reinterpret_cast<const u2u *>(p + i);
+    w[0] = u[0], w[1] = u[1];
+  }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      x[2 * k] = __uint_as_float(w[k] << 16);
-      x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
-    }
+  for (int k = 0; k < EPL / 2; ++k) {
+    x[2 * k] = __uint_as_float(w[k] << 16);
+    x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
   }
 }
+template <typename TB>
+constexpr int row_epl() {
+  return 16 / (int)sizeof(TB);
+}
 
-// VEC: EPL consecutive ia per lane and load (4: 16 bytes of FP32 or 8 of BF16; 8: 16 bytes of BF16,
-// needs ov % 8 == 0); scalar path otherwise
-template <typename TB, int QT, int ST, bool VEC, int EPL = 4>
+template <typename TB, int QT, int ST, int EPL>
 __global__ __launch_bounds__(256) void k_gemv1(const TB *__restrict__ B, const float *__restrict__ X, int nq, int ov,
                                                int ns, int echunk, float *__restrict__ dpart) {
   static_assert(QT * ST <= 64, "one reduced value per lane");
@@ -144,47 +143,52 @@ __global__ __launch_bounds__(256) void k_gemv1(const TB *__restrict__ B, const f
   for (int a = 0; a < QT; ++a)
 #pragma unroll
     for (int b = 0; b < ST; ++b) acc[a][b] = 0.f;
-  if constexpr (VEC) {
+  // (rows past nq read row q0, slices past ns slice s0: their sums are not stored)
+  if constexpr (EPL > 1) {
     for (int e = e0 + EPL * (int)threadIdx.x; e < e1; e += 256 * EPL) {
       float xs[ST][EPL];
 #pragma unroll
       for (int b = 0; b < ST; ++b)
 #pragma unroll
         for (int g = 0; g < EPL / 4; ++g) {
-          const float4 t = b < nsv ? *reinterpret_cast<const float4 *>(X + (size_t)(s0 + b) * ov + e + 4 * g)
-                                   : make_float4(0, 0, 0, 0);
-          xs[b][4 * g] = t.x, xs[b][4 * g + 1] = t.y, xs[b][4 * g + 2] = t.z, xs[b][4 * g + 3] = t.w;
+          const f4u t = *reinterpret_cast<const f4u *>(X + (size_t)(s0 + (b < nsv ? b : 0)) * ov + e + 4 * g);
+          xs[b][4 * g] = t[0], xs[b][4 * g + 1] = t[1], xs[b][4 * g + 2] = t[2], xs[b][4 * g + 3] = t[3];
         }
-      // all QT rows' loads issued before any of their products (rows past nq read row q0)
+      // all QT rows' loads issued before any of their products
       float bq[QT][EPL];
 #pragma unroll
       for (int a = 0; a < QT; ++a) load_row<EPL>(B, (size_t)(q0 + (a < nqv ? a : 0)) * ov + e, bq[a]);
 #pragma unroll
-      for (int a = 0; a < QT; ++a) {
-        if (a < nqv) {
+      for (int a = 0; a < QT; ++a)
 #pragma unroll
-          for (int b = 0; b < ST; ++b) {
-            float t = acc[a][b];
+        for (int b = 0; b < ST; ++b) {
+          float t = acc[a][b];
 #pragma unroll
-            for (int k = 0; k < EPL; ++k) t = fmaf(bq[a][k], xs[b][k], t);
-            acc[a][b] = t;
-          }
+          for (int k = 0; k < EPL; ++k) t = fmaf(bq[a][k], xs[b][k], t);
+          acc[a][b] = t;
         }
-      }
     }
   } else {
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += 256) {
-      float xs[ST];
+    constexpr int U = 4;  // (values past the chunk read its last one again and are left out)
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += 256 * U) {
+      float xs[U][ST], bq[U][QT];
 #pragma unroll
-      for (int b = 0; b < ST; ++b) xs[b] = b < nsv ? X[(size_t)(s0 + b) * ov + e] : 0.f;
+      for (int u = 0; u < U; ++u) {
+        const int ee = min(e + 256 * u, e1 - 1);
 #pragma unroll
-      for (int a = 0; a < QT; ++a) {
-        if (a < nqv) {
-          const float bq = load_b(B, (size_t)(q0 + a) * ov + e);
+        for (int b = 0; b < ST; ++b) xs[u][b] = X[(size_t)(s0 + (b < nsv ? b : 0)) * ov + ee];
 #pragma unroll
-          for (int b = 0; b < ST; ++b) acc[a][b] = fmaf(bq, xs[b], acc[a][b]);
-        }
+        for (int a = 0; a < QT; ++a) bq[u][a] = load_b(B, (size_t)(q0 + (a < nqv ? a : 0)) * ov + ee);
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int a = 0; a < QT; ++a)
+#pragma unroll
+          for (int b = 0; b < ST; ++b) {
+            const float t = fmaf(bq[u][a], xs[u][b], acc[a][b]);
+            acc[a][b] = e + 256 * u < e1 ? t : acc[a][b];
+          }
     }
   }
   float vals[64];
@@ -201,69 +205,32 @@ __global__ __launch_bounds__(256) void k_gemv1(const TB *__restrict__ B, const f
   }
 }
 
-// Sum of the ia-chunk partials into chunk slot 0: dpart[0][q][s] = sum_k dpart[k][q][s] (fixed order).
-__global__ void k_dsum(float *__restrict__ dpart, int n, int nes) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-    float d = dpart[e];
-    for (int k = 1; k < nes; ++k) d += dpart[(size_t)k * n + e];
-    dpart[e] = d;
-  }
-}
-
 // ------------------------------------------------------------------------------------------------
-// Coulomb, second product: P[split][s][ia] = 2 sum_{Q in split} B_ov[Q][ia] d[Q][s]
-// One thread per ia (coalesced along ia), d staged in LDS.
+// Coulomb, second product: P[split][s][ia] = 2 sum_{Q in split} B_ov[Q][ia] d[Q][s], with d the sum of
+// the first product's nes chunk partials (in chunk order), staged in LDS.
+// QW = 4 (ov % 4 == 0): each lane holds EPL consecutive ia, 16 bytes of a B row per load (a row's last
+// lane takes its last EPL values: it stores some a second time, with the same bits), eight rows in
+// flight; a block covers 64 EPL ia and its waves take every fourth Q of the split's range, their
+// partials meeting in LDS in wave order.  QW = 1 (other row lengths): one ia per lane, sixteen rows in
+// flight, every Q.  Each slice's sum depends only on its own d values, so a batch and a single RHS give
+// the same bits.
+// Bound by HBM where B_ov is large (o60 v400 N_Q1500, 3 RHS: 22 us in BF16, 25 us in FP32), by the chain of
+// its loads where it is small.  o24 v184 N_Q480 BF16, one RHS: 5.6 us (with rows past the last batch of a
+// range read one at a time and d's chunks summed in a launch of their own, 9.6 + 1.8 us); rows of any
+// length, o27 v203 N_Q541 FP32, 3 RHS: 7.8 us (one row in flight, 9.9 + 4.8 us).
 // ------------------------------------------------------------------------------------------------
-template <typename TB, int ST>
-__global__ __launch_bounds__(256) void k_gemv2(const TB *__restrict__ B, const float *__restrict__ dvec, int nq,
-                                               int ov, int ns, int nsplit, float *__restrict__ P) {
-  constexpr int QCH = 64;
+template <typename TB, int ST, int QW, int EPL>
+__global__ __launch_bounds__(256) void k_gemv2(const TB *__restrict__ B, const float *__restrict__ dpart, int nes,
+                                               int nq, int ov, int ns, int nsplit, float *__restrict__ P) {
+  constexpr int QCH = 256, U = EPL == 1 ? 16 : 8;
   __shared__ float dsh[QCH][ST];
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int s0 = blockIdx.y * ST, sp = blockIdx.z;
-  const int qa = (int)((long long)sp * nq / nsplit), qb = (int)((long long)(sp + 1) * nq / nsplit);
-  float acc[ST];
-#pragma unroll
-  for (int b = 0; b < ST; ++b) acc[b] = 0.f;
-  for (int qc = qa; qc < qb; qc += QCH) {
-    const int nqc = min(QCH, qb - qc);
-    __syncthreads();
-    for (int k = threadIdx.x; k < QCH * ST; k += 256) {
-      const int qq = k / ST, b = k % ST;
-      dsh[qq][b] = (qq < nqc && s0 + b < ns) ? dvec[(size_t)(qc + qq) * ns + s0 + b] : 0.f;
-    }
-    __syncthreads();
-    if (e < ov) {
-      for (int qq = 0; qq < nqc; ++qq) {
-        const float bq = load_b(B, (size_t)(qc + qq) * ov + e);
-#pragma unroll
-        for (int b = 0; b < ST; ++b) acc[b] += bq * dsh[qq][b];
-      }
-    }
-  }
-  if (e < ov) {
-#pragma unroll
-    for (int b = 0; b < ST; ++b)
-      if (s0 + b < ns) P[((size_t)sp * ns + s0 + b) * ov + e] = 2.f * acc[b];
-  }
-}
-
-// Vector form (ov % EPL == 0): a block covers 64 EPL consecutive ia, EPL per lane (16 bytes of B:
-// four FP32 or eight BF16 values), and its four waves take every fourth Q of the split's range
-// (wave w: Q = qa + w, qa + w + 4, ...), with eight B rows in flight per lane; the wave partials
-// meet in LDS and are summed in wave order.  Each slice's sum depends only on its own d values, so
-// a batch and a single RHS give the same bits.
-template <typename TB, int ST, int EPL>
-__global__ __launch_bounds__(256) void k_gemv2v(const TB *__restrict__ B, const float *__restrict__ dvec, int nq,
-                                                int ov, int ns, int nsplit, float *__restrict__ P) {
-  constexpr int QCH = 64, U = 8;
-  __shared__ float dsh[QCH][ST];
-  __shared__ float4 red[4][ST][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e = blockIdx.x * (64 * EPL) + EPL * lane;
+  const int ebase = ((int)blockIdx.x * (QW == 1 ? 4 : 1) + (QW == 1 ? wave : 0)) * (64 * EPL) + EPL * lane;
+  const bool live = ebase < ov;
+  const int e = min(ebase, ov - EPL);
+  const int w = QW == 1 ? 0 : wave;
   const int s0 = blockIdx.y * ST, sp = blockIdx.z;
   const int qa = (int)((long long)sp * nq / nsplit), qb = (int)((long long)(sp + 1) * nq / nsplit);
-  const bool live = e < ov;  // ov % EPL == 0: the lane's EPL ia are all inside or all outside
   float acc[ST][EPL];
 #pragma unroll
   for (int b = 0; b < ST; ++b)
@@ -272,55 +239,88 @@ __global__ __launch_bounds__(256) void k_gemv2v(const TB *__restrict__ B, const 
   for (int qc = qa; qc < qb; qc += QCH) {
     const int nqc = min(QCH, qb - qc);
     __syncthreads();
-    for (int k = threadIdx.x; k < QCH * ST; k += 256) {
-      const int qq = k / ST, b = k % ST;
-      dsh[qq][b] = (qq < nqc && s0 + b < ns) ? dvec[(size_t)(qc + qq) * ns + s0 + b] : 0.f;
+    // four values of d per thread at a time, four chunks of each in flight
+    for (int k0 = threadIdx.x; k0 < nqc * ST; k0 += 4 * 256) {
+      float d[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < nes; c += 4) {
+        float t[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = min(k0 + 256 * i, nqc * ST - 1), qq = k / ST, b = k % ST;
+          const float *src = dpart + (size_t)(qc + qq) * ns + s0 + (s0 + b < ns ? b : 0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) t[i][u] = src[(size_t)min(c + u, nes - 1) * nq * ns];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) d[i] = c + u < nes ? d[i] + t[i][u] : d[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (k0 + 256 * i < nqc * ST) dsh[(k0 + 256 * i) / ST][(k0 + 256 * i) % ST] = d[i];
     }
     __syncthreads();
     if (live) {
-      int qq = wave;
-      for (; qq + 4 * (U - 1) < nqc; qq += 4 * U) {
+      for (int qq = w; qq < nqc; qq += QW * U) {
+        // (rows past the range read its last one again and are left out of the sums: a condition on the
+        // load would make each wait for the one before it)
         float bq[U][EPL];
 #pragma unroll
-        for (int u = 0; u < U; ++u) load_row<EPL>(B, (size_t)(qc + qq + 4 * u) * ov + e, bq[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+          const size_t at = (size_t)(qc + min(qq + QW * u, nqc - 1)) * ov + e;
+          if constexpr (EPL == 1) bq[u][0] = load_b(B, at);
+          else load_row<EPL>(B, at, bq[u]);
+        }
+        auto add = [&](int u) {
 #pragma unroll
           for (int b = 0; b < ST; ++b) {
-            const float d = dsh[qq + 4 * u][b];
+            const float d = dsh[qq + QW * u][b];
 #pragma unroll
             for (int k = 0; k < EPL; ++k) acc[b][k] = fmaf(bq[u][k], d, acc[b][k]);
           }
-      }
-      for (; qq < nqc; qq += 4) {
-        float bq[EPL];
-        load_row<EPL>(B, (size_t)(qc + qq) * ov + e, bq);
+        };
+        // (a whole batch has no branch between its rows, which would put each row's LDS reads behind
+        // the sums of the one before)
+        if (qq + QW * (U - 1) < nqc) {
 #pragma unroll
-        for (int b = 0; b < ST; ++b) {
-          const float d = dsh[qq][b];
+          for (int u = 0; u < U; ++u) add(u);
+        } else {
 #pragma unroll
-          for (int k = 0; k < EPL; ++k) acc[b][k] = fmaf(bq[k], d, acc[b][k]);
+          for (int u = 0; u < U; ++u) {
+            if (qq + QW * u >= nqc) break;
+            add(u);
+          }
         }
       }
     }
   }
-  // wave partials through LDS, four values per lane at a time; wave w stores slices w, w + 4, ...
+  if constexpr (QW == 1) {
+    if (!live) return;
 #pragma unroll
-  for (int g = 0; g < EPL / 4; ++g) {
-    __syncthreads();
+    for (int b = 0; b < ST; ++b) {
+      if (s0 + b < ns) P[((size_t)sp * ns + s0 + b) * ov + e] = 2.f * acc[b][0];
+    }
+  } else {
+    // wave partials through LDS, four values per lane at a time; wave w stores slices w, w + 4, ...
+    __shared__ float4 red[4][ST][64];
 #pragma unroll
-    for (int b = 0; b < ST; ++b)
-      red[wave][b][lane] = make_float4(acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]);
-    __syncthreads();
-    for (int b = wave; b < ST; b += 4) {
-      if (!live || s0 + b >= ns) continue;
-      const float4 r0 = red[0][b][lane], r1 = red[1][b][lane], r2 = red[2][b][lane], r3 = red[3][b][lane];
-      float4 t;
-      t.x = 2.f * ((r0.x + r1.x) + (r2.x + r3.x));
-      t.y = 2.f * ((r0.y + r1.y) + (r2.y + r3.y));
-      t.z = 2.f * ((r0.z + r1.z) + (r2.z + r3.z));
-      t.w = 2.f * ((r0.w + r1.w) + (r2.w + r3.w));
-      *reinterpret_cast<float4 *>(P + ((size_t)sp * ns + s0 + b) * ov + e + 4 * g) = t;
+    for (int g = 0; g < EPL / 4; ++g) {
+      __syncthreads();
+#pragma unroll
+      for (int b = 0; b < ST; ++b)
+        red[w][b][lane] = make_float4(acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]);
+      __syncthreads();
+      for (int b = wave; b < ST; b += 4) {
+        if (!live || s0 + b >= ns) continue;
+        const float4 r0 = red[0][b][lane], r1 = red[1][b][lane], r2 = red[2][b][lane], r3 = red[3][b][lane];
+        f4u t;
+        t[0] = 2.f * ((r0.x + r1.x) + (r2.x + r3.x));
+        t[1] = 2.f * ((r0.y + r1.y) + (r2.y + r3.y));
+        t[2] = 2.f * ((r0.z + r1.z) + (r2.z + r3.z));
+        t[3] = 2.f * ((r0.w + r1.w) + (r2.w + r3.w));
+        *reinterpret_cast<f4u *>(P + ((size_t)sp * ns + s0 + b) * ov + e + 4 * g) = t;
+      }
     }
   }
 }
@@ -341,7 +341,12 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(512) void k_field(const double *__restrict__ X, const double *__restrict__ X0,
                                                const double *__restrict__ moo, const double *__restrict__ mov,
                                                const double *__restrict__ mvv, int o, int v,
-                                               double *__restrict__ F, double *__restrict__ part) {
+                                               double *__restrict__ F, double *__restrict__ part,
+                                               DevState *__restrict__ st) {
+  if (threadIdx.x == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0 && st->pend) {
+    st->step += 1;  // the step the last RK4 epilogue closed (nothing else in this kernel reads it)
+    st->pend = 0;
+  }
   __shared__ double red[8][4][64];
   __shared__ double sums[2][4];
   const int at = blockIdx.x, it = blockIdx.y, r = blockIdx.z;
@@ -427,123 +432,142 @@ __global__ __launch_bounds__(512) void k_field(const double *__restrict__ X, con
 }
 
 // ------------------------------------------------------------------------------------------------
-// Stage scalars (one block): pulse fields E_r(t_stage), the ground-row product g, the trace and
-// norm samples with the norm guard, and the RK4 update of c0 (dc0/dt = -i(-E g) = i E g).
+// Stage scalars of one right-hand side, by one block of 256 threads: its pulse field E(t_stage), the
+// ground-row product g, the trace, norm and energy samples with the norm guard, and the RK4 update of
+// c0 (dc0/dt = -i(-E g) = i E g).  The field kernel's per-block partial sums are added one component per
+// wave (lanes over blocks, then a fixed shuffle tree).  Several right-hand sides that trip the guard at
+// one step write the same value.
 // ------------------------------------------------------------------------------------------------
+__device__ __forceinline__ double stage_node(int stage) { return stage == 0 ? 0.0 : (stage == 3 ? 1.0 : 0.5); }
+
+__device__ __forceinline__ void scalar_rhs(int r, int R, int nbf, int stage, int mode, double dt,
+                                           const DevPulse *__restrict__ pulses, DevState *__restrict__ st,
+                                           const double *__restrict__ part, double *__restrict__ sc,
+                                           double *__restrict__ c0, double *__restrict__ acc0, double *__restrict__ xs0,
+                                           double *__restrict__ out, double *__restrict__ normref,
+                                           double *__restrict__ s0) {
+  __shared__ double tot[PART_STRIDE + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long step = st->step, k = step - st->step0;
+  {
+    double t = 0.0;
+    const double *pp = part + (size_t)r * nbf * PART_STRIDE + wave;
+    for (int b = lane; b < nbf; b += 64) t += pp[(size_t)b * PART_STRIDE];
+    t = wave_sum(t);
+    if (lane == 0) tot[wave] = t;
+  }
+  if ((mode & SM_ENERGY) && st->energy && wave == 0) {  // the epilogue's per-block partial sums
+    const long long nbe = st->nbe;
+    double e = 0.0;
+    for (long long b = lane; b < nbe; b += 64) e += st->epart[(size_t)r * nbe + b];
+    e = wave_sum(e);
+    if (lane == 0) st->energy[k * R + r] = e;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const double g0 = tot[0], g1 = tot[1], tr = tot[2], nr = tot[3];
+  double E = 0.0;
+  if (mode & SM_EFIELD)
+    E = pulse_field(pulses[r], ((double)step + stage_node(stage)) * dt);
+  else if (mode & SM_KEEP_E)
+    E = sc[r * SC_STRIDE + SC_E];
+  sc[r * SC_STRIDE + SC_GRE] = g0;
+  sc[r * SC_STRIDE + SC_GIM] = g1;
+  sc[r * SC_STRIDE + SC_E] = E;
+  // X0 of this stage (c0 at stage 0, else the stage value)
+  const double x0r = (stage == 0) ? c0[2 * r] : xs0[2 * r];
+  const double x0i = (stage == 0) ? c0[2 * r + 1] : xs0[2 * r + 1];
+  if (mode & (SM_TRACE | SM_OUT)) {
+    const double t = tr + (x0r * g0 + x0i * g1);
+    const double n2 = nr + (x0r * x0r + x0i * x0i);
+    if (mode & SM_OUT) out[r] = t;
+    if (mode & SM_TRACE) {
+      if (st->trace) st->trace[k * R + r] = t;
+      if (st->norms) st->norms[k * R + r] = n2;
+      if (k == 0 && !st->keep_ref) {
+        normref[r] = n2;
+      } else if (!(n2 <= 2.0 * normref[r]) && st->bad_step < 0) {  // also catches NaN
+        st->bad_step = step;
+      }
+    }
+  }
+  if (mode & SM_SIGMA0) {
+    s0[2 * r] = -E * g0;
+    s0[2 * r + 1] = -E * g1;
+  }
+  if (mode & SM_C0) {
+    // k0 = -i * (H X)_0 = -i * (-E g) = i E g
+    const double kr = -E * g1, ki = E * g0;
+    const double cr = c0[2 * r], ci = c0[2 * r + 1];
+    if (stage == 0) {
+      acc0[2 * r] = cr + dt / 6.0 * kr;
+      acc0[2 * r + 1] = ci + dt / 6.0 * ki;
+      xs0[2 * r] = cr + 0.5 * dt * kr;
+      xs0[2 * r + 1] = ci + 0.5 * dt * ki;
+    } else if (stage == 1) {
+      acc0[2 * r] += dt / 3.0 * kr;
+      acc0[2 * r + 1] += dt / 3.0 * ki;
+      xs0[2 * r] = cr + 0.5 * dt * kr;
+      xs0[2 * r + 1] = ci + 0.5 * dt * ki;
+    } else if (stage == 2) {
+      acc0[2 * r] += dt / 3.0 * kr;
+      acc0[2 * r + 1] += dt / 3.0 * ki;
+      xs0[2 * r] = cr + dt * kr;
+      xs0[2 * r + 1] = ci + dt * ki;
+    } else {
+      c0[2 * r] = acc0[2 * r] + dt / 6.0 * kr;
+      c0[2 * r + 1] = acc0[2 * r + 1] + dt / 6.0 * ki;
+    }
+  }
+}
+
+// The stage scalars as a launch of their own (one block per right-hand side), where no RK4 epilogue
+// follows that carries them
 __global__ __launch_bounds__(256) void k_scalar(int R, int nbf, int stage, int mode, double dt,
                                                 const DevPulse *__restrict__ pulses, DevState *__restrict__ st,
                                                 const double *__restrict__ part, double *__restrict__ sc,
                                                 double *__restrict__ c0, double *__restrict__ acc0,
                                                 double *__restrict__ xs0, double *__restrict__ out,
                                                 double *__restrict__ normref, double *__restrict__ s0) {
-  __shared__ int bad;
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  const long long step = st->step;
-  const long long k = step - st->step0;
-  double *trace = st->trace;
-  double *norms = st->norms;
-  const double node = (stage == 0) ? 0.0 : (stage == 3 ? 1.0 : 0.5);
-  // the field kernel's per-block partial sums of each RHS, 64 RHS at a time: wave w adds those of
-  // RHS r0 + w, r0 + w + 4, ... (lanes over blocks, then a fixed shuffle tree)
-  __shared__ double tot[64][PART_STRIDE];
+  scalar_rhs(blockIdx.x, R, nbf, stage, mode, dt, pulses, st, part, sc, c0, acc0, xs0, out, normref, s0);
+  if ((mode & SM_INC) && blockIdx.x == 0 && threadIdx.x == 0) st->pend = 1;
+}
+
+// Sum of nslab partial slabs at element e of a block of 256 threads that holds 64 elements: each wave
+// adds a quarter of the slabs (eight loads per plane in flight, in slab order), and the quarters meet in
+// LDS in wave order.  Every thread of lane l receives the sum of element l.  NP planes, `plane` floats
+// apart.  (Slabs past a quarter read its last one again and are left out of the sum: a condition on the
+// load would make each wait for the one before it.)
+template <int NP>
+__device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t slab, size_t plane, int nslab, size_t e,
+                                         bool live, double (&out)[NP]) {
+  __shared__ double quarter[4][NP][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r0 = 0; r0 < R; r0 += 64) {
-    const int nr0 = min(64, R - r0);
-    for (int rr = wave; rr < nr0; rr += (int)(blockDim.x >> 6)) {
-      const double *pp = part + (size_t)(r0 + rr) * nbf * PART_STRIDE;
-      double s_0 = 0.0, s_1 = 0.0, s_2 = 0.0, s_3 = 0.0;
-      for (int b = lane; b < nbf; b += 64) {
-        s_0 += pp[(size_t)b * PART_STRIDE + 0];
-        s_1 += pp[(size_t)b * PART_STRIDE + 1];
-        s_2 += pp[(size_t)b * PART_STRIDE + 2];
-        s_3 += pp[(size_t)b * PART_STRIDE + 3];
-      }
-      s_0 = wave_sum(s_0);
-      s_1 = wave_sum(s_1);
-      s_2 = wave_sum(s_2);
-      s_3 = wave_sum(s_3);
-      if (lane == 0) {
-        tot[rr][0] = s_0;
-        tot[rr][1] = s_1;
-        tot[rr][2] = s_2;
-        tot[rr][3] = s_3;
-      }
-    }
-    __syncthreads();
-    for (int r = r0 + (int)threadIdx.x; r < r0 + nr0; r += blockDim.x) {
-      const double g0 = tot[r - r0][0], g1 = tot[r - r0][1], tr = tot[r - r0][2], nr = tot[r - r0][3];
-      double E = 0.0;
-      if (mode & SM_EFIELD)
-        E = pulse_field(pulses[r], ((double)step + node) * dt);
-      else if (mode & SM_KEEP_E)
-        E = sc[r * SC_STRIDE + SC_E];
-      sc[r * SC_STRIDE + SC_GRE] = g0;
-      sc[r * SC_STRIDE + SC_GIM] = g1;
-      sc[r * SC_STRIDE + SC_E] = E;
-      // X0 of this stage (c0 at stage 0, else the stage value)
-      const double x0r = (stage == 0) ? c0[2 * r] : xs0[2 * r];
-      const double x0i = (stage == 0) ? c0[2 * r + 1] : xs0[2 * r + 1];
-      if (mode & (SM_TRACE | SM_OUT)) {
-        const double t = tr + (x0r * g0 + x0i * g1);
-        const double n2 = nr + (x0r * x0r + x0i * x0i);
-        if (mode & SM_OUT) out[r] = t;
-        if (mode & SM_TRACE) {
-          if (trace) trace[k * R + r] = t;
-          if (norms) norms[k * R + r] = n2;
-          if (k == 0 && !st->keep_ref) {
-            normref[r] = n2;
-          } else if (!(n2 <= 2.0 * normref[r])) {  // also catches NaN
-            bad = 1;
-          }
-        }
-      }
-      if (mode & SM_SIGMA0) {
-        s0[2 * r] = -E * g0;
-        s0[2 * r + 1] = -E * g1;
-      }
-      if (mode & SM_C0) {
-        // k0 = -i * (H X)_0 = -i * (-E g) = i E g
-        const double kr = -E * g1, ki = E * g0;
-        const double cr = c0[2 * r], ci = c0[2 * r + 1];
-        if (stage == 0) {
-          acc0[2 * r] = cr + dt / 6.0 * kr;
-          acc0[2 * r + 1] = ci + dt / 6.0 * ki;
-          xs0[2 * r] = cr + 0.5 * dt * kr;
-          xs0[2 * r + 1] = ci + 0.5 * dt * ki;
-        } else if (stage == 1) {
-          acc0[2 * r] += dt / 3.0 * kr;
-          acc0[2 * r + 1] += dt / 3.0 * ki;
-          xs0[2 * r] = cr + 0.5 * dt * kr;
-          xs0[2 * r + 1] = ci + 0.5 * dt * ki;
-        } else if (stage == 2) {
-          acc0[2 * r] += dt / 3.0 * kr;
-          acc0[2 * r + 1] += dt / 3.0 * ki;
-          xs0[2 * r] = cr + dt * kr;
-          xs0[2 * r + 1] = ci + dt * ki;
-        } else {
-          c0[2 * r] = acc0[2 * r] + dt / 6.0 * kr;
-          c0[2 * r + 1] = acc0[2 * r + 1] + dt / 6.0 * ki;
-        }
-      }
-    }
-    __syncthreads();
-  }
-  // energy sample: the epilogue's per-block partial sums of each RHS, added lane-wise then by a
-  // fixed shuffle tree (one wave per RHS)
-  if ((mode & SM_ENERGY) && st->energy) {
-    const long long nbe = st->nbe;
-    for (int r = wave; r < R; r += (int)(blockDim.x >> 6)) {
-      double e = 0.0;
-      for (long long b = lane; b < nbe; b += 64) e += st->epart[(size_t)r * nbe + b];
-      e = wave_sum(e);
-      if (lane == 0) st->energy[k * R + r] = e;
+  const int a = wave * nslab / 4, b = (wave + 1) * nslab / 4;
+  double t[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) t[p] = 0.0;
+  if (live) {
+    constexpr int U = 8;
+    for (int sl = a; sl < b; sl += U) {
+      float x[NP][U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) x[p][u] = P[(size_t)min(sl + u, b - 1) * slab + p * plane + e];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) t[p] += sl + u < b ? (double)x[p][u] : 0.0;
     }
   }
-  if (threadIdx.x == 0) {
-    if (bad && st->bad_step < 0) st->bad_step = step;
-    if (mode & SM_INC) st->step = step + 1;
-  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) quarter[wave][p][lane] = t[p];
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    out[p] = (quarter[0][p][lane] + quarter[1][p][lane]) + (quarter[2][p][lane] + quarter[3][p][lane]);
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -554,7 +578,8 @@ __global__ __launch_bounds__(256) void k_scalar(int R, int nbf, int stage, int m
 // with H x = D x + (Coulomb + exchange partials of x) - E F_x on one real plane and ground element
 // (H x)_0 = -E g_x.  c holds (q, p) at whole steps; W (the stage buffer) holds the work state
 // (q, p_h).  The FP32 (+ BF16 hi/lo) copy of the next plane to multiply goes to x32 [R][o][v].
-// One thread per (r, i, a); the ground element of RHS r by the thread with ia == 0.
+// A block of 256 threads holds 64 (r, i, a): its waves share the slabs, the first updates; the ground
+// element of RHS r by the thread with ia == 0.
 // ------------------------------------------------------------------------------------------------
 template <int PREC>
 __global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, int nslab, int mode, int use_field, double dt,
@@ -568,22 +593,16 @@ __global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, int nsl
   const size_t total = (size_t)R * ov;
   const size_t slab = total;  // one plane per RHS: floats per partial slab
   const int pl = (mode == SSO_DRIFT) ? 1 : 0;  // plane of the multiplied vector
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
+  for (size_t e0 = blockIdx.x * (size_t)64; e0 < total; e0 += (size_t)gridDim.x * 64) {
+    const size_t e = e0 + (threadIdx.x & 63);
+    double psum[1];
+    slab_sum<1>(P, slab, 0, nslab, e, e < total, psum);
+    if (threadIdx.x >= 64 || e >= total) continue;
     const size_t r = e / ov, ia = e - r * ov;
     const size_t iq = r * 2 * ov + ia, ip = iq + ov;
     const double x = (mode == SSO_KICK_FIRST) ? c[iq] : W[pl ? ip : iq];
-    double psum = 0.0;
-    int sl = 0;
-    for (; sl + 8 <= nslab; sl += 8) {
-      float a[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = P[(sl + u) * slab + e];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) psum += (double)a[u];
-    }
-    for (; sl < nslab; ++sl) psum += (double)P[sl * slab + e];
     const double E = sc[r * SC_STRIDE + SC_E];
-    double hx = D[ia] * x + psum;
+    double hx = D[ia] * x + psum[0];
     if (use_field) hx -= E * F[pl ? ip : iq];
     double nxt;
     if (mode == SSO_DRIFT) {
@@ -667,17 +686,20 @@ __global__ __launch_bounds__(256) void k_lz_init(long long n, double *__restrict
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// w = A v - beta vprev, part = <w, v>
+// w = A v - beta vprev, part = <w, v>; a block of 256 threads holds 64 elements at a time, its waves
+// share the slabs
 __global__ __launch_bounds__(256) void k_lz_apply(long long n, int nslab, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ v,
                                                   const double *__restrict__ vprev, double beta,
                                                   double *__restrict__ w, double *__restrict__ part) {
   __shared__ double sh[4];
   double acc = 0.0;
-  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
-    double s = D[e] * v[e];
-    for (int k = 0; k < nslab; ++k) s += (double)P[(size_t)k * n + e];
-    s -= beta * vprev[e];
+  for (long long e0 = blockIdx.x * 64LL; e0 < n; e0 += (long long)gridDim.x * 64) {
+    const long long e = e0 + (threadIdx.x & 63);
+    double p[1];
+    slab_sum<1>(P, (size_t)n, 0, nslab, (size_t)e, e < n, p);
+    if (threadIdx.x >= 64 || e >= n) continue;
+    const double s = D[e] * v[e] + p[0] - beta * vprev[e];
     w[e] = s;
     acc += s * v[e];
   }
@@ -717,95 +739,78 @@ __global__ __launch_bounds__(256) void k_lz_next(long long n, double scale, cons
 // ------------------------------------------------------------------------------------------------
 // RK4 epilogue (FP64): sigma = D X + sum of Coulomb/exchange partials - E F;  k = -i sigma;
 // stage accumulation into acc, next stage input (FP64 + FP32 or BF16 hi/lo copy), c at stage 4.
-// One thread per (r, i, a), both planes.
+// A block of 256 threads holds 64 (i, a) of one RHS: its four waves share the slabs (a chain of load
+// latencies where there are many of them and few elements), then two of them update one plane each:
+// Re k = Im sigma and Im k = -Re sigma, so plane p's update takes the other plane's sigma.
+// The last block of each RHS carries its stage scalars (es.mode != 0), which nothing else here reads.
+// o24 v184 N_Q480, one RHS: 6.4 us; one thread per (i, a) summing every slab took 10.9 us, and the
+// scalars' own launch 4.1 us.
 // ------------------------------------------------------------------------------------------------
 template <int PREC>
 __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab, int stage, int mode, int use_field,
                                                   double dt, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ F,
-                                                  const double *__restrict__ sc, const double *__restrict__ Xin,
+                                                  double *__restrict__ sc, const double *__restrict__ Xin,
                                                   double *__restrict__ c, double *__restrict__ acc,
                                                   double *__restrict__ xs64, float *__restrict__ x32,
                                                   __hip_bfloat16 *__restrict__ xhi, __hip_bfloat16 *__restrict__ xlo,
-                                                  double *__restrict__ s_out, double *__restrict__ epart) {
+                                                  double *__restrict__ s_out, double *__restrict__ epart, int nbe,
+                                                  StageScalars es) {
   const size_t ov = (size_t)o * v;
   const size_t slab = 2 * (size_t)R * ov;  // floats per partial slab
-  const size_t r = blockIdx.y;             // one RHS per block row
-  double en = 0.0;                         // this thread's part of <X, A X> (both planes)
-  for (size_t ia = blockIdx.x * (size_t)blockDim.x + threadIdx.x; ia < ov; ia += (size_t)gridDim.x * blockDim.x) {
-    const size_t i0 = r * 2 * ov + ia, i1 = i0 + ov;
-    const double x0 = Xin[i0], x1 = Xin[i1];
-    const double d = D[ia];
-    // partial slabs: eight independent loads in flight per plane, summed in a fixed order
-    double p0 = 0.0, p1 = 0.0;
-    int sl = 0;
-    for (; sl + 8 <= nslab; sl += 8) {
-      float a[8], b[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        a[u] = P[(sl + u) * slab + i0];
-        b[u] = P[(sl + u) * slab + i1];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        p0 += (double)a[u];
-        p1 += (double)b[u];
-      }
-    }
-    for (; sl < nslab; ++sl) {
-      p0 += (double)P[sl * slab + i0];
-      p1 += (double)P[sl * slab + i1];
-    }
-    double s0v = d * x0 + p0, s1v = d * x1 + p1;
-    if (epart) en += x0 * s0v + x1 * s1v;
+  const int r = blockIdx.y;                // one RHS per block row
+  if ((int)blockIdx.x == nbe) {
+    scalar_rhs(r, R, es.nbf, stage, es.mode, dt, es.pulses, es.st, es.part, sc, es.c0, es.acc0, es.xs0, nullptr,
+               es.normref, nullptr);
+    if ((es.mode & SM_INC) && r == 0 && threadIdx.x == 0) es.st->pend = 1;
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ double Esh;  // (read behind the slab sum's barriers)
+  if (use_field && threadIdx.x == 0)  // with the scalars in this launch the field is this block's own to evaluate
+    Esh = es.mode & SM_EFIELD ? pulse_field(es.pulses[r], ((double)es.st->step + stage_node(stage)) * dt)
+                              : sc[r * SC_STRIDE + SC_E];
+  double en = 0.0;  // this thread's part of <X, A X>
+  for (size_t ia0 = blockIdx.x * (size_t)64; ia0 < ov; ia0 += (size_t)nbe * 64) {
+    const size_t ia = ia0 + lane;
+    const size_t ib = (size_t)r * 2 * ov + ia;
+    double ps[2];
+    slab_sum<2>(P, slab, ov, nslab, ib, ia < ov, ps);
+    if (wave >= 2 || ia >= ov) continue;
+    const int p = wave, q = 1 - p;  // this wave updates plane p from plane q's sigma
+    const size_t ip = ib + p * ov, iq = ib + q * ov;
+    const double x = Xin[iq];
+    double sg = D[ia] * x + ps[q];
+    if (epart) en += x * sg;
     if (mode == EP_ENERGY) continue;
-    if (use_field) {
-      const double E = sc[r * SC_STRIDE + SC_E];
-      s0v -= E * F[i0];
-      s1v -= E * F[i1];
-    }
+    if (use_field) sg -= Esh * F[iq];
     if (mode == EP_SIGMA) {
-      s_out[i0] = s0v;
-      s_out[i1] = s1v;
+      s_out[iq] = sg;
       continue;
     }
-    // k = -i sigma: Re k = Im sigma, Im k = -Re sigma
-    const double k0 = s1v, k1 = -s0v;
-    double n0, n1;
+    const double k = p == 0 ? sg : -sg;
+    double n;
     if (stage == 0) {
-      acc[i0] = x0 + dt / 6.0 * k0;
-      acc[i1] = x1 + dt / 6.0 * k1;
-      n0 = x0 + 0.5 * dt * k0;
-      n1 = x1 + 0.5 * dt * k1;
+      const double y = Xin[ip];
+      acc[ip] = y + dt / 6.0 * k;
+      n = y + 0.5 * dt * k;
     } else if (stage == 3) {
-      n0 = acc[i0] + dt / 6.0 * k0;
-      n1 = acc[i1] + dt / 6.0 * k1;
-      c[i0] = n0;
-      c[i1] = n1;
+      n = acc[ip] + dt / 6.0 * k;
+      c[ip] = n;
     } else {
-      acc[i0] += dt / 3.0 * k0;
-      acc[i1] += dt / 3.0 * k1;
-      const double h = (stage == 1) ? 0.5 * dt : dt;
-      n0 = c[i0] + h * k0;
-      n1 = c[i1] + h * k1;
+      acc[ip] += dt / 3.0 * k;
+      n = c[ip] + ((stage == 1) ? 0.5 * dt : dt) * k;
     }
-    if (stage != 3) {
-      xs64[i0] = n0;
-      xs64[i1] = n1;
-    }
-    x32[i0] = (float)n0;
-    x32[i1] = (float)n1;
-    if (PREC == 1) {
-      split_bf16(n0, xhi[i0], xlo[i0]);
-      split_bf16(n1, xhi[i1], xlo[i1]);
-    }
+    if (stage != 3) xs64[ip] = n;
+    x32[ip] = (float)n;
+    if (PREC == 1) split_bf16(n, xhi[ip], xlo[ip]);
   }
-  if (epart) {  // block sum in a fixed order: waves, then the four wave totals
+  if (epart) {  // block sum in a fixed order: waves, then the wave totals
     __shared__ double ws[4];
     en = wave_sum(en);
-    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = en;
+    if (lane == 0) ws[wave] = en;
     __syncthreads();
-    if (threadIdx.x == 0) epart[r * gridDim.x + blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
+    if (threadIdx.x == 0) epart[(size_t)r * nbe + blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
   }
 }
 
@@ -866,6 +871,7 @@ __global__ void k_set_state(DevState *st, long long step0, double *trace, double
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     st->step = step0;
     st->step0 = step0;
+    st->pend = 0;
     if (!resume) st->bad_step = -1;
     st->keep_ref = resume;
     st->energy = energy;
@@ -905,7 +911,7 @@ __global__ __launch_bounds__(256) void k_pop(int R, size_t ov, const double *__r
   __syncthreads();
   if (threadIdx.x == 0) {
     const double a = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]), b = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-    const long long k = st->step - st->step0;
+    const long long k = st->step + st->pend - st->step0;
     pops[(k * R + r) * K + I] = a * a + b * b;
   }
 }
@@ -937,7 +943,7 @@ __global__ __launch_bounds__(256) void k_corr(int R, size_t ov, const double *__
   __syncthreads();
   if (threadIdx.x == 0) {
     const double g0 = xref0[2 * r], g1 = xref0[2 * r + 1], c0 = X0[2 * r], c1 = X0[2 * r + 1];
-    const long long k = st->step - st->step0;
+    const long long k = st->step + st->pend - st->step0;
     corr[(k * R + r) * 2] = (g0 * c0 + g1 * c1) + ((sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]));
     corr[(k * R + r) * 2 + 1] = (g0 * c1 - g1 * c0) + ((sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]));
   }
@@ -986,36 +992,25 @@ int gemv1_chunks(int nq, int ov) {
   return (ov + echunk - 1) / echunk;
 }
 
-template <typename TB, int ST>
-static void gemv1_go(hipStream_t s, const TB *B, const float *X, int nq, int ov, int ns, int nes, float *dpart) {
-  constexpr int QT = 8;
-  const bool vec = (ov % 4) == 0;
-  const int echunk = nes == 1 ? ov : (((ov + nes - 1) / nes) + 1023) / 1024 * 1024;
-  dim3 grid((nq + QT - 1) / QT, (ns + ST - 1) / ST, nes);
-  bool done = false;
-  if constexpr (std::is_same<TB, __hip_bfloat16>::value) {
-    if (ov % 8 == 0) {  // 16-byte loads of eight BF16 values
-      hipLaunchKernelGGL((k_gemv1<TB, QT, ST, true, 8>), grid, dim3(256), 0, s, B, X, nq, ov, ns, echunk, dpart);
-      done = true;
-    }
-  }
-  if (done) {
-  } else if (vec)
-    hipLaunchKernelGGL((k_gemv1<TB, QT, ST, true>), grid, dim3(256), 0, s, B, X, nq, ov, ns, echunk, dpart);
-  else
-    hipLaunchKernelGGL((k_gemv1<TB, QT, ST, false>), grid, dim3(256), 0, s, B, X, nq, ov, ns, echunk, dpart);
-  if (nes > 1) {
-    const int n = nq * ns;
-    hipLaunchKernelGGL(k_dsum, dim3(grid_for(n)), dim3(256), 0, s, dpart, n, nes);
-  }
-}
-
 template <typename TB>
 static void gemv1_st(hipStream_t s, const TB *B, const float *X, int nq, int ov, int ns, int nes, float *dpart) {
-  if (ns <= 2) gemv1_go<TB, 2>(s, B, X, nq, ov, ns, nes, dpart);
-  else if (ns <= 4) gemv1_go<TB, 4>(s, B, X, nq, ov, ns, nes, dpart);
-  else if (ns <= 6) gemv1_go<TB, 6>(s, B, X, nq, ov, ns, nes, dpart);
-  else gemv1_go<TB, 8>(s, B, X, nq, ov, ns, nes, dpart);
+  constexpr int QT = 8;
+  const int echunk = nes == 1 ? ov : (((ov + nes - 1) / nes) + 1023) / 1024 * 1024;
+  auto go = [&](auto st) {
+    constexpr int ST = decltype(st)::value;
+    const dim3 grid((nq + QT - 1) / QT, (ns + ST - 1) / ST, nes);
+    auto run = [&](auto epl) {
+      hipLaunchKernelGGL((k_gemv1<TB, QT, ST, decltype(epl)::value>), grid, dim3(256), 0, s, B, X, nq, ov, ns, echunk,
+                         dpart);
+    };
+    if (ov % row_epl<TB>() == 0) run(std::integral_constant<int, row_epl<TB>()>{});
+    else if (ov % 4 == 0) run(std::integral_constant<int, 4>{});
+    else run(std::integral_constant<int, 1>{});
+  };
+  if (ns <= 2) go(std::integral_constant<int, 2>{});
+  else if (ns <= 4) go(std::integral_constant<int, 4>{});
+  else if (ns <= 6) go(std::integral_constant<int, 6>{});
+  else go(std::integral_constant<int, 8>{});
 }
 
 hipError_t launch_gemv1(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns, int nes,
@@ -1027,71 +1022,75 @@ hipError_t launch_gemv1(hipStream_t s, int b_dtype, const void *B, const float *
   return hipGetLastError();
 }
 
-hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *dvec, int nq, int ov, int ns,
-                        int nsplit, float *P) {
-  constexpr int ST = 8;
-  dim3 grid((ov + 255) / 256, (ns + ST - 1) / ST, nsplit);
-  if (b_dtype == RTTDA_BF16 && ov % 8 == 0) {
-    dim3 g8((ov + 511) / 512, (ns + ST - 1) / ST, nsplit);
-    hipLaunchKernelGGL((k_gemv2v<__hip_bfloat16, ST, 8>), g8, dim3(256), 0, s,
-                       static_cast<const __hip_bfloat16 *>(B), dvec, nq, ov, ns, nsplit, P);
-    return hipGetLastError();
-  }
-  if (ov % 4 == 0) {
-    if (b_dtype == RTTDA_BF16)
-      hipLaunchKernelGGL((k_gemv2v<__hip_bfloat16, ST, 4>), grid, dim3(256), 0, s,
-                         static_cast<const __hip_bfloat16 *>(B), dvec, nq, ov, ns, nsplit, P);
+template <typename TB>
+static void gemv2_st(hipStream_t s, const TB *B, const float *dpart, int nes, int nq, int ov, int ns, int nsplit,
+                     float *P) {
+  constexpr int EPL = row_epl<TB>();
+  auto go = [&](auto st) {
+    constexpr int ST = decltype(st)::value;
+    const int sy = (ns + ST - 1) / ST;
+    if (ov % 4 == 0 && ov >= EPL)
+      hipLaunchKernelGGL((k_gemv2<TB, ST, 4, EPL>), dim3((ov + 64 * EPL - 1) / (64 * EPL), sy, nsplit), dim3(256), 0, s,
+                         B, dpart, nes, nq, ov, ns, nsplit, P);
     else
-      hipLaunchKernelGGL((k_gemv2v<float, ST, 4>), grid, dim3(256), 0, s, static_cast<const float *>(B), dvec, nq,
+      hipLaunchKernelGGL((k_gemv2<TB, ST, 1, 1>), dim3((ov + 255) / 256, sy, nsplit), dim3(256), 0, s, B, dpart, nes, nq,
                          ov, ns, nsplit, P);
-    return hipGetLastError();
-  }
+  };
+  if (ns <= 2) go(std::integral_constant<int, 2>{});
+  else if (ns <= 4) go(std::integral_constant<int, 4>{});
+  else if (ns <= 6) go(std::integral_constant<int, 6>{});
+  else go(std::integral_constant<int, 8>{});
+}
+
+hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *dpart, int nes, int nq, int ov, int ns,
+                        int nsplit, float *P) {
   if (b_dtype == RTTDA_BF16)
-    hipLaunchKernelGGL((k_gemv2<__hip_bfloat16, ST>), grid, dim3(256), 0, s, static_cast<const __hip_bfloat16 *>(B),
-                       dvec, nq, ov, ns, nsplit, P);
+    gemv2_st(s, static_cast<const __hip_bfloat16 *>(B), dpart, nes, nq, ov, ns, nsplit, P);
   else
-    hipLaunchKernelGGL((k_gemv2<float, ST>), grid, dim3(256), 0, s, static_cast<const float *>(B), dvec, nq, ov, ns,
-                       nsplit, P);
+    gemv2_st(s, static_cast<const float *>(B), dpart, nes, nq, ov, ns, nsplit, P);
   return hipGetLastError();
 }
 
 hipError_t launch_field(hipStream_t s, const double *X, const double *X0, const double *moo, const double *mov,
-                        const double *mvv, int o, int v, int R, double *F, double *part) {
+                        const double *mvv, int o, int v, int R, double *F, double *part, DevState *st) {
   dim3 grid(field_blocks_a(v), field_blocks_i(o), R);
-  hipLaunchKernelGGL(k_field, grid, dim3(512), 0, s, X, X0, moo, mov, mvv, o, v, F, part);
+  hipLaunchKernelGGL(k_field, grid, dim3(512), 0, s, X, X0, moo, mov, mvv, o, v, F, part, st);
   return hipGetLastError();
 }
 
 hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, double dt, const DevPulse *pulses,
                          DevState *st, const double *part, double *sc, double *c0, double *acc0, double *xs0,
                          double *out, double *normref, double *s0) {
-  hipLaunchKernelGGL(k_scalar, dim3(1), dim3(256), 0, s, R, nbf, stage, mode, dt, pulses, st, part, sc, c0, acc0,
+  hipLaunchKernelGGL(k_scalar, dim3(R), dim3(256), 0, s, R, nbf, stage, mode, dt, pulses, st, part, sc, c0, acc0,
                      xs0, out, normref, s0);
   return hipGetLastError();
 }
 
 hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, int nslab, int stage, int mode,
-                           int use_field, double dt, const double *D, const float *P, const double *F,
-                           const double *sc, const double *Xin, double *c, double *acc, double *xs64, float *x32,
-                           __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, double *s_out, double *epart) {
-  dim3 grid(epilogue_blocks((long long)o * v), R);
+                           int use_field, double dt, const double *D, const float *P, const double *F, double *sc,
+                           const double *Xin, double *c, double *acc, double *xs64, float *x32, __hip_bfloat16 *xhi,
+                           __hip_bfloat16 *xlo, double *s_out, double *epart, const StageScalars *scalars) {
+  StageScalars es{};
+  if (scalars) es = *scalars;
+  const int nbe = epilogue_blocks((long long)o * v);
+  dim3 grid(nbe + (es.mode ? 1 : 0), R);
   if (prec == RTTDA_PREC_MIXED_BF16)
     hipLaunchKernelGGL((k_epilogue<1>), grid, dim3(256), 0, s, R, o, v, nslab, stage, mode, use_field, dt, D, P, F,
-                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart);
+                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
   else
     hipLaunchKernelGGL((k_epilogue<0>), grid, dim3(256), 0, s, R, o, v, nslab, stage, mode, use_field, dt, D, P, F,
-                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart);
+                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
   return hipGetLastError();
 }
 
-int epilogue_blocks(long long ov) { return (int)std::min<long long>((ov + 255) / 256, EP_BX_MAX); }
+int epilogue_blocks(long long ov) { return (int)std::min<long long>((ov + 63) / 64, EP_BX_MAX); }
 
 hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, int nslab, int mode, int use_field,
                              double dt, const double *D, const float *P, const double *F, const double *sc, double *c,
                              double *c0, double *W, double *W0, float *x32, __hip_bfloat16 *xhi,
                              __hip_bfloat16 *xlo) {
   const long long n = (long long)R * o * v;
-  dim3 grid(grid_for(n, 256, 65536));
+  dim3 grid(grid_for(n, 64, 65536));
   if (prec == RTTDA_PREC_MIXED_BF16)
     hipLaunchKernelGGL((k_sso_update<1>), grid, dim3(256), 0, s, R, o, v, nslab, mode, use_field, dt, D, P, F, sc, c,
                        c0, W, W0, x32, xhi, xlo);
@@ -1112,7 +1111,7 @@ hipError_t launch_plane_copy(hipStream_t s, int prec, int R, size_t ov, int plan
   return hipGetLastError();
 }
 
-int lz_blocks(long long n) { return (int)std::min<long long>(LZ_BLOCKS_MAX, std::max<long long>(1, (n + 255) / 256)); }
+int lz_blocks(long long n) { return (int)std::min<long long>(LZ_BLOCKS_MAX, std::max<long long>(1, (n + 63) / 64)); }
 
 hipError_t launch_lz_init(hipStream_t s, long long n, double *v, double *part) {
   hipLaunchKernelGGL(k_lz_init, dim3(lz_blocks(n)), dim3(256), 0, s, n, v, part);

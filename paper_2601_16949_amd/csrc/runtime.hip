@@ -520,7 +520,7 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   } else {
     const int nes = gemv1_chunks(ctx->nq, ov);
     HIP_TRY(launch_gemv1(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->x32(), ctx->nq, ov, ns, nes, ctx->dvec()));
-    HIP_TRY(launch_gemv2(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->dvec(), ctx->nq, ov, ns, ctx->sj, ctx->P()));
+    HIP_TRY(launch_gemv2(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->dvec(), nes, ctx->nq, ov, ns, ctx->sj, ctx->P()));
   }
   if (pr) HIP_TRY(ctx->prof.end(PC_COULOMB, sc));
   if (fork) HIP_TRY(hipEventRecord(ctx->ev_join, ctx->aux));
@@ -575,7 +575,7 @@ rttda_status enqueue_step(rttda_ctx *ctx, int nrhs, double dt, bool has_field, b
     const bool pr = ctx->prof.on;
     if (need_field) {
       if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
-      HIP_TRY(launch_field(s, Xin, X0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+      HIP_TRY(launch_field(s, Xin, X0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
       if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
     }
     if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
@@ -584,13 +584,13 @@ rttda_status enqueue_step(rttda_ctx *ctx, int nrhs, double dt, bool has_field, b
     if (has_field) mode |= SM_C0 | SM_EFIELD;
     if (stage == 3) mode |= SM_INC;
     if (stage == 1 && energy) mode |= SM_ENERGY;  // the sample of this step, from stage 0's partials
-    HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, stage, mode, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
-                          c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
+    const StageScalars es{mode,         ctx->L.nbf, ctx->pulses(), ctx->state(),  ctx->part(),
+                          c0,           ctx->acc0(), ctx->xs0(),   ctx->normref()};
     if (corr && stage == 0) HIP_TRY(launch_corr(s, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
     if (pops && stage == 0) HIP_TRY(launch_pop(s, nrhs, ctx->ov, c, ctx->state()));
     HIP_TRY(launch_epilogue(s, ctx->prec, nrhs, o, v, nslab(ctx), stage, EP_RK4, has_field ? 1 : 0, dt, ctx->D(),
                             ctx->P(), ctx->F(), ctx->sc(), Xin, c, ctx->acc(), ctx->xs64(), ctx->x32(), ctx->xhi(),
-                            ctx->xlo(), nullptr, energy && stage == 0 ? ctx->epart() : nullptr));
+                            ctx->xlo(), nullptr, energy && stage == 0 ? ctx->epart() : nullptr, &es));
     if (pr) HIP_TRY(ctx->prof.end(PC_EPILOGUE, s));
   }
   return RTTDA_OK;
@@ -606,7 +606,7 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
   double *W = ctx->xs64(), *W0 = ctx->xs0();
   rttda_status st;
   if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
-  HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+  HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, SM_TRACE, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), c0,
                         ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   if (corr) HIP_TRY(launch_corr(s, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
@@ -616,7 +616,7 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
     if ((st = enqueue_two_electron(ctx, nrhs, SL_REAL)) != RTTDA_OK) return st;
     if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
     if (has_field)
-      HIP_TRY(launch_field(s, W, W0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+      HIP_TRY(launch_field(s, W, W0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
     if (has_field || half == 1)
       HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, half == 0 ? 1 : 3,
                             (has_field ? SM_EFIELD : 0) | (half == 1 ? SM_INC : 0), dt, ctx->pulses(), ctx->state(),
@@ -636,7 +636,7 @@ rttda_status enqueue_sso_start(rttda_ctx *ctx, int nrhs, double dt, bool has_fie
   rttda_status st = enqueue_two_electron(ctx, nrhs, SL_REAL);
   if (st != RTTDA_OK) return st;
   if (has_field)
-    HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part()));
+    HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, has_field ? SM_EFIELD : 0, dt, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx, SL_REAL), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
@@ -813,7 +813,7 @@ rttda_status sigma_enqueue(rttda_ctx *ctx, int nrhs, const double *c0, const dou
   HIP_TRY(launch_mu_blocks(hs, ctx->d.mu, ctx->pulses(), ctx->o, ctx->v, nrhs, ctx->moo(), ctx->mov(), ctx->mvv()));
   if ((st = to_stage_copy(ctx, c, nrhs)) != RTTDA_OK) return st;
   if ((st = enqueue_two_electron(ctx, 2 * nrhs)) != RTTDA_OK) return st;
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part()));
+  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_SIGMA0 | SM_KEEP_E, 0.0, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), const_cast<double *>(c0), ctx->acc0(), ctx->xs0(), nullptr,
                         ctx->normref(), s0));
@@ -1075,7 +1075,7 @@ rttda_status rttda_dipole_trace(rttda_ctx *ctx, int32_t nrhs, const double *dir,
   drop_graph(ctx);
   hipStream_t hs = ctx->stream;
   HIP_TRY(launch_mu_blocks(hs, ctx->d.mu, ctx->pulses(), ctx->o, ctx->v, nrhs, ctx->moo(), ctx->mov(), ctx->mvv()));
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part()));
+  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_OUT, 0.0, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
                         const_cast<double *>(c0), ctx->acc0(), ctx->xs0(), out, ctx->normref(), nullptr));
   return RTTDA_OK;
@@ -1137,7 +1137,7 @@ rttda_status exact_kick_apply(rttda_ctx *ctx, int nrhs, int J, double *c0, doubl
   HIP_TRY(hipMemcpyAsync(T, c, (size_t)2 * nrhs * ov * sizeof(double), hipMemcpyDeviceToDevice, hs));
   HIP_TRY(hipMemcpyAsync(T0, c0, (size_t)2 * nrhs * sizeof(double), hipMemcpyDeviceToDevice, hs));
   for (int j = 1; j <= J; ++j) {
-    HIP_TRY(launch_field(hs, T, T0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+    HIP_TRY(launch_field(hs, T, T0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
     HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, 0, 0.0, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), T0,
                           ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
     HIP_TRY(launch_kick_term(hs, nrhs, (int)ov, ctx->pulses(), ctx->F(), ctx->sc(), 1.0 / j, T, T0, c, c0));
@@ -1216,7 +1216,7 @@ rttda_status propagate_impl(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse *pul
   HIP_TRY(launch_set_state(hs, ctx->state(), step0, trace, norms, corr, pops, popU, popk, energy, ctx->epart(),
                            epilogue_blocks((long long)ctx->ov), resume ? 1 : 0));
   if (has_kick && step0 == 0) {
-    HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+    HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
     HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, 0, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), c0,
                           ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
     HIP_TRY(launch_kick(hs, nrhs, (int)ctx->ov, ctx->pulses(), ctx->F(), ctx->sc(), c, c0));
@@ -1297,7 +1297,7 @@ rttda_status propagate_impl(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse *pul
                              ctx->acc0(), ctx->xs64(), ctx->xs0(), ctx->x32(), ctx->xhi(), ctx->xlo(), ctx->normref()));
     return RTTDA_OK;
   }
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part()));
+  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_TRACE, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
                         c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   if (energy) {  // the final energy sample needs one more product A c
