@@ -204,12 +204,17 @@ hipError_t launch_corr(hipStream_t s, int R, size_t ov, const double *X, const d
                        const double *xref0, const DevState *st);
 
 // Exchange: K partials P[split][slice][o][v] = scale * sum_{Q in split} B_oo^Q X_slice B_vv^Q.
-// Large-o split-BF16 path (two batched GEMMs per chunk of Q through a W scratch buffer): used
-// for o >= XGEMM_O_MIN with o % 8 == 0 and v % 8 == 0; the scratch holds W hi/lo for up to
-// XGEMM_SCRATCH_MAX bytes' worth of Q values.
-constexpr int XGEMM_O_MIN = 128;
+// Large-o split-BF16 path (two batched GEMMs per chunk of Q through a W scratch buffer) for o >= XGEMM_O_MIN
+// with v % 8 == 0; the scratch holds W hi/lo for up to XGEMM_SCRATCH_MAX bytes' worth of Q values.
+constexpr int XGEMM_O_MIN = 65;
 constexpr size_t XGEMM_SCRATCH_MAX = size_t(2048) << 20;
 constexpr size_t XGEMM_SCRATCH_MID = size_t(256) << 20;  // below o = 128, where 256 MiB hold hundreds of Q
+inline int xgemm_op(int o) { return (o + 7) / 8 * 8; }   // a slice's rows there: 16-byte groups
+// bytes behind the W scratch for X (rows = slices x op) in the order the first GEMM stages it: columns in
+// whole chunks of 32, rows in whole tiles of at most 256, hi and lo; and behind those B_oo of a chunk of
+// Q, padded, where o is not a multiple of 8
+inline size_t xgemm_x_bytes(int v, size_t rows) { return (size_t)((v + 31) / 32) * 32 * (rows + 255) * 4; }
+inline size_t xgemm_o_bytes(int o, size_t qc) { return o % 8 ? qc * xgemm_op(o) * xgemm_op(o) * 2 : 0; }
 
 // work of an X-resident exchange workgroup (see shape_xres)
 struct ResShape {
@@ -236,6 +241,8 @@ struct ExchangeVariant {
   int rank = 0;          // preference among variants of equal tile waste (higher first)
   int v_max = 1 << 30;
   void (*res)(int v, int ns, struct ResShape *) = nullptr;  // X resident in LDS (one workgroup fills a CU)
+  int rows = 0;  // scratch variants: stacked rows per tile of the first GEMM (nt: its columns)
+  int cols = 0;  //                   columns per tile of the second
   bool applies(int o, int v) const {
     return o <= o16 && o >= o_min && v >= v_min && v <= v_max && v % v_mod == 0 && o % o_mod == 0;
   }

@@ -288,8 +288,7 @@ __global__ __launch_bounds__(256) void k_gemv2(const TB *__restrict__ B, const f
         } else {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            if (qq + QW * u >= nqc) break;
-            add(u);
+            if (qq + QW * u < nqc) add(u);
           }
         }
       }

@@ -78,6 +78,15 @@ struct Layout {
   int sk_max, sj_max;
 };
 
+// Whether the GEMM path takes the exchange.  Below o = 128 and up to 128 virtuals with few slices its
+// launches (X, then two per chunk of Q) and partly filled 256-column tiles cost more than the fused kernels'
+// repeated reads of X: o72 v128 N_Q300, one RHS: 49 against 43 us; three RHS: 77 against 160 us; o96 v136,
+// one RHS: 52 against 61 us, o96 v720 N_Q1920, one RHS: 1.23 against 3.67 ms.
+bool xgemm_applies(int o, int v, size_t ns) {
+  if (o < XGEMM_O_MIN || o > 256 || v % 8 != 0 || (size_t)v * ns * xgemm_op(o) >= size_t(1) << 30) return false;
+  return o >= 128 || v > 128 || ns * v >= 400;
+}
+
 // slab_bytes: workspace for the exchange's partial K slabs (at least 32 slabs); gemm_scratch: carve
 // the W scratch of the large-o GEMM exchange path where that path applies
 Layout make_layout(int o, int v, int nq, int R, int prec, size_t slab_bytes = SK_SLAB_BYTES,
@@ -117,12 +126,13 @@ Layout make_layout(int o, int v, int nq, int R, int prec, size_t slab_bytes = SK
   L.xref0 = take(ns * 8);
   L.epart = take((size_t)R * EP_BX_MAX * 8);
   L.scratch_bytes = 0;
-  if (gemm_scratch && prec == RTTDA_PREC_MIXED_BF16 && nq > 0 && o >= XGEMM_O_MIN && o <= 256 && o % 8 == 0 &&
-      v % 8 == 0) {
-    const size_t per_q = (size_t)v * ns * o * 4;  // W hi + lo for one Q at the largest RHS count
+  if (gemm_scratch && prec == RTTDA_PREC_MIXED_BF16 && nq > 0 && xgemm_applies(o, v, ns)) {
+    const size_t per_q = (size_t)v * ns * xgemm_op(o) * 4;  // W hi + lo for one Q at the largest RHS count
     L.scratch_bytes = std::min((size_t)nq * per_q, std::max(per_q, o >= 128 ? XGEMM_SCRATCH_MAX : XGEMM_SCRATCH_MID));
   }
-  L.scratch = take(L.scratch_bytes);
+  L.scratch = take(L.scratch_bytes ? L.scratch_bytes + xgemm_x_bytes(v, ns * xgemm_op(o)) +
+                                         xgemm_o_bytes(o, L.scratch_bytes / ((size_t)v * ns * xgemm_op(o) * 4))
+                                   : 0);
   L.lz = take(3 * ov * 8);
   L.lzp = take((size_t)LZ_BLOCKS_MAX * 8);
   L.total = off;
@@ -366,11 +376,22 @@ int resident_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int 
 
 int auto_variant(int prec, int o, int ns, int v, int nq, const Layout &L) {
   const int n = variant_count(prec);
-  // the large-o GEMM path first whenever the workspace carries its scratch
+  // the GEMM path for large o first whenever the workspace carries its scratch: the second GEMM's tile that
+  // holds o with the fewest rows, the first's that pads the stacked rows least (a 192-row tile has fewer
+  // products per LDS read: about 1.1 times the time per row of a 256-row tile)
+  int gemm = -1;
+  double gemm_cost = 1e300;
   for (int k = 0; k < n; ++k) {
     const ExchangeVariant *x = variant_of(prec, k);
-    if (x->scratch && usable(x, o, v, L)) return k;
+    if (!x->scratch || !usable(x, o, v, L)) continue;
+    const double rows = (ns * xgemm_op(o) + x->rows - 1) / x->rows * x->rows * (x->rows < 256 ? 1.1 : 1.0);
+    const double cost = x->o16 * 1e9 + rows;
+    if (cost < gemm_cost) {
+      gemm_cost = cost;
+      gemm = k;
+    }
   }
+  if (gemm >= 0) return gemm;
   // then X resident in LDS wherever it fits: on every shape tried (o 12..64, v 56..800, 1..64 RHS, both
   // precisions) as fast as the best of the others or faster, e.g. o60 v400 N_Q1500, 3 RHS: 386 against
   // 536 us (split BF16) and 1660 against 1870 us (FP32) per launch; o40 v300 N_Q1000, 32 RHS: 1.21
@@ -414,15 +435,49 @@ int auto_variant(int prec, int o, int ns, int v, int nq, const Layout &L) {
   return best;
 }
 
+// Q per chunk of the GEMM path: the scratch holds qmax of them.  The first GEMM's workgroups, one per CU,
+// take its tiles in rounds; chunks that fill whole rounds leave no CU idle in the last one (o96 v720
+// N_Q1920, one RHS: 4 x 455 + 100 Q are 22 rounds, five equal chunks 25).  A launch pair more is worth
+// about a quarter of a round.
+int gemm_chunk(const ExchangeVariant *x, int o, int ns, int v, int nq, int qmax) {
+  const int n_rt = (ns * xgemm_op(o) + x->rows - 1) / x->rows;
+  auto rounds = [&](int q) { return (((long long)q * v + x->nt - 1) / x->nt * n_rt + 255) / 256; };
+  int best = qmax;
+  double best_cost = 1e300;
+  const long long r0 = rounds(qmax);
+  for (long long r = r0; r >= 1 && r > r0 - 32; --r) {
+    const int q = (int)std::min<long long>(qmax, r * 256 / n_rt * x->nt / v);
+    if (q < 1) break;
+    const int full = nq / q, rem = nq % q;
+    const double cost = full * (rounds(q) + 0.25) + (rem ? rounds(rem) + 0.25 : 0.0);
+    if (cost < best_cost * (1 - 1e-12)) {
+      best_cost = cost;
+      best = q;
+    }
+  }
+  return best;
+}
+
 int auto_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap, const Layout &L) {
   if (x->scratch) {
-    // GEMM path: splits of each chunk's Q range for the B_oo product (about two workgroups per
-    // CU), at most the chunk length
-    const size_t per_q = (size_t)v * ns * o * 4;
-    const int qc = (int)std::max<size_t>(1, std::min<size_t>((size_t)nq, L.scratch_bytes / per_q));
-    const int tiles_b = ns * ((v + 127) / 128);
-    int s = (512 + tiles_b - 1) / tiles_b;
-    return std::max(1, std::min({s, std::max(1, qc / 2), cap}));
+    // GEMM path: splits of each chunk's Q range for the B_oo product, so that its workgroups fill whole
+    // rounds of the 256 CUs: a workgroup takes about 1.3 us per Q and 32 j, and a split adds a slab that
+    // every chunk after the first reads and writes again (4 TB/s).  o240 v1800, 3 RHS: 85 tiles in 3
+    // splits (255 workgroups) 9088 us, in 8 (680, the third round a third empty) 9312
+    const int tiles_b = (ns * v + x->cols - 1) / x->cols;
+    const size_t per_q = (size_t)v * ns * xgemm_op(o) * 4;
+    const int qc = gemm_chunk(x, o, ns, v, nq, (int)std::max<size_t>(1, std::min<size_t>(nq, L.scratch_bytes / per_q)));
+    const double step = 1.3 * ((o + 31) / 32), slab = (double)ns * o * v * 4 * 2 / 4e6;
+    int best = 1;
+    double best_us = 1e300;
+    for (int s = 1; s <= std::min({cap, qc, 512}); ++s) {
+      const double us = ((long long)tiles_b * s + 255) / 256 * ((qc + s - 1) / s) * step + s * slab;
+      if (us < best_us * (1 - 1e-12)) {
+        best_us = us;
+        best = s;
+      }
+    }
+    return best;
   }
   if (x->res) {
     double t;
@@ -461,10 +516,14 @@ rttda_status check_dirs(const double *dir, int nrhs) {
 // chunk), so a batch and a single RHS sum their Q chunks identically.
 size_t scratch_for(const rttda_ctx *ctx, int ns) {
   if (ctx->L.scratch_bytes == 0) return 0;
-  const size_t per_q_max = (size_t)ctx->v * (2 * (size_t)ctx->R) * ctx->o * 4;
-  size_t qc = std::max<size_t>(1, ctx->L.scratch_bytes / per_q_max);
-  if (ctx->qchunk > 0) qc = std::min(qc, (size_t)ctx->qchunk);
-  return qc * (size_t)ctx->v * ns * ctx->o * 4;
+  const int ns_max = 2 * ctx->R;
+  const size_t per_q_max = (size_t)ctx->v * ns_max * xgemm_op(ctx->o) * 4;
+  const int qmax = (int)std::max<size_t>(1, std::min<size_t>(ctx->nq, ctx->L.scratch_bytes / per_q_max));
+  const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  const int qc = !x->scratch      ? qmax
+                 : ctx->qchunk > 0 ? std::min(qmax, ctx->qchunk)
+                                   : gemm_chunk(x, ctx->o, ns_max, ctx->v, ctx->nq, qmax);
+  return (size_t)qc * ctx->v * ns * xgemm_op(ctx->o) * 4;
 }
 
 // What a launch's slices are: both planes of every RHS (RK4, sigma, Davidson batches), one plane per
