@@ -67,8 +67,9 @@ constexpr int PART_STRIDE = 4;
 
 // Field-kernel tile (i x a) and its grid per RHS.
 constexpr int FT_I = 16, FT_A = 16;
-inline int field_blocks_a(int v) { return (v + FT_A - 1) / FT_A; }
-inline int field_blocks_i(int o) { return (o + FT_I - 1) / FT_I; }
+__host__ __device__ inline int field_blocks_a(int v) { return (v + FT_A - 1) / FT_A; }
+__host__ __device__ inline int field_blocks_i(int o) { return (o + FT_I - 1) / FT_I; }
+__host__ __device__ inline int field_blocks(int o, int v) { return 2 * field_blocks_a(v) * field_blocks_i(o); }
 
 // k_scalar modes (bit mask).
 enum : int {
@@ -84,28 +85,35 @@ enum : int {
 
 // Epilogue modes.
 enum : int { EP_RK4 = 0, EP_SIGMA = 1, EP_ENERGY = 2 };
+// Field product of `blocks` / field_blocks(o, v) right-hand sides (see field.h), as a launch of its own or
+// beside the blocks of another launch that reads the same X; blocks = 0: none.
+struct FieldArgs {
+  const double *X, *X0, *moo, *mov, *mvv;
+  int o, v;
+  double *F, *part;
+  DevState *st;
+  int blocks;
+};
+
 // Small problems (o v <= SMALL_OV_MAX, at most SMALL_R_MAX RHS): one launch for the Coulomb and
-// exchange partial slabs of a stage, one single-workgroup launch for the whole stage epilogue.
+// exchange partial slabs of a stage and the field product, one for the stage update.
 constexpr int SMALL_OV_MAX = 2048;
 constexpr int SMALL_R_MAX = 64;
-// the small path is the default up to this many exchange flops per stage at max_rhs (measured: at
-// o10 v40 N_Q120 with one or two RHS it is 10-25 % faster than the general kernels; at o12 v48
-// N_Q160 with one RHS, 2.2e7 flops, it is slower)
+// the small path is the default up to this many exchange flops per stage at max_rhs: 16 steps of o10 v40
+// N_Q120 with one RHS (1e7) take 0.91 ms, with the general kernels 1.46.  Above, the choice depends on the
+// shape (o10 v40 N_Q120 with six RHS, 6e7: 1.56 against 1.69 ms; o13 v45 N_Q160 with two, 4.3e7: 1.36 and
+// 1.36; o10 v40 N_Q120 with eight, 8e7: 1.70 against 1.43): a caller who knows can ask for it
 constexpr double SMALL_DEFAULT_FLOPS = 2e7;
-// LDS of the two small-path kernels: the epilogue stages one RHS's X (two planes), mu_vv and mu_oo
-// in FP64, the partial-sum kernel a slice's X and W and one Q's B_vv and B_oo in FP32
+// (with the partial-sum kernel's LDS, a slice's X and W and one Q's B_vv and B_oo in FP32, the shapes that
+// the path takes)
 constexpr int SMALL_LDS_DOUBLES = 12288;
 inline bool small_shape_ok(int o, int v) {
   return (long long)o * v <= SMALL_OV_MAX && 2LL * o * v + (long long)v * v + (long long)o * o <= SMALL_LDS_DOUBLES;
 }
 hipError_t prepare_small();  // one-time kernel attributes (dynamic LDS); call outside graph capture
 hipError_t launch_small_2e(hipStream_t s, int b_dtype, const void *Bov, const void *Boo, const void *Bvv,
-                           const float *X, int o, int v, int nq, int ns, int nsplit, float cx, float *P);
-hipError_t launch_small_epi(hipStream_t s, int prec, int R, int o, int v, int nslab, int stage, int use_field,
-                            int want_trace, double dt, const DevPulse *pulses, DevState *st, const double *D,
-                            const float *P, const double *moo, const double *mov, const double *mvv,
-                            const double *Xin, double *c, double *c0, double *acc, double *acc0, double *xs64,
-                            double *xs0, float *x32, __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, double *normref);
+                           const float *X, int o, int v, int nq, int ns, int nsplit, float cx, float *P,
+                           const FieldArgs &f);
 // Epilogue grid: blocks per RHS along ia (the energy partial sums come one per block)
 constexpr int EP_BX_MAX = 2048;
 int epilogue_blocks(long long ov);
@@ -126,7 +134,7 @@ hipError_t launch_to_bf16x2(hipStream_t s, const double *c, long long n, float *
 constexpr int GEMV1_CHUNKS_MAX = 16;
 int gemv1_chunks(int nq, int ov);
 hipError_t launch_gemv1(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns, int nes,
-                        float *dpart);
+                        float *dpart, const FieldArgs &f);
 hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *dpart, int nes, int nq, int ov, int ns,
                         int nsplit, float *P);
 // The same pair on the FP32 matrix cores for batches of many slices (the context's 2 max_rhs >= 32):
@@ -135,8 +143,7 @@ hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *
 int coulomb_mfma_chunks(int nq, int ov);
 hipError_t launch_coulomb_mfma(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns,
                                int nes, int nsplit, float *dpart, float *P);
-hipError_t launch_field(hipStream_t s, const double *X, const double *X0, const double *moo, const double *mov,
-                        const double *mvv, int o, int v, int R, double *F, double *part, DevState *st);
+hipError_t launch_field(hipStream_t s, const FieldArgs &f);
 hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, double dt, const DevPulse *pulses,
                          DevState *st, const double *part, double *sc, double *c0, double *acc0, double *xs0,
                          double *out, double *normref, double *s0);

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "field.h"
 
 namespace rttda {
 
@@ -133,10 +134,15 @@ constexpr int row_epl() {
 
 template <typename TB, int QT, int ST, int EPL>
 __global__ __launch_bounds__(256) void k_gemv1(const TB *__restrict__ B, const float *__restrict__ X, int nq, int ov,
-                                               int ns, int echunk, float *__restrict__ dpart) {
+                                               int ns, int echunk, float *__restrict__ dpart, FieldArgs f) {
   static_assert(QT * ST <= 64, "one reduced value per lane");
-  const int q0 = blockIdx.x * QT, s0 = blockIdx.y * ST;
-  const int e0 = blockIdx.z * echunk, e1 = min(ov, e0 + echunk);
+  if ((int)blockIdx.x < f.blocks) {
+    field_block(f, blockIdx.x);
+    return;
+  }
+  const int nqb = (nq + QT - 1) / QT, nsb = (ns + ST - 1) / ST, lb = (int)blockIdx.x - f.blocks;
+  const int q0 = lb % nqb * QT, s0 = lb / nqb % nsb * ST, ez = lb / (nqb * nsb);
+  const int e0 = ez * echunk, e1 = min(ov, e0 + echunk);
   const int nqv = min(QT, nq - q0), nsv = min(ST, ns - s0);
   float acc[QT][ST];
 #pragma unroll
@@ -201,7 +207,7 @@ __global__ __launch_bounds__(256) void k_gemv1(const TB *__restrict__ B, const f
   if (threadIdx.x < QT * ST) {
     const int k = threadIdx.x, a = k / ST, b = k % ST;
     if (a < nqv && b < nsv)
-      dpart[((size_t)blockIdx.z * nq + q0 + a) * ns + s0 + b] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+      dpart[((size_t)ez * nq + q0 + a) * ns + s0 + b] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
   }
 }
 
@@ -324,111 +330,8 @@ __global__ __launch_bounds__(256) void k_gemv2(const TB *__restrict__ B, const f
   }
 }
 
-// ------------------------------------------------------------------------------------------------
-// Field product (FP64), eqs. sc2-sc5 in factorised form, on the FP64 matrix cores:
-//   F_p = X_p mu_vv - mu_oo X_p + sqrt2 mu_ov c0_p      (p = 0, 1: the real and imaginary planes)
-// plus per-block partial sums g_p = sqrt2 <mu_ov, X_p>, <X, F> and |X|^2.
-// One block per (RHS, 16 x 16 tile of (i, a)); 8 waves: waves 0-3 form plane 0, waves 4-7 plane 1,
-// each over a quarter of the contraction index (b for X mu_vv, j for mu_oo X) with
-// v_mfma_f64_16x16x4 (operands read straight from memory, four K steps' loads issued before their
-// MFMAs); the quarters are added in a fixed order through LDS.
-// f64 16x16x4 operand layout: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; the result
-// element t of lane l is D[4 t + l / 16][l % 16].
-// ------------------------------------------------------------------------------------------------
-typedef double d4v __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(512) void k_field(const double *__restrict__ X, const double *__restrict__ X0,
-                                               const double *__restrict__ moo, const double *__restrict__ mov,
-                                               const double *__restrict__ mvv, int o, int v,
-                                               double *__restrict__ F, double *__restrict__ part,
-                                               DevState *__restrict__ st) {
-  if (threadIdx.x == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0 && st->pend) {
-    st->step += 1;  // the step the last RK4 epilogue closed (nothing else in this kernel reads it)
-    st->pend = 0;
-  }
-  __shared__ double red[8][4][64];
-  __shared__ double sums[2][4];
-  const int at = blockIdx.x, it = blockIdx.y, r = blockIdx.z;
-  const int nbf = gridDim.x * gridDim.y, blk = it * gridDim.x + at;
-  const int i0 = it * FT_I, a0 = at * FT_A;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int p = wave >> 2, q = wave & 3;
-  const int m = lane & 15, g = lane >> 4;
-  const size_t ov = (size_t)o * v;
-  const double *Xp = X + ((size_t)r * 2 + p) * ov;
-  const double *moo_r = moo + (size_t)r * o * o;
-  const double *mov_r = mov + (size_t)r * ov;
-  const double *mvv_r = mvv + (size_t)r * v * v;
-  const int i = i0 + m, a = a0 + m;  // this lane's operand row (A) and column (B)
-  d4v acc = {0.0, 0.0, 0.0, 0.0};
-
-  // X_p mu_vv over b in this wave's quarter [bq, be)
-  {
-    const int kq = (((v + 3) / 4) + 3) / 4 * 4;
-    const int bq = q * kq, be = min(v, bq + kq);
-    for (int b0 = bq; b0 < be; b0 += 16) {
-      double xa[4], mb[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int b = b0 + 4 * u + g;
-        xa[u] = (i < o && b < be) ? Xp[(size_t)i * v + b] : 0.0;
-        mb[u] = (b < be && a < v) ? mvv_r[(size_t)b * v + a] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[u], mb[u], acc, 0, 0, 0);
-    }
-  }
-  // - mu_oo X_p over j in this wave's quarter [jq, je)
-  {
-    const int kq = (((o + 3) / 4) + 3) / 4 * 4;
-    const int jq = q * kq, je = min(o, jq + kq);
-    for (int j0 = jq; j0 < je; j0 += 16) {
-      double ma[4], xb[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + 4 * u + g;
-        ma[u] = (i < o && j < je) ? -moo_r[(size_t)i * o + j] : 0.0;
-        xb[u] = (j < je && a < v) ? Xp[(size_t)j * v + a] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u], xb[u], acc, 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) red[wave][t][lane] = acc[t];
-  __syncthreads();
-  // plane leaders (waves 0 and 4): add the quarters, + sqrt2 mu_ov c0_p, outputs, partial sums
-  if (q == 0) {
-    const double c0p = X0[2 * r + p];
-    double pg = 0.0, ptr = 0.0, pnr = 0.0;
-    double *Fp = F + ((size_t)r * 2 + p) * ov;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int ii = i0 + 4 * t + g, aa = a0 + m;
-      if (ii < o && aa < v) {
-        const size_t ia = (size_t)ii * v + aa;
-        const double mo = mov_r[ia], x = Xp[ia];
-        const double f = ((red[wave][t][lane] + red[wave + 1][t][lane]) + (red[wave + 2][t][lane] + red[wave + 3][t][lane])) +
-                         SQRT2 * mo * c0p;
-        Fp[ia] = f;
-        pg += SQRT2 * mo * x;
-        ptr += x * f;
-        pnr += x * x;
-      }
-    }
-    pg = wave_sum(pg);
-    ptr = wave_sum(ptr);
-    pnr = wave_sum(pnr);
-    if (lane == 0) {
-      sums[p][0] = p == 0 ? pg : 0.0;
-      sums[p][1] = p == 1 ? pg : 0.0;
-      sums[p][2] = ptr;
-      sums[p][3] = pnr;
-    }
-  }
-  __syncthreads();
-  if (tid < 4) part[((size_t)r * nbf + blk) * PART_STRIDE + tid] = sums[0][tid] + sums[1][tid];
-}
+// The field product as a launch of its own (see field.h)
+__global__ __launch_bounds__(256) void k_field(FieldArgs f) { field_block(f, blockIdx.x); }
 
 // ------------------------------------------------------------------------------------------------
 // Stage scalars of one right-hand side, by one block of 256 threads: its pulse field E(t_stage), the
@@ -772,17 +675,25 @@ __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab
   double en = 0.0;  // this thread's part of <X, A X>
   for (size_t ia0 = blockIdx.x * (size_t)64; ia0 < ov; ia0 += (size_t)nbe * 64) {
     const size_t ia = ia0 + lane;
-    const size_t ib = (size_t)r * 2 * ov + ia;
+    // the update's operands are under way while the slabs are summed (from a clamped place and of any
+    // plane, where they are not used)
+    const int p = wave & 1, q = 1 - p;  // waves 0 and 1: plane p's update takes plane q's sigma
+    const size_t im = (size_t)r * 2 * ov + (ia < ov ? ia : ov - 1);
+    const size_t ip = im + p * ov, iq = im + q * ov;
+    const double x = Xin[iq], d = D[im - (size_t)r * 2 * ov];
+    const double f = use_field ? F[iq] : 0.0;
+    double y = 0.0, ya = 0.0;
+    if (mode == EP_RK4) {
+      y = stage == 0 ? Xin[ip] : stage == 3 ? 0.0 : c[ip];
+      ya = stage == 0 ? 0.0 : acc[ip];
+    }
     double ps[2];
-    slab_sum<2>(P, slab, ov, nslab, ib, ia < ov, ps);
+    slab_sum<2>(P, slab, ov, nslab, im, ia < ov, ps);
     if (wave >= 2 || ia >= ov) continue;
-    const int p = wave, q = 1 - p;  // this wave updates plane p from plane q's sigma
-    const size_t ip = ib + p * ov, iq = ib + q * ov;
-    const double x = Xin[iq];
-    double sg = D[ia] * x + ps[q];
+    double sg = d * x + ps[q];
     if (epart) en += x * sg;
     if (mode == EP_ENERGY) continue;
-    if (use_field) sg -= Esh * F[iq];
+    if (use_field) sg -= Esh * f;
     if (mode == EP_SIGMA) {
       s_out[iq] = sg;
       continue;
@@ -790,15 +701,14 @@ __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab
     const double k = p == 0 ? sg : -sg;
     double n;
     if (stage == 0) {
-      const double y = Xin[ip];
       acc[ip] = y + dt / 6.0 * k;
       n = y + 0.5 * dt * k;
     } else if (stage == 3) {
-      n = acc[ip] + dt / 6.0 * k;
+      n = ya + dt / 6.0 * k;
       c[ip] = n;
     } else {
-      acc[ip] += dt / 3.0 * k;
-      n = c[ip] + ((stage == 1) ? 0.5 * dt : dt) * k;
+      acc[ip] = ya + dt / 3.0 * k;
+      n = y + ((stage == 1) ? 0.5 * dt : dt) * k;
     }
     if (stage != 3) xs64[ip] = n;
     x32[ip] = (float)n;
@@ -992,15 +902,16 @@ int gemv1_chunks(int nq, int ov) {
 }
 
 template <typename TB>
-static void gemv1_st(hipStream_t s, const TB *B, const float *X, int nq, int ov, int ns, int nes, float *dpart) {
+static void gemv1_st(hipStream_t s, const TB *B, const float *X, int nq, int ov, int ns, int nes, float *dpart,
+                     const FieldArgs &f) {
   constexpr int QT = 8;
   const int echunk = nes == 1 ? ov : (((ov + nes - 1) / nes) + 1023) / 1024 * 1024;
   auto go = [&](auto st) {
     constexpr int ST = decltype(st)::value;
-    const dim3 grid((nq + QT - 1) / QT, (ns + ST - 1) / ST, nes);
+    const dim3 grid(f.blocks + (nq + QT - 1) / QT * ((ns + ST - 1) / ST) * nes);
     auto run = [&](auto epl) {
       hipLaunchKernelGGL((k_gemv1<TB, QT, ST, decltype(epl)::value>), grid, dim3(256), 0, s, B, X, nq, ov, ns, echunk,
-                         dpart);
+                         dpart, f);
     };
     if (ov % row_epl<TB>() == 0) run(std::integral_constant<int, row_epl<TB>()>{});
     else if (ov % 4 == 0) run(std::integral_constant<int, 4>{});
@@ -1013,11 +924,11 @@ static void gemv1_st(hipStream_t s, const TB *B, const float *X, int nq, int ov,
 }
 
 hipError_t launch_gemv1(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns, int nes,
-                        float *dpart) {
+                        float *dpart, const FieldArgs &f) {
   if (b_dtype == RTTDA_BF16)
-    gemv1_st(s, static_cast<const __hip_bfloat16 *>(B), X, nq, ov, ns, nes, dpart);
+    gemv1_st(s, static_cast<const __hip_bfloat16 *>(B), X, nq, ov, ns, nes, dpart, f);
   else
-    gemv1_st(s, static_cast<const float *>(B), X, nq, ov, ns, nes, dpart);
+    gemv1_st(s, static_cast<const float *>(B), X, nq, ov, ns, nes, dpart, f);
   return hipGetLastError();
 }
 
@@ -1050,10 +961,8 @@ hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *
   return hipGetLastError();
 }
 
-hipError_t launch_field(hipStream_t s, const double *X, const double *X0, const double *moo, const double *mov,
-                        const double *mvv, int o, int v, int R, double *F, double *part, DevState *st) {
-  dim3 grid(field_blocks_a(v), field_blocks_i(o), R);
-  hipLaunchKernelGGL(k_field, grid, dim3(512), 0, s, X, X0, moo, mov, mvv, o, v, F, part, st);
+hipError_t launch_field(hipStream_t s, const FieldArgs &f) {
+  if (f.blocks > 0) hipLaunchKernelGGL(k_field, dim3(f.blocks), dim3(256), 0, s, f);
   return hipGetLastError();
 }
 

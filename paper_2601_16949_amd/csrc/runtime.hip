@@ -57,7 +57,7 @@ constexpr int SJ_MAX = 8;    // Coulomb second-product Q splits
 constexpr int SK_MAX = 768;  // exchange Q splits
 // exchange flops per stage (at the largest RHS count) from which the Coulomb pair gets its own stream
 constexpr double OVERLAP_MIN_FLOPS = 5e10;
-constexpr int SMALL_SPLITS = 64;
+constexpr int SMALL_BLOCKS = 512;  // workgroups of the small path's partial-sum launch: two per CU
 // slices (2 max_rhs) from which the Coulomb pair runs on the matrix cores
 constexpr int COUL_MFMA_MIN_SLICES = 32;
 // the exchange's partial K slabs (one per split) take at most this much workspace, or 32 slabs
@@ -100,7 +100,7 @@ Layout make_layout(int o, int v, int nq, int R, int prec, size_t slab_bytes = SK
     off += up(bytes > 0 ? bytes : 1);
     return at;
   };
-  L.nbf = field_blocks_a(v) * field_blocks_i(o);
+  L.nbf = field_blocks(o, v);
   L.sj_max = nq > 0 ? std::min(SJ_MAX, nq) : 0;
   L.sk_max = nq > 0 ? std::min({SK_MAX, nq, (int)std::max<size_t>(32, slab_bytes / (ns * ov * 4))}) : 0;
   L.D = take(ov * 8);
@@ -526,6 +526,11 @@ size_t scratch_for(const rttda_ctx *ctx, int ns) {
   return (size_t)qc * ctx->v * ns * xgemm_op(ctx->o) * 4;
 }
 
+FieldArgs field_args(const rttda_ctx *ctx, const double *X, const double *X0, int nrhs) {
+  return {X,      X0,         ctx->moo(),   ctx->mov(),        ctx->mvv(), ctx->o, ctx->v,
+          ctx->F(), ctx->part(), ctx->state(), nrhs * ctx->L.nbf};
+}
+
 // What a launch's slices are: both planes of every RHS (RK4, sigma, Davidson batches), one plane per
 // RHS (split operator) or a single vector (Lanczos).  The split count goes by this and the context's
 // largest RHS count, not by the call's, so that a batch and a single RHS sum alike.
@@ -553,15 +558,21 @@ void default_overlap(rttda_ctx *ctx) {
 }
 
 // Coulomb + exchange partials for the current stage input (x32 or xhi/xlo), `ns` real slices
-rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPLEX) {
-  if (ctx->nq == 0) return RTTDA_OK;
+// (f: a field product of the same stage input, carried by the first launch where that has blocks to spare)
+rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPLEX, FieldArgs f = FieldArgs{}) {
   const int ov = (int)ctx->ov;
   hipStream_t s = ctx->stream;
   const bool pr = ctx->prof.on;
+  if (f.blocks > 0 && (ctx->nq == 0 || (ctx->coul_mfma && !ctx->small))) {
+    if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
+    HIP_TRY(launch_field(s, f));
+    if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
+  }
+  if (ctx->nq == 0) return RTTDA_OK;
   if (ctx->small) {
     if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
     HIP_TRY(launch_small_2e(s, ctx->d.b_dtype, ctx->d.b_ov, ctx->d.b_oo, ctx->d.b_vv, ctx->x32(), ctx->o, ctx->v,
-                            ctx->nq, ns, ctx->small_splits, (float)ctx->d.cx, ctx->P()));
+                            ctx->nq, ns, ctx->small_splits, (float)ctx->d.cx, ctx->P(), f));
     if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
     return RTTDA_OK;
   }
@@ -578,7 +589,7 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
                                 coulomb_mfma_chunks(ctx->nq, ov), ctx->sj, ctx->dvec(), ctx->P()));
   } else {
     const int nes = gemv1_chunks(ctx->nq, ov);
-    HIP_TRY(launch_gemv1(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->x32(), ctx->nq, ov, ns, nes, ctx->dvec()));
+    HIP_TRY(launch_gemv1(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->x32(), ctx->nq, ov, ns, nes, ctx->dvec(), f));
     HIP_TRY(launch_gemv2(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->dvec(), nes, ctx->nq, ov, ns, ctx->sj, ctx->P()));
   }
   if (pr) HIP_TRY(ctx->prof.end(PC_COULOMB, sc));
@@ -607,36 +618,13 @@ rttda_status enqueue_step(rttda_ctx *ctx, int nrhs, double dt, bool has_field, b
                           double *c0, double *c) {
   hipStream_t s = ctx->stream;
   const int o = ctx->o, v = ctx->v;
-  if (ctx->small) {  // two launches per stage
-    for (int stage = 0; stage < 4; ++stage) {
-      double *Xin = stage == 0 ? c : ctx->xs64();
-      rttda_status st = enqueue_two_electron(ctx, 2 * nrhs);
-      if (st != RTTDA_OK) return st;
-      const bool pr = ctx->prof.on;
-      if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
-      if (corr && stage == 0) HIP_TRY(launch_corr(s, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
-      if (pops && stage == 0) HIP_TRY(launch_pop(s, nrhs, ctx->ov, c, ctx->state()));
-      HIP_TRY(launch_small_epi(s, ctx->prec, nrhs, o, v, nslab(ctx), stage, has_field ? 1 : 0, stage == 0 ? 1 : 0, dt,
-                               ctx->pulses(), ctx->state(), ctx->D(), ctx->P(), ctx->moo(), ctx->mov(), ctx->mvv(), Xin,
-                               c, c0, ctx->acc(), ctx->acc0(), ctx->xs64(), ctx->xs0(), ctx->x32(), ctx->xhi(),
-                               ctx->xlo(), ctx->normref()));
-      if (pr) HIP_TRY(ctx->prof.end(PC_EPILOGUE, s));
-    }
-    (void)energy;  // the small epilogue writes the energy sample itself (stage 0)
-    return RTTDA_OK;
-  }
   for (int stage = 0; stage < 4; ++stage) {
     double *Xin = stage == 0 ? c : ctx->xs64();
     double *X0 = stage == 0 ? c0 : ctx->xs0();
-    rttda_status st = enqueue_two_electron(ctx, 2 * nrhs);
-    if (st != RTTDA_OK) return st;
-    const bool need_field = stage == 0 || has_field;
     const bool pr = ctx->prof.on;
-    if (need_field) {
-      if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
-      HIP_TRY(launch_field(s, Xin, X0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
-      if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
-    }
+    rttda_status st = enqueue_two_electron(ctx, 2 * nrhs, SL_COMPLEX,
+                                           stage == 0 || has_field ? field_args(ctx, Xin, X0, nrhs) : FieldArgs{});
+    if (st != RTTDA_OK) return st;
     if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
     int mode = 0;
     if (stage == 0) mode |= SM_TRACE;
@@ -665,17 +653,16 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
   double *W = ctx->xs64(), *W0 = ctx->xs0();
   rttda_status st;
   if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
-  HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+  HIP_TRY(launch_field(s, field_args(ctx, c, c0, nrhs)));
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, SM_TRACE, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), c0,
                         ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   if (corr) HIP_TRY(launch_corr(s, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
   if (pops) HIP_TRY(launch_pop(s, nrhs, ctx->ov, c, ctx->state()));
   if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
   for (int half = 0; half < 2; ++half) {  // 0: drift (stage node 1/2), 1: kick (node 1)
-    if ((st = enqueue_two_electron(ctx, nrhs, SL_REAL)) != RTTDA_OK) return st;
+    st = enqueue_two_electron(ctx, nrhs, SL_REAL, has_field ? field_args(ctx, W, W0, nrhs) : FieldArgs{});
+    if (st != RTTDA_OK) return st;
     if (pr) HIP_TRY(ctx->prof.begin(PC_EPILOGUE, s));
-    if (has_field)
-      HIP_TRY(launch_field(s, W, W0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
     if (has_field || half == 1)
       HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, half == 0 ? 1 : 3,
                             (has_field ? SM_EFIELD : 0) | (half == 1 ? SM_INC : 0), dt, ctx->pulses(), ctx->state(),
@@ -692,10 +679,9 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
 rttda_status enqueue_sso_start(rttda_ctx *ctx, int nrhs, double dt, bool has_field, double *c0, double *c) {
   hipStream_t s = ctx->stream;
   HIP_TRY(launch_plane_copy(s, ctx->prec, nrhs, ctx->ov, 0, c, ctx->x32(), ctx->xhi(), ctx->xlo()));
-  rttda_status st = enqueue_two_electron(ctx, nrhs, SL_REAL);
+  rttda_status st =
+      enqueue_two_electron(ctx, nrhs, SL_REAL, has_field ? field_args(ctx, c, c0, nrhs) : FieldArgs{});
   if (st != RTTDA_OK) return st;
-  if (has_field)
-    HIP_TRY(launch_field(s, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, has_field ? SM_EFIELD : 0, dt, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx, SL_REAL), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
@@ -872,7 +858,7 @@ rttda_status sigma_enqueue(rttda_ctx *ctx, int nrhs, const double *c0, const dou
   HIP_TRY(launch_mu_blocks(hs, ctx->d.mu, ctx->pulses(), ctx->o, ctx->v, nrhs, ctx->moo(), ctx->mov(), ctx->mvv()));
   if ((st = to_stage_copy(ctx, c, nrhs)) != RTTDA_OK) return st;
   if ((st = enqueue_two_electron(ctx, 2 * nrhs)) != RTTDA_OK) return st;
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+  HIP_TRY(launch_field(hs, field_args(ctx, c, c0, nrhs)));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_SIGMA0 | SM_KEEP_E, 0.0, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), const_cast<double *>(c0), ctx->acc0(), ctx->xs0(), nullptr,
                         ctx->normref(), s0));
@@ -940,12 +926,12 @@ rttda_status rttda_create(const rttda_desc *desc, rttda_ctx **out) {
     default_launch(ctx);
     ctx->sj = L.sj_max;
     default_overlap(ctx);
-    // the small path: at most 2e9 exchange flops per stage (a few tens of microseconds of FP32 FMA);
-    // up to SMALL_SPLITS Q ranges (the epilogue adds one slab per range)
-    ctx->small_splits = std::max(1, std::min({SMALL_SPLITS, ctx->nq, L.sj_max + L.sk_max}));
+    // the small path's Q ranges (the update adds one slab per range): one Q each where that takes no more than
+    // SMALL_BLOCKS workgroups (o10 v40 N_Q120, one RHS, 16 steps: 120 ranges 0.90 ms, 64 1.02 ms; with
+    // eight RHS 64 ranges, 1024 workgroups, 1.70 ms and 120 2.02 ms)
+    ctx->small_splits = std::max(1, std::min({SMALL_BLOCKS / (2 * ctx->R), ctx->nq, L.sj_max + L.sk_max}));
     ctx->coul_mfma = 2 * ctx->R >= COUL_MFMA_MIN_SLICES ? 1 : 0;
-    // the default only for the smallest problems (8 launches per RK4 step instead of 21; each of
-    // its launches takes longer, so from about 2e7 exchange flops per stage it loses)
+    // the default only for the smallest problems (see SMALL_DEFAULT_FLOPS)
     ctx->small = small_fits(ctx->o, ctx->v, ctx->R) &&
                          4.0 * ctx->nq * (double)ctx->ov * (ctx->o + ctx->v) * ctx->R <= SMALL_DEFAULT_FLOPS
                      ? 1
@@ -1134,7 +1120,7 @@ rttda_status rttda_dipole_trace(rttda_ctx *ctx, int32_t nrhs, const double *dir,
   drop_graph(ctx);
   hipStream_t hs = ctx->stream;
   HIP_TRY(launch_mu_blocks(hs, ctx->d.mu, ctx->pulses(), ctx->o, ctx->v, nrhs, ctx->moo(), ctx->mov(), ctx->mvv()));
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), ctx->o, ctx->v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+  HIP_TRY(launch_field(hs, field_args(ctx, c, c0, nrhs)));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_OUT, 0.0, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
                         const_cast<double *>(c0), ctx->acc0(), ctx->xs0(), out, ctx->normref(), nullptr));
   return RTTDA_OK;
@@ -1190,13 +1176,12 @@ rttda_status exact_kick_terms(rttda_ctx *ctx, int nrhs, const rttda_pulse *pulse
 
 rttda_status exact_kick_apply(rttda_ctx *ctx, int nrhs, int J, double *c0, double *c) {
   hipStream_t hs = ctx->stream;
-  const int o = ctx->o, v = ctx->v;
   const long long ov = (long long)ctx->ov;
   double *T = ctx->xs64(), *T0 = ctx->xs0();
   HIP_TRY(hipMemcpyAsync(T, c, (size_t)2 * nrhs * ov * sizeof(double), hipMemcpyDeviceToDevice, hs));
   HIP_TRY(hipMemcpyAsync(T0, c0, (size_t)2 * nrhs * sizeof(double), hipMemcpyDeviceToDevice, hs));
   for (int j = 1; j <= J; ++j) {
-    HIP_TRY(launch_field(hs, T, T0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+    HIP_TRY(launch_field(hs, field_args(ctx, T, T0, nrhs)));
     HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, 0, 0.0, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), T0,
                           ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
     HIP_TRY(launch_kick_term(hs, nrhs, (int)ov, ctx->pulses(), ctx->F(), ctx->sc(), 1.0 / j, T, T0, c, c0));
@@ -1275,7 +1260,7 @@ rttda_status propagate_impl(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse *pul
   HIP_TRY(launch_set_state(hs, ctx->state(), step0, trace, norms, corr, pops, popU, popk, energy, ctx->epart(),
                            epilogue_blocks((long long)ctx->ov), resume ? 1 : 0));
   if (has_kick && step0 == 0) {
-    HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+    HIP_TRY(launch_field(hs, field_args(ctx, c, c0, nrhs)));
     HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, 0, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(), c0,
                           ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
     HIP_TRY(launch_kick(hs, nrhs, (int)ctx->ov, ctx->pulses(), ctx->F(), ctx->sc(), c, c0));
@@ -1346,17 +1331,7 @@ rttda_status propagate_impl(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse *pul
   // final samples at step0 + n_steps
   if (corr) HIP_TRY(launch_corr(hs, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
   if (pops) HIP_TRY(launch_pop(hs, nrhs, ctx->ov, c, ctx->state()));
-  if (ctx->small && integ == INTEG_RK4) {  // the small epilogue's own sums, as at every step
-    if (energy) {  // the energy sample needs one more product A c
-      if ((st = to_stage_copy(ctx, c, nrhs)) != RTTDA_OK) return st;
-      if ((st = enqueue_two_electron(ctx, 2 * nrhs)) != RTTDA_OK) return st;
-    }
-    HIP_TRY(launch_small_epi(hs, ctx->prec, nrhs, o, v, energy ? nslab(ctx) : 0, -1, 0, 1, dt, ctx->pulses(),
-                             ctx->state(), ctx->D(), ctx->P(), ctx->moo(), ctx->mov(), ctx->mvv(), c, c, c0, ctx->acc(),
-                             ctx->acc0(), ctx->xs64(), ctx->xs0(), ctx->x32(), ctx->xhi(), ctx->xlo(), ctx->normref()));
-    return RTTDA_OK;
-  }
-  HIP_TRY(launch_field(hs, c, c0, ctx->moo(), ctx->mov(), ctx->mvv(), o, v, nrhs, ctx->F(), ctx->part(), ctx->state()));
+  HIP_TRY(launch_field(hs, field_args(ctx, c, c0, nrhs)));
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_TRACE, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
                         c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
   if (energy) {  // the final energy sample needs one more product A c

@@ -81,3 +81,42 @@ def test_stage_update_over_few_and_many_slabs(gpu_lib, o, v, nq, prec):
                 assert np.linalg.norm(got[r] - S) <= TOL_STEP[prec] * np.linalg.norm(S)
                 assert np.max(np.abs(energy[:, r].cpu().numpy() - en)) <= TOL_STEP[prec] * np.max(np.abs(en))
                 assert np.max(np.abs(tr[:, r] - mu)) <= TOL_STEP[prec] * np.max(np.abs(mu))
+
+
+@pytest.mark.parametrize("o,v,nrhs", [(1, 1, 1), (2, 15, 2), (16, 16, 1), (17, 33, 2), (15, 64, 1), (9, 65, 3),
+                                      (33, 129, 1), (64, 67, 2), (5, 257, 1)])
+def test_field_product_tiles_alone_and_beside_other_launches(gpu_lib, o, v, nrhs):
+    """The FP64 field product at the edges of its tiles and contraction quarters: the dipole expectation
+    (its own launch), and steps under a field, where the small path's and the first Coulomb product's
+    launches carry it, from graphs and directly."""
+    import torch
+
+    nq = 24
+    prob = I.make_problem(I.Shape(o, v, nq, 0.05, storage="f32"), 3 * o + v)
+    op = O.Operator.from_problem(prob)
+    c0, c = I.random_state(o, v, nrhs, seed=o)
+    dirs = np.random.default_rng(o + v).standard_normal((nrhs, 3))
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, "fp32"), max_rhs=nrhs)
+    c0d, cd = gpu_lib.to_planes(c0, c)
+    mu = ctx.dipole_trace(dirs, c0d, cd).cpu().numpy()
+    for r in range(nrhs):  # FP64 throughout
+        ref = O.dipole_expectation(O.dipole_blocks(op, dirs[r] / np.linalg.norm(dirs[r])), c0[r], c[r])
+        assert abs(mu[r] - ref) <= 1e-12 * max(1.0, abs(ref)), r
+    pulses = [I.Pulse(kind=I.PULSE_CW, e0=0.05, omega=0.6, phase=0.4, direction=tuple(dirs[r] / np.linalg.norm(dirs[r])))
+              for r in range(nrhs)]
+    dt, n = 0.05, 4
+    ref = [O.propagate(op, pulses[r], dt, n) for r in range(nrhs)]
+    for path in (1, 2):
+        for graph in (1, 2):
+            ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, "fp32"), max_rhs=nrhs)
+            try:
+                ctx.set_tuning(small_path=path, use_graph=graph, steps_per_graph=2)
+            except gpu_lib.RttdaError:
+                continue  # (too large for the small path)
+            say(f"[field] o={o} v={v} nrhs={nrhs} path {path} graph {graph}")
+            g0, g = gpu_lib.ground_state(nrhs, o, v)
+            tr = ctx.propagate(pulses, dt, n, g0, g).cpu().numpy()
+            got = gpu_lib.from_planes(g0, g)[1]
+            for r, (t, c0f, cf) in enumerate(ref):
+                assert np.max(np.abs(tr[:, r] - t)) <= TOL_STEP["fp32"] * np.max(np.abs(t))
+                assert np.linalg.norm(got[r] - cf) <= TOL_STEP["fp32"] * np.linalg.norm(cf)
