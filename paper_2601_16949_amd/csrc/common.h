@@ -167,15 +167,21 @@ hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, int n
                              __hip_bfloat16 *xlo);
 hipError_t launch_plane_copy(hipStream_t s, int prec, int R, size_t ov, int plane, const double *c, float *x32,
                              __hip_bfloat16 *xhi, __hip_bfloat16 *xlo);
-// Lanczos guard: block partial sums (at most LZ_BLOCKS_MAX) are written to part[] and added on the host
+// Lanczos guard: a launch's block partial sums (at most LZ_BLOCKS_MAX) are added by the next launch, which
+// leaves the coefficient in device memory; at most LZ_STEPS_MAX steps
 constexpr int LZ_BLOCKS_MAX = 1024;
+constexpr int LZ_STEPS_MAX = 500;
 int lz_blocks(long long n);
 hipError_t launch_lz_init(hipStream_t s, long long n, double *v, double *part);
+// w = A v - beta vprev (beta: device, or null for 0), part = <w, v>
 hipError_t launch_lz_apply(hipStream_t s, long long n, int nslab, const double *D, const float *P, const double *v,
-                           const double *vprev, double beta, double *w, double *part);
-hipError_t launch_lz_orth(hipStream_t s, long long n, const double *v, double alpha, double *w, double *part);
-hipError_t launch_lz_next(hipStream_t s, int prec, long long n, double scale, const double *w, double *v,
-                          double *vprev, float *x32, __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, int shift);
+                           const double *vprev, const double *beta, double *w, double *part);
+// alpha = sum dots, w -= alpha v, part = <w, w>
+hipError_t launch_lz_orth(hipStream_t s, long long n, const double *v, const double *dots, double *alpha, double *w,
+                          double *part);
+// beta = sqrt(sum dots), vprev = v (shift), v = w / beta and its stage copies
+hipError_t launch_lz_next(hipStream_t s, int prec, long long n, const double *dots, double *beta, const double *w,
+                          double *v, double *vprev, float *x32, __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, int shift);
 // Block Davidson (lowest eigenpairs of A) and populations: FP64 vectors of n = o*v stored one after
 // another; per-block partial sums (at most DV_BLOCKS_MAX per vector) are added on the host.
 constexpr int DV_BLOCKS_MAX = 1024;

@@ -588,13 +588,29 @@ __global__ __launch_bounds__(256) void k_lz_init(long long n, double *__restrict
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
+// Sum of a launch's nb block partials, by a whole block of 256 threads (threads over blocks, waves by
+// shuffles, the waves in order): every block of the next launch forms it for itself, so that no launch and no
+// copy to the host stand between the dot products and their use
+__device__ __forceinline__ double lz_total(const double *__restrict__ part, int nb) {
+  __shared__ double sh[4];
+  __shared__ double tot;
+  double t = 0.0;
+  for (int k = threadIdx.x; k < nb; k += 256) t += part[k];
+  t = block_sum(t, sh);
+  if (threadIdx.x == 0) tot = t;
+  __syncthreads();
+  return tot;
+}
+
 // w = A v - beta vprev, part = <w, v>; a block of 256 threads holds 64 elements at a time, its waves
 // share the slabs
 __global__ __launch_bounds__(256) void k_lz_apply(long long n, int nslab, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ v,
-                                                  const double *__restrict__ vprev, double beta,
-                                                  double *__restrict__ w, double *__restrict__ part) {
+                                                  const double *__restrict__ vprev,
+                                                  const double *__restrict__ pbeta, double *__restrict__ w,
+                                                  double *__restrict__ part) {
   __shared__ double sh[4];
+  const double beta = pbeta ? *pbeta : 0.0;
   double acc = 0.0;
   for (long long e0 = blockIdx.x * 64LL; e0 < n; e0 += (long long)gridDim.x * 64) {
     const long long e = e0 + (threadIdx.x & 63);
@@ -610,9 +626,12 @@ __global__ __launch_bounds__(256) void k_lz_apply(long long n, int nslab, const 
 }
 
 // w -= alpha v, part = |w|^2
-__global__ __launch_bounds__(256) void k_lz_orth(long long n, const double *__restrict__ v, double alpha,
+__global__ __launch_bounds__(256) void k_lz_orth(long long n, const double *__restrict__ v,
+                                                 const double *__restrict__ dots, double *__restrict__ alpha_out,
                                                  double *__restrict__ w, double *__restrict__ part) {
   __shared__ double sh[4];
+  const double alpha = lz_total(dots, gridDim.x);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = alpha;
   double acc = 0.0;
   for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
     const double x = w[e] - alpha * v[e];
@@ -625,10 +644,13 @@ __global__ __launch_bounds__(256) void k_lz_orth(long long n, const double *__re
 
 // vprev = v; v = w * scale; FP32 (+ BF16 hi/lo) copy of v for the next product
 template <int PREC>
-__global__ __launch_bounds__(256) void k_lz_next(long long n, double scale, const double *__restrict__ w,
+__global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__restrict__ dots,
+                                                 double *__restrict__ beta_out, const double *__restrict__ w,
                                                  double *__restrict__ v, double *__restrict__ vprev,
                                                  float *__restrict__ x32, __hip_bfloat16 *__restrict__ xhi,
                                                  __hip_bfloat16 *__restrict__ xlo, int shift) {
+  const double b = sqrt(fmax(lz_total(dots, gridDim.x), 0.0)), scale = 1.0 / b;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *beta_out = b;
   for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
     if (shift) vprev[e] = v[e];
     const double x = w[e] * scale;
@@ -1026,21 +1048,22 @@ hipError_t launch_lz_init(hipStream_t s, long long n, double *v, double *part) {
   return hipGetLastError();
 }
 hipError_t launch_lz_apply(hipStream_t s, long long n, int nslab, const double *D, const float *P, const double *v,
-                           const double *vprev, double beta, double *w, double *part) {
+                           const double *vprev, const double *beta, double *w, double *part) {
   hipLaunchKernelGGL(k_lz_apply, dim3(lz_blocks(n)), dim3(256), 0, s, n, nslab, D, P, v, vprev, beta, w, part);
   return hipGetLastError();
 }
-hipError_t launch_lz_orth(hipStream_t s, long long n, const double *v, double alpha, double *w, double *part) {
-  hipLaunchKernelGGL(k_lz_orth, dim3(lz_blocks(n)), dim3(256), 0, s, n, v, alpha, w, part);
+hipError_t launch_lz_orth(hipStream_t s, long long n, const double *v, const double *dots, double *alpha, double *w,
+                          double *part) {
+  hipLaunchKernelGGL(k_lz_orth, dim3(lz_blocks(n)), dim3(256), 0, s, n, v, dots, alpha, w, part);
   return hipGetLastError();
 }
-hipError_t launch_lz_next(hipStream_t s, int prec, long long n, double scale, const double *w, double *v,
-                          double *vprev, float *x32, __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, int shift) {
+hipError_t launch_lz_next(hipStream_t s, int prec, long long n, const double *dots, double *beta, const double *w,
+                          double *v, double *vprev, float *x32, __hip_bfloat16 *xhi, __hip_bfloat16 *xlo, int shift) {
   if (prec == RTTDA_PREC_MIXED_BF16)
-    hipLaunchKernelGGL((k_lz_next<1>), dim3(lz_blocks(n)), dim3(256), 0, s, n, scale, w, v, vprev, x32, xhi, xlo,
+    hipLaunchKernelGGL((k_lz_next<1>), dim3(lz_blocks(n)), dim3(256), 0, s, n, dots, beta, w, v, vprev, x32, xhi, xlo,
                        shift);
   else
-    hipLaunchKernelGGL((k_lz_next<0>), dim3(lz_blocks(n)), dim3(256), 0, s, n, scale, w, v, vprev, x32, xhi, xlo,
+    hipLaunchKernelGGL((k_lz_next<0>), dim3(lz_blocks(n)), dim3(256), 0, s, n, dots, beta, w, v, vprev, x32, xhi, xlo,
                        shift);
   return hipGetLastError();
 }

@@ -134,7 +134,7 @@ Layout make_layout(int o, int v, int nq, int R, int prec, size_t slab_bytes = SK
                                          xgemm_o_bytes(o, L.scratch_bytes / ((size_t)v * ns * xgemm_op(o) * 4))
                                    : 0);
   L.lz = take(3 * ov * 8);
-  L.lzp = take((size_t)LZ_BLOCKS_MAX * 8);
+  L.lzp = take((size_t)(2 * LZ_BLOCKS_MAX + 2 * LZ_STEPS_MAX + 1) * 8);
   L.total = off;
   return L;
 }
@@ -1398,42 +1398,36 @@ rttda_status rttda_propagate_sso(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse
 
 rttda_status rttda_spectral_radius(rttda_ctx *ctx, int32_t n_iter, double *rho, double *rho_bound) {
   if (!ctx || !rho || !rho_bound) return fail(RTTDA_E_INVAL, "NULL argument");
-  if (n_iter < 2 || n_iter > 500) return fail(RTTDA_E_INVAL, "n_iter %d outside 2..500", n_iter);
+  if (n_iter < 2 || n_iter > LZ_STEPS_MAX) return fail(RTTDA_E_INVAL, "n_iter %d outside 2..%d", n_iter, LZ_STEPS_MAX);
   hipStream_t hs = ctx->stream;
   const long long n = (long long)ctx->ov;
-  double *v = ctx->lz(), *vprev = v + n, *w = v + 2 * n, *part = ctx->lzp();
-  const int nb = lz_blocks(n);
-  std::vector<double> hp(nb);
-  auto host_sum = [&](double &out) -> rttda_status {
-    HIP_TRY(hipMemcpyAsync(hp.data(), part, nb * sizeof(double), hipMemcpyDeviceToHost, hs));
-    HIP_TRY(hipStreamSynchronize(hs));
-    out = 0.0;
-    for (double t : hp) out += t;
-    return RTTDA_OK;
-  };
+  double *v = ctx->lz(), *vprev = v + n, *w = v + 2 * n;
+  // block partials of <w, v> and <w, w>, then the coefficients: all of them are formed on the device and read
+  // once at the end (a copy to the host and back per dot product cost 40 of a step's 137 us at o48 v360
+  // N_Q960)
+  double *pa = ctx->lzp(), *pb = pa + LZ_BLOCKS_MAX, *da = pb + LZ_BLOCKS_MAX, *db = da + LZ_STEPS_MAX;
   rttda_status st;
-  double n0 = 0.0;
-  HIP_TRY(launch_lz_init(hs, n, w, part));
-  if ((st = host_sum(n0)) != RTTDA_OK) return st;
+  HIP_TRY(launch_lz_init(hs, n, w, pb));
   HIP_TRY(hipMemsetAsync(vprev, 0, n * sizeof(double), hs));
-  HIP_TRY(launch_lz_next(hs, ctx->prec, n, 1.0 / std::sqrt(n0), w, v, vprev, ctx->x32(), ctx->xhi(), ctx->xlo(), 0));
-  std::vector<double> alpha, beta;
-  double bj = 0.0, blast = 0.0;
+  HIP_TRY(launch_lz_next(hs, ctx->prec, n, pb, db + LZ_STEPS_MAX, w, v, vprev, ctx->x32(), ctx->xhi(), ctx->xlo(), 0));
   const int kmax = (int)std::min<long long>(n_iter, n);
   for (int j = 0; j < kmax; ++j) {
     if (ctx->nq > 0 && (st = enqueue_two_electron(ctx, 1, SL_ONE)) != RTTDA_OK) return st;
-    double aj = 0.0, b2 = 0.0;
-    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx, SL_ONE), ctx->D(), ctx->P(), v, vprev, bj, w, part));
-    if ((st = host_sum(aj)) != RTTDA_OK) return st;
-    HIP_TRY(launch_lz_orth(hs, n, v, aj, w, part));
-    if ((st = host_sum(b2)) != RTTDA_OK) return st;
+    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx, SL_ONE), ctx->D(), ctx->P(), v, vprev, j ? db + j - 1 : nullptr, w, pa));
+    HIP_TRY(launch_lz_orth(hs, n, v, pa, da + j, w, pb));
+    HIP_TRY(launch_lz_next(hs, ctx->prec, n, pb, db + j, w, v, vprev, ctx->x32(), ctx->xhi(), ctx->xlo(), 1));
+  }
+  double co[2 * LZ_STEPS_MAX];
+  HIP_TRY(hipMemcpyAsync(co, da, sizeof(co), hipMemcpyDeviceToHost, hs));
+  HIP_TRY(hipStreamSynchronize(hs));
+  std::vector<double> alpha, beta;
+  double blast = 0.0;
+  for (int j = 0; j < kmax; ++j) {
+    const double aj = co[j], b = co[LZ_STEPS_MAX + j];
     alpha.push_back(aj);
-    const double b = std::sqrt(std::max(b2, 0.0));
     blast = b;
     if (j + 1 == kmax || !(b > 1e-13 * std::max(1.0, std::fabs(aj)))) break;  // done, or invariant subspace
     beta.push_back(b);
-    HIP_TRY(launch_lz_next(hs, ctx->prec, n, 1.0 / b, w, v, vprev, ctx->x32(), ctx->xhi(), ctx->xlo(), 1));
-    bj = b;
   }
   const int k = (int)alpha.size();
   const double tmin = tridiag_eig(alpha, beta, 0), tmax = tridiag_eig(alpha, beta, k - 1);

@@ -120,3 +120,18 @@ def test_field_product_tiles_alone_and_beside_other_launches(gpu_lib, o, v, nrhs
             for r, (t, c0f, cf) in enumerate(ref):
                 assert np.max(np.abs(tr[:, r] - t)) <= TOL_STEP["fp32"] * np.max(np.abs(t))
                 assert np.linalg.norm(got[r] - cf) <= TOL_STEP["fp32"] * np.linalg.norm(cf)
+
+
+@pytest.mark.parametrize("o,v,nq,gaps", [(4, 5, 3, 1), (8, 33, 7, 2), (3, 4, 2, 3)])
+def test_spectral_radius_where_the_start_spans_an_invariant_space(gpu_lib, o, v, nq, gaps):
+    """A with `gaps` distinct eigenvalues (no two-electron part): Lanczos ends after that many steps, and the
+    steps queued behind its end leave the answer alone."""
+    prob = I.make_problem(I.Shape(o, v, nq, 0.05, storage="f32"), 5)
+    prob.b_ov[:], prob.b_oo[:], prob.b_vv[:] = 0, 0, 0
+    prob.e_occ[:] = -0.5
+    prob.e_virt[:] = 0.25 + 0.5 * (np.arange(v) * gaps // v)
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, "fp32"), max_rhs=1)
+    rho, bound = ctx.spectral_radius(n_iter=20)
+    top = prob.e_virt[-1] + 0.5
+    say(f"[lanczos] {gaps} distinct gaps: rho {rho!r} bound {bound!r} exact {top!r}")
+    assert abs(rho - top) <= 1e-12 * top and top * (1 - 1e-12) <= bound <= top * (1 + 1e-6)
