@@ -142,7 +142,7 @@ hipError_t launch_gemv2(hipStream_t s, int b_dtype, const void *B, const float *
 // dpart, then the partial slabs P[split][s][ia] of J.
 int coulomb_mfma_chunks(int nq, int ov);
 hipError_t launch_coulomb_mfma(hipStream_t s, int b_dtype, const void *B, const float *X, int nq, int ov, int ns,
-                               int nes, int nsplit, float *dpart, float *P);
+                               int nes, int nsplit, float *dpart, float *P, const FieldArgs &f);
 hipError_t launch_field(hipStream_t s, const FieldArgs &f);
 hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, double dt, const DevPulse *pulses,
                          DevState *st, const double *part, double *sc, double *c0, double *acc0, double *xs0,

@@ -563,7 +563,7 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   const int ov = (int)ctx->ov;
   hipStream_t s = ctx->stream;
   const bool pr = ctx->prof.on;
-  if (f.blocks > 0 && (ctx->nq == 0 || (ctx->coul_mfma && !ctx->small))) {
+  if (f.blocks > 0 && ctx->nq == 0) {
     if (pr) HIP_TRY(ctx->prof.begin(PC_FIELD, s));
     HIP_TRY(launch_field(s, f));
     if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
@@ -586,7 +586,7 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   if (pr) HIP_TRY(ctx->prof.begin(PC_COULOMB, sc));
   if (ctx->coul_mfma) {
     HIP_TRY(launch_coulomb_mfma(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->x32(), ctx->nq, ov, ns,
-                                coulomb_mfma_chunks(ctx->nq, ov), ctx->sj, ctx->dvec(), ctx->P()));
+                                coulomb_mfma_chunks(ctx->nq, ov), ctx->sj, ctx->dvec(), ctx->P(), f));
   } else {
     const int nes = gemv1_chunks(ctx->nq, ov);
     HIP_TRY(launch_gemv1(sc, ctx->d.b_dtype, ctx->d.b_ov, ctx->x32(), ctx->nq, ov, ns, nes, ctx->dvec(), f));

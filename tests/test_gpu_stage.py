@@ -135,3 +135,35 @@ def test_spectral_radius_where_the_start_spans_an_invariant_space(gpu_lib, o, v,
     top = prob.e_virt[-1] + 0.5
     say(f"[lanczos] {gaps} distinct gaps: rho {rho!r} bound {bound!r} exact {top!r}")
     assert abs(rho - top) <= 1e-12 * top and top * (1 - 1e-12) <= bound <= top * (1 + 1e-6)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+@pytest.mark.parametrize("o,v,nq,nrhs", [(5, 7, 3, 16), (9, 33, 70, 16), (8, 40, 64, 31), (7, 9, 65, 32), (6, 25, 33, 33),
+                                         (11, 13, 129, 47), (8, 16, 31, 64), (5, 5, 40, 70)])
+def test_coulomb_batches_match_oracle(gpu_lib, o, v, nq, nrhs, prec):
+    """The matrix-core Coulomb pair over its widths (32, 64 and 128 slices and more than one such block) and
+    rows that do and do not come in fours; under a field, which the first launch carries."""
+    import torch
+
+    prob = I.make_problem(I.Shape(o, v, nq, 0.05, cx=0.0, storage="f32" if prec == "fp32" else "bf16"), 77 + o)
+    op = O.Operator.from_problem(prob)
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, prec), max_rhs=nrhs)
+    ctx.set_tuning(small_path=2)
+    assert ctx.get_tuning()["coulomb_path"] == 2
+    c0, c = I.random_state(o, v, nrhs, seed=o + v)
+    dirs = [I.AXES[r % 3] for r in range(nrhs)]
+    field = [0.01 * ((r % 5) - 2) for r in range(nrhs)]
+    c0d, cd = gpu_lib.to_planes(c0, c)
+    _, sd = ctx.sigma(field, dirs, c0d, cd)
+    torch.cuda.synchronize()
+    s = gpu_lib.from_planes(torch.zeros_like(c0d), sd)[1]
+    for r in range(nrhs):
+        ref = O.apply_H(op, O.dipole_blocks(op, dirs[r]), field[r], c0[r], c[r])[1]
+        assert np.linalg.norm(s[r] - ref) <= TOL_J * np.linalg.norm(ref), r
+    say(f"[coulomb batches] {prec} o={o} v={v} nq={nq} nrhs={nrhs}")
+    pulses = [I.Pulse(kind=I.PULSE_CW, e0=0.05, omega=0.6, phase=0.1 * r, direction=dirs[r]) for r in range(nrhs)]
+    g0, g = gpu_lib.ground_state(nrhs, o, v)
+    tr = ctx.propagate(pulses, 0.05, 2, g0, g).cpu().numpy()
+    for r in (0, nrhs - 1):
+        t, _, _ = O.propagate(op, pulses[r], 0.05, 2)
+        assert np.max(np.abs(tr[:, r] - t)) <= TOL_STEP[prec] * np.max(np.abs(t))
