@@ -317,15 +317,16 @@ typedef struct rttda_tuning {
   int32_t steps_per_graph;  /* RK4 steps captured in one graph                              */
   int32_t exchange_chunk;   /* Q values per chunk of the large-o GEMM exchange path (its W
                                scratch holds W hi/lo for one chunk, so at most what fits);
-                               -1 = as many as fit (the default)                           */
+                               -1 = the library's choice (the default): about as many as
+                               fit, in whole rounds of the chip's workgroups               */
   int32_t overlap;          /* 1 = the Coulomb pair runs on a second stream alongside the
                                exchange, 2 = both in order on the context's stream; the
                                default is 1 when the exchange has at least 5e10 flops per
                                stage at max_rhs and its kernel shares the CUs (not the
                                X-resident variants), else 2                                 */
   int32_t small_path;       /* 1 = small-problem path: per RK4 stage one launch for the
-                               Coulomb and exchange partial sums and one single-workgroup
-                               launch for the whole stage epilogue (o*v <= 2048,
+                               Coulomb and exchange partial sums and the field product and
+                               one for the stage update (o*v <= 2048,
                                2 o v + v^2 + o^2 <= 12288, max_rhs <= 64, n_aux > 0);
                                2 = the general kernels.  The default is 1 where the shape fits
                                and the exchange has at most 2e7 flops per stage at max_rhs

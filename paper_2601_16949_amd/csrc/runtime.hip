@@ -260,15 +260,15 @@ struct rttda_ctx {
   // Equal to sk for the other variants and once a tile or split count has been chosen by the caller.
   int sk_real = 0, sk_one = 0;
   int use_graph = 1, steps_per_graph = 8;
-  int qchunk = 0;  // Q per chunk of the GEMM exchange path, 0 = as many as the scratch holds
+  int qchunk = 0;  // Q per chunk of the GEMM exchange path, 0 = gemm_chunk's choice
   // second stream for the Coulomb pair, which then runs alongside the exchange (HBM-bound next to
   // MFMA-bound work); fork and join through two events, also inside a captured graph
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   int overlap = 2;  // 1: Coulomb pair on the second stream, 2: in order on the context's stream
   bool overlap_set = false;  // chosen by the caller (else it follows the exchange variant)
-  // small problems: the stage's Coulomb + exchange slabs in one launch (small_splits slabs) and the
-  // RK4 stage epilogue in one single-workgroup launch
+  // small problems: the stage's Coulomb + exchange slabs (small_splits of them) and field product in one
+  // launch
   int small = 0, small_splits = 0;
   // Coulomb pair on the matrix cores (batches of many slices) instead of the vector-unit GEMVs
   int coul_mfma = 0;
@@ -512,7 +512,7 @@ rttda_status check_dirs(const double *dir, int nrhs) {
 }
 
 // Scratch bytes handed to the exchange: the GEMM path sizes its Q chunk from them.  The chunk
-// length is fixed per context (what the scratch holds at the largest RHS count, or the tuned
+// length is fixed per context (gemm_chunk's choice at the largest RHS count, or the tuned
 // chunk), so a batch and a single RHS sum their Q chunks identically.
 size_t scratch_for(const rttda_ctx *ctx, int ns) {
   if (ctx->L.scratch_bytes == 0) return 0;
