@@ -55,9 +55,17 @@ constexpr size_t LDS_MAX = (size_t)160 << 10;  // a CU's LDS
 
 // BF: split BF16 (else FP32); JB 16-row blocks per slice, KS slices per workgroup, at most NCBM column
 // blocks per wave
-template <bool BF, int JB, int KS, int NCBM>
+// PK (FP32): two slices of at most 16 JB - 8 rows share 2 JB - 1 row blocks, the first eight rows of each in
+// the halves of the middle one, its other rows in the blocks on its side (so that a slice's sums run in one
+// order wherever it stands).  Where the matrix cores set the time, that is the work of o up to 24 or 40 rows
+// without a half-empty block per slice: o40 v300 N_Q1000, 64 RHS 10.4 -> 8.6 ms per launch (the best paired
+// LDS-staged tile: 9.3), o24 v168 N_Q600, 32 RHS 732 -> 610 us, o36 v252 N_Q900, 3 RHS 333 -> 308 us.
+template <bool BF, int JB, int KS, int NCBM, bool PK = false>
 struct CfgR {
-  static constexpr int RB = JB * KS;
+  static_assert(!PK || (!BF && KS == 2), "packed pairs: FP32, two slices");
+  static constexpr int RB = PK ? 2 * JB - 1 : JB * KS;  // row blocks of X and W
+  static constexpr int KB = JB * KS;                     // row blocks of K
+  static constexpr int OMAX = PK ? 16 * JB - 8 : 16 * JB;
   static constexpr int PL = BF ? 2 : 1;           // planes of X
   static constexpr int GV = BF ? 8 : 4;           // values per 16-byte group
   static constexpr int SZ = BF ? 2 : 4;           // bytes per factor value
@@ -129,18 +137,19 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
   return j0 < o && j >= j0 ? j : -1;
 }
 
-template <bool BF, int JB, int KS, int NCBM>
+template <bool BF, int JB, int KS, int NCBM, bool PK>
 __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__restrict__ Boo,
                                                                 const char *__restrict__ Bvv,
                                                                 const char *__restrict__ X,
                                                                 const char *__restrict__ Xlo, int o, int v, int nq,
                                                                 int ns, int n_sg, int nct, int ncg, int qs, int rem,
                                                                 int nsplit, float scale, float *__restrict__ P) {
-  using C = CfgR<BF, JB, KS, NCBM>;
-  constexpr int RB = C::RB, PL = C::PL, GV = C::GV, SZ = C::SZ;
+  using C = CfgR<BF, JB, KS, NCBM, PK>;
+  constexpr int RB = C::RB, KB = C::KB, PL = C::PL, GV = C::GV, SZ = C::SZ;
   constexpr int D = 2;                       // double steps of B_vv in flight (three measure the same)
   constexpr int HA = (RB + 1) / 2;           // row blocks of the first half of a step
-  constexpr int NP = BF ? (JB + 1) / 2 : JB;  // K-product steps: pairs of row blocks (the last may be a single one)
+  // K-product steps: pairs of row blocks (the last may be a single one); packed: each slice's JB
+  constexpr int NP = BF ? (JB + 1) / 2 : PK ? 2 * JB : JB;
   extern __shared__ __attribute__((aligned(16))) char ldsr[];
 
   // XCD-aware logical block id (hardware deals workgroups to the 8 XCDs round robin): slice groups
@@ -163,7 +172,12 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
     const int row = lane >> 2, gl = lane & 3;  // four groups of 16 rows: 64 contiguous bytes per row
     for (int f = wave; f < nfrag; f += NWAVE) {
       const int st = f / RB, rb = f - st * RB;
-      const int sl = s_base + rb / JB, j = slot_row<BF, JB>((rb % JB) * 16 + row, o);
+      int sl = s_base + rb / JB, j = slot_row<BF, JB>((rb % JB) * 16 + row, o);
+      if constexpr (PK) {
+        const int up = rb > JB - 1 || (rb == JB - 1 && row >= 8) ? 1 : 0;  // second slice
+        sl = s_base + up;
+        j = slot_row<BF, JB>(rb == JB - 1 ? row & 7 : 8 + 16 * (up ? rb - JB : rb) + row, o);
+      }
       const int grp = odd_k && st == nst - 1 ? 4 * st + gl : 8 * (st >> 1) + 2 * gl + (st & 1);
       const bool live = sl < ns && j >= 0 && grp < ng;
       const int a0 = grp == ng - 1 ? v - GV : GV * grp;  // first value of the group's load
@@ -201,11 +215,15 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   auto run = [&](auto ncb_tag, int b0, int qa, int qb, int part, int nparts, int grp, int pstride)
                  __attribute__((always_inline)) {
     constexpr int NCB = decltype(ncb_tag)::value;
-    f4 K[RB][NCB], W[RB][NCB];
+    f4 K[KB][NCB], W[RB][NCB];
+#pragma unroll
+    for (int a = 0; a < KB; ++a)
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) K[a][c] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int a = 0; a < RB; ++a)
 #pragma unroll
-      for (int c = 0; c < NCB; ++c) K[a][c] = W[a][c] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < NCB; ++c) W[a][c] = f4{0.f, 0.f, 0.f, 0.f};
     // byte offset of the first of the two rows (columns of the output) this lane loads; the second is
     // the row after it, or the last one
     unsigned roff[NCB];
@@ -276,7 +294,9 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
         int ln = lane;  // (once per Q: offsets recomputed rather than held in registers)
         asm volatile("" : "+v"(ln));
         const int g = ln >> 4, n = ln & 15;
-        const int j0 = pair ? 32 * p + 8 * g : (BF ? 32 : 16) * p + 4 * g;
+        // (packed: the middle block first, whose two halves are the slices' rows 0..7)
+        const int j0 = PK ? (p % JB == 0 ? 4 * (g & 1) : 16 * (p % JB) - 8 + 4 * g)
+                          : pair ? 32 * p + 8 * g : (BF ? 32 : 16) * p + 4 * g;
         const int j = j0 + w <= o ? j0 : j0 < o ? o - w : 0;
         const char *Oq = Boo + (size_t)q * o * o * SZ;
 #pragma unroll
@@ -330,6 +350,19 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
                         __builtin_bit_cast(s4v, u2{F[ib][0], F[ib][1]}),
                         __builtin_bit_cast(s4v, u2{w[s][c][h][0], w[s][c][h][1]}), k, 0, 0, 0);
                 }
+        } else if constexpr (PK) {
+          const int s = p / JB, pp = p % JB, blk = pp == 0 ? JB - 1 : s * JB + pp - 1;
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) {
+              // (the other slice's half of the middle block is left out, whatever it holds)
+              const float w = pp == 0 && (g >= 2) != (s == 1) ? 0.f : W[blk][c][t];
+#pragma unroll
+              for (int ib = 0; ib < JB; ++ib)
+                K[s * JB + ib][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f4, F[ib])[t], w,
+                                                                         K[s * JB + ib][c], 0, 0, 0);
+            }
         } else {
 #pragma unroll
           for (int t = 0; t < 4; ++t)
@@ -420,21 +453,21 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
     };
     if (nparts == 1) {
 #pragma unroll
-      for (int a = 0; a < RB; ++a)
+      for (int a = 0; a < KB; ++a)
 #pragma unroll
         for (int c = 0; c < NCB; ++c) store(a, c, K[a][c]);
       return;
     }
     // the parts' sums meet in LDS (X is no longer needed), added in order, the blocks dealt to the parts
-    constexpr int SLOT = RB * NCBM * 1024;
+    constexpr int SLOT = KB * NCBM * 1024;
     __syncthreads();
 #pragma unroll
-    for (int a = 0; a < RB; ++a)
+    for (int a = 0; a < KB; ++a)
 #pragma unroll
       for (int c = 0; c < NCB; ++c)
         *reinterpret_cast<f4 *>(ldsr + (size_t)wave * SLOT + (a * NCB + c) * 1024 + lane * 16) = K[a][c];
     __syncthreads();
-    for (int f = part; f < RB * NCB; f += nparts) {
+    for (int f = part; f < KB * NCB; f += nparts) {
       f4 k = f4{0.f, 0.f, 0.f, 0.f};
       for (int p = 0; p < nparts; ++p)
         k += *reinterpret_cast<const f4 *>(ldsr + (size_t)(p * pstride + grp) * SLOT + f * 1024 + lane * 16);
@@ -470,41 +503,41 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   }
 }
 
-template <bool BF, int JB, int KS, int NCBM>
+template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t launch_xres(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o, int v,
                        int nq, int ns, int nsplit, float scale, float *P, void *, size_t) {
-  using C = CfgR<BF, JB, KS, NCBM>;
-  if (o > 16 * JB || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || nsplit > nq)
+  using C = CfgR<BF, JB, KS, NCBM, PK>;
+  if (o > C::OMAX || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || nsplit > nq)
     return hipErrorInvalidValue;
   const Split sp = choose_split(v, NCBM);
   const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;  // K steps
-  const size_t lds = std::max((size_t)nst * C::STEP_LDS, sp.qs > 1 || sp.rem ? (size_t)NWAVE * C::RB * NCBM * 1024 : (size_t)0);
+  const size_t lds = std::max((size_t)nst * C::STEP_LDS, sp.qs > 1 || sp.rem ? (size_t)NWAVE * C::KB * NCBM * 1024 : (size_t)0);
   if (lds > LDS_MAX) return hipErrorInvalidValue;
   const int n_sg = (ns + KS - 1) / KS;
   const int total = n_sg * sp.nct * nsplit;
   const dim3 grid((total + 7) / 8 * 8);
-  hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM>), grid, dim3(64 * NWAVE), lds, s,
+  hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM, PK>), grid, dim3(64 * NWAVE), lds, s,
                      static_cast<const char *>(Boo), static_cast<const char *>(Bvv), static_cast<const char *>(X),
                      static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, nsplit,
                      scale, P);
   return hipGetLastError();
 }
 
-template <bool BF, int JB, int KS, int NCBM>
+template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t prepare_xres() {
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM>),
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
 }
 
 // What auto_splits needs of a shape: workgroups per Q split, Q subranges per workgroup, and the cycles
 // of a workgroup per Q (of one subrange) and before its first.
-template <bool BF, int JB, int KS, int NCBM>
+template <bool BF, int JB, int KS, int NCBM, bool PK>
 void shape_xres(int v, int ns, ResShape *r) {
-  using C = CfgR<BF, JB, KS, NCBM>;
+  using C = CfgR<BF, JB, KS, NCBM, PK>;
   const Split sp = choose_split(v, NCBM);
   const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;
   const double per_block = (double)nst * C::RB * (BF ? 2 * 16 : 4 * 32) +
-                           (BF ? 2 * 16 * ((JB + 1) / 2) : 4 * 32 * JB) * (double)C::RB;  // matrix cycles per Q
+                           (BF ? 2 * 16 * ((JB + 1) / 2) : 4 * 32 * JB) * (double)C::KB;  // matrix cycles per Q
   const int nb = ((v + 15) / 16 + sp.nct - 1) / sp.nct;
   r->tiles = (ns + KS - 1) / KS * sp.nct;
   r->qs = sp.qs;
@@ -515,16 +548,19 @@ void shape_xres(int v, int ns, ResShape *r) {
 
 // Column blocks per wave: as many as keep the accumulators, the ring and two halves of a step's X
 // within (about) the 256 registers of two waves per SIMD.
-#define XRES(BF, JB, KS, NCBM, NAME)                                                                               \
+#define XRES_(BF, JB, KS, NCBM, PK, NAME)                                                                          \
   ExchangeVariant {                                                                                                \
-    BF ? RTTDA_PREC_MIXED_BF16 : RTTDA_PREC_FP32, 16 * JB, KS, 16 * NWAVE * NCBM, NAME, &launch_xres<BF, JB, KS, NCBM>, \
-        LDS_MAX, &prepare_xres<BF, JB, KS, NCBM>, CfgR<BF, JB, KS, NCBM>::GV, 1, 1, JB > 1 ? 8 : 4, false, 3,      \
-        CfgR<BF, JB, KS, NCBM>::VMAX, &shape_xres<BF, JB, KS, NCBM>                                                \
+    BF ? RTTDA_PREC_MIXED_BF16 : RTTDA_PREC_FP32, CfgR<BF, JB, KS, NCBM, PK>::OMAX, KS, 16 * NWAVE * NCBM, NAME,   \
+        &launch_xres<BF, JB, KS, NCBM, PK>, LDS_MAX, &prepare_xres<BF, JB, KS, NCBM, PK>,                          \
+        CfgR<BF, JB, KS, NCBM, PK>::GV, 1, 1, JB > 1 ? 8 : 4, false, 3, CfgR<BF, JB, KS, NCBM, PK>::VMAX,          \
+        &shape_xres<BF, JB, KS, NCBM, PK>                                                                          \
   }
+#define XRES(BF, JB, KS, NCBM, NAME) XRES_(BF, JB, KS, NCBM, false, NAME)
 
 const ExchangeVariant kResF32[] = {
     XRES(false, 4, 1, 4, "f32r_o64"), XRES(false, 3, 1, 4, "f32r_o48"), XRES(false, 2, 2, 4, "f32r_o32_s2"),
     XRES(false, 2, 1, 5, "f32r_o32_s1"), XRES(false, 1, 2, 5, "f32r_o16_s2"),
+    XRES_(false, 3, 2, 3, true, "f32r_p40"), XRES_(false, 2, 2, 4, true, "f32r_p24"),
 };
 const ExchangeVariant kResBf16[] = {
     XRES(true, 4, 1, 4, "bf16x2r_o64"), XRES(true, 3, 1, 4, "bf16x2r_o48"), XRES(true, 2, 2, 4, "bf16x2r_o32_s2"),

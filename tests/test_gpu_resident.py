@@ -86,3 +86,41 @@ def test_resident_tile_is_the_default_for_every_alignment(gpu_lib, prec):
         for r, p in enumerate(pulses):
             ref = O.propagate_sso(op, p, 0.05, 3)[0]
             assert np.max(np.abs(tr[:, r] - ref)) / np.max(np.abs(ref)) < TOL[prec]
+
+
+@pytest.mark.parametrize("o,v,nq", [(17, 33, 5), (23, 40, 9), (24, 64, 6), (33, 47, 4), (39, 100, 7), (40, 96, 5)])
+def test_packed_pairs_keep_their_slices_apart(gpu_lib, o, v, nq):
+    """Two slices of different states share a packed tile in the split operator (one real plane per state):
+    each state of an odd batch gives the bits that it gives alone, in either half of a tile and next to a
+    state that is not finite, and follows the oracle."""
+    import torch
+    from paper_2601_16949_amd import rttda
+
+    prob = I.make_problem(I.Shape(o, v, nq, b_scale=0.05, storage="f32"), 17 + o)
+    op = O.Operator.from_problem(prob)
+    pulses = I.kick_pulses()
+    ctx = rttda.Context(rttda.DeviceProblem(prob, "fp32"), max_rhs=3)
+    name = "f32r_p24" if o <= 24 else "f32r_p40"
+    k = [k for k in range(1, ctx.lib.rttda_exchange_variants(ctx.desc.precision) + 1) if ctx.variant_name(k) == name]
+    ctx.set_tuning(exchange_variant=k[0], exchange_splits=min(3, nq), small_path=2)
+    say(f"[packed] {name} o={o} v={v} nq={nq}")
+
+    def run(idx, spoil=None):
+        c0, c = gpu_lib.ground_state(len(idx), o, v)
+        if spoil is not None:
+            c[spoil] = float("nan")
+        tr = ctx.propagate([pulses[r] for r in idx], 0.05, 6, c0, c, integrator="sso")
+        torch.cuda.synchronize()
+        return tr.cpu().numpy(), c
+
+    tr, c = run([0, 1, 2])
+    for r in range(3):
+        one, c1 = run([r])
+        assert np.array_equal(one[:, 0], tr[:, r]) and torch.equal(c1[0], c[r]), r
+        ref, _, _ = O.propagate_sso(op, pulses[r], 0.05, 6)
+        assert np.max(np.abs(tr[:, r] - ref)) <= 1e-5 * np.max(np.abs(ref)), r
+    for spoil in range(3):
+        bad, cb = run([0, 1, 2], spoil)
+        for r in range(3):
+            if r != spoil:
+                assert np.array_equal(bad[:, r], tr[:, r]) and torch.equal(cb[r], c[r]), (spoil, r)
