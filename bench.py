@@ -56,11 +56,12 @@ TRAFFIC = {
     ("bf16x2k64_o64_wc2_w8", "o60_v400_nq1500_kick_xyz", 220, 6):
         {"file": "exchange_bf16_dl.hip", "src": "f90b2171f434b93d",
          "fetch_bytes": 264290.89 * 1024 * 2.0, "write_bytes": 125895.47 * 1024 * 1.0},
-    # the GEMM path: one exchange stage is 25 chunks of 200 Q, each a k_xgemm_w + k_boo_w pair
-    ("bf16x2gemm_a256x256w8_b256x128w8", "o240_v1800_nq5000_kick_xyz_mixed", 8, 6):
-        {"file": "exchange_bf16_gemm.hip", "src": "7dc7d8bb3f4ee411",
-         "fetch_bytes": 25 * (8459398.4 + 1347847.4) * 1024 * 2.0,
-         "write_bytes": 25 * (2257817.4 + 96479.69) * 1024 * 1.0},
+    ("f32r_o64", "o60_v400_nq1500_kick_xyz", 42, 6):
+        {"file": "exchange_res.hip", "src": "4ac513fa6caa5001",
+         "fetch_bytes": 603471.58 * 1024 * 2.0, "write_bytes": 24919.92 * 1024 * 1.0},
+    ("bf16x2r_o64", "o60_v400_nq1500_kick_xyz", 42, 6):
+        {"file": "exchange_res.hip", "src": "4ac513fa6caa5001",
+         "fetch_bytes": 279773.81 * 1024 * 2.0, "write_bytes": 25584.86 * 1024 * 1.0},
 }
 PEAK = {"fp32": 157.3, "mixed": 2516.6}  # dense MFMA TFLOP/s: FP32, BF16
 HBM_PEAK_GBS = 8000.0
