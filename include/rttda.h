@@ -323,7 +323,7 @@ typedef struct rttda_tuning {
                                exchange, 2 = both in order on the context's stream; the
                                default is 1 when the exchange has at least 5e10 flops per
                                stage at max_rhs and its kernel shares the CUs (not the
-                               X-resident variants), else 2                                 */
+                               X-resident variants and the GEMM path), else 2               */
   int32_t small_path;       /* 1 = small-problem path: per RK4 stage one launch for the
                                Coulomb and exchange partial sums and the field product and
                                one for the stage update (o*v <= 2048,

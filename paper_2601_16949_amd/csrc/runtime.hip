@@ -543,7 +543,10 @@ int exchange_splits(const rttda_ctx *ctx, Slices k) {
 // Default splits of the current variant, and whether the Coulomb pair runs alongside it: only where
 // the exchange is long enough to cover the cost of the fork and join (small problems and many
 // concurrent contexts lose), and not next to an X-resident variant, whose workgroups leave no
-// registers for others on their CU.
+// registers for others on their CU, or the GEMM path, whose workgroups stay on theirs for a whole chunk
+// of Q (in order instead: o72 v256 N_Q960, one RHS 1480 -> 1366 us, o184 v1384 N_Q600, three RHS 56.1 ->
+// 53.5 ms, o240 v1800 N_Q1000, three RHS 167 -> 164 ms per two steps, 1.5 % faster over fifteen shapes,
+// the least of them, o160 v1200 with one RHS, 2 % slower).
 void default_launch(rttda_ctx *ctx) {
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
   const int cap = ctx->L.sk_max;
@@ -554,7 +557,7 @@ void default_launch(rttda_ctx *ctx) {
 void default_overlap(rttda_ctx *ctx) {
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
   const double flops = 4.0 * ctx->nq * (double)ctx->ov * (ctx->o + ctx->v) * ctx->R;
-  ctx->overlap = !x->res && flops >= OVERLAP_MIN_FLOPS ? 1 : 2;
+  ctx->overlap = !x->res && !x->scratch && flops >= OVERLAP_MIN_FLOPS ? 1 : 2;
 }
 
 // Coulomb + exchange partials for the current stage input (x32 or xhi/xlo), `ns` real slices
