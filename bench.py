@@ -278,7 +278,7 @@ def main():
     # time-step guard: Lanczos bound on rho(A) against the integrator's stability limit
     rho, rho_bound = ctx.spectral_radius(30)
     limit = 2.5 if args.integrator == "rk4" else 2.0
-    if rho_bound * wl.dt > limit:
+    if not rho_bound * wl.dt <= limit:
         raise SystemExit(f"refused: rho(A) dt <= {rho_bound * wl.dt:.3f} exceeds the stability limit {limit}")
     tun = ctx.get_tuning()
     c0, c = rttda.ground_state(R, dev.o, dev.v)

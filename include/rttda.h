@@ -279,6 +279,8 @@ rttda_status rttda_pool_usage(const rttda_pool *pool, size_t *used_bytes, int32_
  * *rho_bound adds the Ritz residual of the extreme pairs, so that rho(A) <= rho_bound up
  * to the rounding of the sigma product.  Classic RK4 is stable for rho(A) dt up to about
  * 2.83 (the split operator for rho(A) dt < 2); callers check rho_bound * dt before a run.
+ * Where the sigma product is not finite (factors that hold a NaN, or overflow FP32), rho_bound
+ * is not either: refuse with !(rho_bound * dt <= limit), which a NaN does not pass.
  * Synchronises the context's stream; uses the workspace's stage buffers (no effect on
  * the state of later rttda_propagate calls). */
 rttda_status rttda_spectral_radius(rttda_ctx *ctx, int32_t n_iter, double *rho, double *rho_bound);

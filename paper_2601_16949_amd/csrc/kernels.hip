@@ -649,7 +649,8 @@ __global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__re
                                                  double *__restrict__ v, double *__restrict__ vprev,
                                                  float *__restrict__ x32, __hip_bfloat16 *__restrict__ xhi,
                                                  __hip_bfloat16 *__restrict__ xlo, int shift) {
-  const double b = sqrt(fmax(lz_total(dots, gridDim.x), 0.0)), scale = 1.0 / b;
+  const double t = lz_total(dots, gridDim.x);
+  const double b = sqrt(t < 0.0 ? 0.0 : t), scale = 1.0 / b;  // (a NaN stays one: fmax would make it 0, "the end")
   if (blockIdx.x == 0 && threadIdx.x == 0) *beta_out = b;
   for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
     if (shift) vprev[e] = v[e];

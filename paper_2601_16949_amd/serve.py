@@ -160,7 +160,7 @@ class Server:
             trace = torch.empty((req.n_steps + 1, 1), dtype=torch.float64, device=self.device)
         if self.stability_steps > 0:
             _, bound = ctx.spectral_radius(self.stability_steps)
-            if bound * req.dt > RK4_LIMIT:
+            if not bound * req.dt <= RK4_LIMIT:  # (a bound that is not a number refuses too)
                 ctx.close()
                 why = f"rho(A) dt <= {bound * req.dt:.3f} exceeds the RK4 stability limit {RK4_LIMIT}"
                 self.results[req.rid] = Result(req.rid, req.shape.o, req.n_steps, req.arrival, now, now, None, why)
