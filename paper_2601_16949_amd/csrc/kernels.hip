@@ -667,6 +667,8 @@ __global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__re
 // A block of 256 threads holds 64 (i, a) of one RHS: its four waves share the slabs (a chain of load
 // latencies where there are many of them and few elements), then two of them update one plane each:
 // Re k = Im sigma and Im k = -Re sigma, so plane p's update takes the other plane's sigma.
+// Xin is c in stage 0 and xs64 after it, and one wave writes the plane of xs64 that the other has read: the
+// barriers of the slab sum stand between the two, and none of the three pointers is __restrict__.
 // The last block of each RHS carries its stage scalars (es.mode != 0), which nothing else here reads.
 // o24 v184 N_Q480, one RHS: 6.4 us; one thread per (i, a) summing every slab took 10.9 us, and the
 // scalars' own launch 4.1 us.
@@ -675,9 +677,8 @@ template <int PREC>
 __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab, int stage, int mode, int use_field,
                                                   double dt, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ F,
-                                                  double *__restrict__ sc, const double *__restrict__ Xin,
-                                                  double *__restrict__ c, double *__restrict__ acc,
-                                                  double *__restrict__ xs64, float *__restrict__ x32,
+                                                  double *__restrict__ sc, const double *Xin, double *c,
+                                                  double *__restrict__ acc, double *xs64, float *__restrict__ x32,
                                                   __hip_bfloat16 *__restrict__ xhi, __hip_bfloat16 *__restrict__ xlo,
                                                   double *__restrict__ s_out, double *__restrict__ epart, int nbe,
                                                   StageScalars es) {
