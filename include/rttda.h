@@ -313,7 +313,12 @@ rttda_status rttda_populations(rttda_ctx *ctx, int32_t k, const double *evecs, i
  * does not have, RTTDA_E_NOMEM when the splits do not fit the workspace. */
 typedef struct rttda_tuning {
   int32_t exchange_variant; /* index into the exchange tile table (1-based), 0 = auto      */
-  int32_t exchange_splits;  /* number of Q ranges the exchange is split into               */
+  int32_t exchange_splits;  /* number of partial sums over Q of a full launch (2 max_rhs
+                               slices); the library's own count of a variant leaves the
+                               launches on fewer slices theirs (split operator, time-step
+                               check).  An X-resident variant may add a sum from shorter
+                               ranges, which a call with few right-hand sides spreads over
+                               the CUs: the bits are the same either way               */
   int32_t coulomb_splits;   /* number of Q ranges the second Coulomb product is split into */
   int32_t use_graph;        /* 1 = replay RK4 steps from a captured HIP graph, 2 = direct  */
   int32_t steps_per_graph;  /* RK4 steps captured in one graph                              */

@@ -83,6 +83,12 @@ enum : int {
   SM_ENERGY = 128,  // energy sample at index step - step0 from the epilogue's partial sums
 };
 
+// Partial slabs of a stage's two-electron part: `n` of them to be added in FP64, the first `nc` as they are,
+// each of the others the FP32 sum, in order, of `grp` neighbours in memory.
+struct Slabs {
+  int n, nc, grp;
+};
+
 // Epilogue modes.
 enum : int { EP_RK4 = 0, EP_SIGMA = 1, EP_ENERGY = 2 };
 // Field product of `blocks` / field_blocks(o, v) right-hand sides (see field.h), as a launch of its own or
@@ -156,12 +162,12 @@ struct StageScalars {
   double *c0, *acc0, *xs0, *normref;
 };
 // epart != NULL: also the per-block partial sums of <X, A X> per RHS ([R][epilogue_blocks(ov)])
-hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, int nslab, int stage, int mode,
+hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, Slabs slabs, int stage, int mode,
                            int use_field, double dt, const double *D, const float *P, const double *F, double *sc,
                            const double *Xin, double *c, double *acc, double *xs64, float *x32, __hip_bfloat16 *xhi,
                            __hip_bfloat16 *xlo, double *s_out, double *epart = nullptr,
                            const StageScalars *scalars = nullptr);
-hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, int nslab, int mode, int use_field,
+hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, Slabs slabs, int mode, int use_field,
                              double dt, const double *D, const float *P, const double *F, const double *sc, double *c,
                              double *c0, double *W, double *W0, float *x32, __hip_bfloat16 *xhi,
                              __hip_bfloat16 *xlo);
@@ -254,6 +260,10 @@ struct ExchangeVariant {
   int rank = 0;          // preference among variants of equal tile waste (higher first)
   int v_max = 1 << 30;
   void (*res)(int v, int ns, struct ResShape *) = nullptr;  // X resident in LDS (one workgroup fills a CU)
+  // X-resident variants, of whose splits each is cut into m ranges of Q: nsplit slabs, either each the FP32 sum
+  // of its m ranges in order (in_slab) or one range each, every m of them to be added so by the reader
+  hipError_t (*launch_ranges)(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o,
+                              int v, int nq, int ns, int nsplit, int m, bool in_slab, float scale, float *P) = nullptr;
   int rows = 0;  // scratch variants: stacked rows per tile of the first GEMM (nt: its columns)
   int cols = 0;  //                   columns per tile of the second
   bool applies(int o, int v) const {

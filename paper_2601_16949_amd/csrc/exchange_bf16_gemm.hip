@@ -609,7 +609,7 @@ hipError_t prepare_xgemm() {
         &launch_xgemm<NWC, NWR, CB, RB, NWM, NWN, MB, NB>,                                              \
         std::max(CfgA<NWC, NWR, CB, RB>::LDS, CfgB<NWM, NWN, MB, NB>::LDS),                                  \
         &prepare_xgemm<NWC, NWR, CB, RB, NWM, NWN, MB, NB>, 8, 8, 1, XGEMM_O_MIN, true, 0, 1 << 30, nullptr,   \
-        CfgA<NWC, NWR, CB, RB>::TR, CfgB<NWM, NWN, MB, NB>::TN                                               \
+        nullptr, CfgA<NWC, NWR, CB, RB>::TR, CfgB<NWM, NWN, MB, NB>::TN                                               \
   }
 
 const ExchangeVariant kGemmVariants[] = {

@@ -103,15 +103,13 @@ inline Split choose_split(int v, int ncbm) {
     for (int ncg = 1; ncg <= NWAVE; ++ncg) {
       const int qs = NWAVE / ncg;
       for (int rem = 0; rem <= (qs == 1 ? std::min(ncbm, nb - 1) : 0); ++rem) {
+        if ((nb - rem + ncg - 1) / ncg > ncbm) continue;
         double load[4] = {0, 0, 0, 0};
-        int wmax = 0;
         for (int w = 0; w < ncg * qs; ++w) {
           int b0, width;
           group_blocks(nb, rem, ncg, w % ncg, b0, width);
           load[w % 4] += width ? cost(width) : 0.0;
-          wmax = std::max(wmax, width);
         }
-        if (wmax > ncbm) continue;
         const double c = nct * (std::max(std::max(load[0], load[1]), std::max(load[2], load[3])) / qs +
                                 (rem ? 2.0 * cost(rem) / NWAVE + 0.05 : 0.0));
         if (c < best - 1e-12) {
@@ -137,13 +135,23 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
   return j0 < o && j >= j0 ? j : -1;
 }
 
-template <bool BF, int JB, int KS, int NCBM, bool PK>
+// Each of a launch's splits is cut into m ranges of Q, whose sums are added in FP32, in order.  RNG: a workgroup
+// takes a split and adds them in its slab; else one takes a range, leaves its sum, and the stage update adds
+// them, with the same bits.  So a context whose full batch fills the CUs with long splits (few slabs, X staged
+// once) keeps short ones for a call with few of its right-hand sides, which would else run on a few CUs, and the
+// FP32 chains stay short in both: o40 v300 N_Q1000 FP32, max_rhs 64, 4 splits of 32 ranges: one RHS 1.6 ms per
+// step (34.9 without ranges), all 64 36.0 (35.6); o60 v400 N_Q1500, max_rhs 3, one RHS: 5.7 ms (13.9) in FP32, 42
+// splits of 3, and 2.0 (3.6) in split BF16, 42 of 2; all three 14.05 (13.98) and 3.83 (3.78).  (The second
+// phase's blocks, whose waves share the split's Q in eighths, are left out of that: the workgroup of a split's
+// first range takes them, the others' slabs hold zeros there.)
+template <bool BF, int JB, int KS, int NCBM, bool PK, bool RNG>
 __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__restrict__ Boo,
                                                                 const char *__restrict__ Bvv,
                                                                 const char *__restrict__ X,
                                                                 const char *__restrict__ Xlo, int o, int v, int nq,
                                                                 int ns, int n_sg, int nct, int ncg, int qs, int rem,
-                                                                int nsplit, float scale, float *__restrict__ P) {
+                                                                int nsplit, int m, float scale,
+                                                                float *__restrict__ P) {
   using C = CfgR<BF, JB, KS, NCBM, PK>;
   constexpr int RB = C::RB, KB = C::KB, PL = C::PL, GV = C::GV, SZ = C::SZ;
   constexpr int D = 2;                       // double steps of B_vv in flight (three measure the same)
@@ -204,7 +212,9 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
 
   const int nblk = (v + 15) / 16;
   const int t0 = tile_block(nblk, nct, ct), t1 = tile_block(nblk, nct, ct + 1);
-  const int qa0 = (int)((long long)sp * nq / nsplit), qb0 = (int)((long long)(sp + 1) * nq / nsplit);
+  const int n_split = RNG ? nsplit : nsplit / m, split = RNG ? sp : sp / m, range = RNG ? 0 : sp % m;
+  const int Qa = (int)((long long)split * nq / n_split), Qb = (int)((long long)(split + 1) * nq / n_split);
+  auto bound = [&](int k) { return Qa + k * (Qb - Qa) / m; };  // the split's ranges
 
   // byte offset of this lane's load in the last double step of a row: the row's last group ends at v
   const int odd = n & 1;
@@ -230,6 +240,43 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
     const unsigned row_bytes = (unsigned)(v * SZ), row_last = (unsigned)(v - 1) * row_bytes;
 #pragma unroll
     for (int c = 0; c < NCB; ++c) roff[c] = (unsigned)min((b0 + c) * 16 + (n & ~1), v - 1) * row_bytes;
+    // RNG: K to the slab; ranges after a split's first are added to what it holds
+    auto flush = [&](bool add) __attribute__((always_inline)) {
+      int ln = lane;  // (opaque here: addresses made from it would be held in registers through the loop)
+      asm volatile("" : "+v"(ln));
+      unsigned col[NCB];  // byte offsets, from clamped places
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) col[c] = 4u * min((b0 + c) * 16 + (ln & 15), v - 1);
+      auto slab = [&](int a) __attribute__((always_inline)) {
+        return reinterpret_cast<char *>(P + ((size_t)sp * ns + min(s_base + a / JB, ns - 1)) * o * v);
+      };
+      auto row = [&](int a, int t) __attribute__((always_inline)) {
+        return 4u * (unsigned)v * min((a % JB) * 16 + 4 * (ln >> 4) + t, o - 1);
+      };
+      f4 old[KB][NCB] = {};
+      if (add) {  // (all of them on their way before the first is used)
+#pragma unroll
+        for (int a = 0; a < KB; ++a)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c)
+              old[a][c][t] = *reinterpret_cast<const float *>(slab(a) + (row(a, t) + col[c]));
+      }
+#pragma unroll
+      for (int a = 0; a < KB; ++a)
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) {
+#pragma clang fp contract(off)  // (the stage update, which adds the ranges elsewhere, rounds each of them)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float x = scale * K[a][c][t];
+            if (s_base + a / JB < ns && (a % JB) * 16 + 4 * (ln >> 4) + t < o && (b0 + c) * 16 + (ln & 15) < v)
+              *reinterpret_cast<float *>(slab(a) + (row(a, t) + col[c])) = add ? old[a][c][t] + x : x;
+          }
+        }
+    };
+    int rg = 0, qf = RNG && nparts == 1 ? bound(1) : qb;  // RNG: ranges done, and the next one's end
     if (qa < qb) {
       const size_t qstride = (size_t)v * v * SZ;
       const char *ql = Bvv + (size_t)qa * qstride;  // Q and double step of the next load
@@ -421,6 +468,17 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
             if (p + 1 < NP) load_o(p & 1 ? of0 : of1, q, p + 1);
             mfma_k(p & 1 ? of1 : of0, p);
           }
+          if constexpr (RNG) {
+            if (q + 1 == qf && q + 1 < qb) {
+              flush(rg > 0);
+#pragma unroll
+              for (int a = 0; a < KB; ++a)
+#pragma unroll
+                for (int c = 0; c < NCB; ++c) K[a][c] = f4{0.f, 0.f, 0.f, 0.f};
+              ++rg;
+              qf = bound(rg + 1);
+            }
+          }
 #pragma unroll
           for (int a = 0; a < RB; ++a)
 #pragma unroll
@@ -441,7 +499,13 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
         if (q >= qb) break;
       }
     }
-    int ln = lane;  // (opaque here: addresses made from it would be held in registers through the loop)
+    if constexpr (RNG) {
+      if (nparts == 1) {
+        flush(rg > 0);
+        return;
+      }
+    }
+    int ln = lane;  // (opaque here too)
     asm volatile("" : "+v"(ln));
     auto store = [&](int a, int c, f4 k) __attribute__((always_inline)) {
       const int sl = s_base + a / JB, col = (b0 + c) * 16 + (ln & 15);
@@ -492,10 +556,12 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   };
   for (int phase = 0; phase < (rem ? 2 : 1); ++phase) {
     int cg = wave % ncg, part = wave / ncg, nparts = qs, pstride = ncg, b0 = 0, w = 0;
+    int qa0 = RNG ? Qa : bound(range), qb0 = RNG ? Qb : bound(range + 1);
     if (phase == 0) {
       if (part < qs) group_blocks(t1 - t0, rem, ncg, cg, b0, w);
     } else {
       cg = 0, part = wave, nparts = NWAVE, pstride = 1, b0 = t1 - t0 - rem, w = rem;
+      qa0 = Qa, qb0 = RNG || range == 0 ? Qb : Qa;
     }
     const int qa = qa0 + (int)((long long)part * (qb0 - qa0) / nparts);
     const int qb = qa0 + (int)((long long)(part + 1) * (qb0 - qa0) / nparts);
@@ -503,30 +569,48 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   }
 }
 
+// nsplit slabs, each the sum of its own m ranges (RNG) or every m of them to be added by the reader
 template <bool BF, int JB, int KS, int NCBM, bool PK>
-hipError_t launch_xres(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o, int v,
-                       int nq, int ns, int nsplit, float scale, float *P, void *, size_t) {
+hipError_t launch_xres_ranges(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o,
+                              int v, int nq, int ns, int nsplit, int m, bool in_slab, float scale, float *P) {
   using C = CfgR<BF, JB, KS, NCBM, PK>;
-  if (o > C::OMAX || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || nsplit > nq)
-    return hipErrorInvalidValue;
   const Split sp = choose_split(v, NCBM);
+  const long long ranges = in_slab ? (long long)nsplit * m : nsplit;
+  if (o > C::OMAX || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || m < 1 ||
+      ranges > nq || ranges % m != 0 || (m > 1 && sp.qs > 1))
+    return hipErrorInvalidValue;
   const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;  // K steps
   const size_t lds = std::max((size_t)nst * C::STEP_LDS, sp.qs > 1 || sp.rem ? (size_t)NWAVE * C::KB * NCBM * 1024 : (size_t)0);
   if (lds > LDS_MAX) return hipErrorInvalidValue;
   const int n_sg = (ns + KS - 1) / KS;
   const int total = n_sg * sp.nct * nsplit;
   const dim3 grid((total + 7) / 8 * 8);
-  hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM, PK>), grid, dim3(64 * NWAVE), lds, s,
-                     static_cast<const char *>(Boo), static_cast<const char *>(Bvv), static_cast<const char *>(X),
-                     static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, nsplit,
-                     scale, P);
+  auto go = [&](auto rng) {
+    hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM, PK, decltype(rng)::value>), grid, dim3(64 * NWAVE), lds, s,
+                       static_cast<const char *>(Boo), static_cast<const char *>(Bvv), static_cast<const char *>(X),
+                       static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, nsplit, m,
+                       scale, P);
+  };
+  if (in_slab && m > 1) go(std::true_type{});
+  else go(std::false_type{});
   return hipGetLastError();
 }
 
 template <bool BF, int JB, int KS, int NCBM, bool PK>
+hipError_t launch_xres(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o, int v,
+                       int nq, int ns, int nsplit, float scale, float *P, void *, size_t) {
+  return launch_xres_ranges<BF, JB, KS, NCBM, PK>(s, Boo, Bvv, X, Xlo, o, v, nq, ns, nsplit, 1, false, scale, P);
+}
+
+template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t prepare_xres() {
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+  const void *fn[] = {reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, false>),
+                      reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, true>)};
+  for (const void *f : fn) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // What auto_splits needs of a shape: workgroups per Q split, Q subranges per workgroup, and the cycles
@@ -553,7 +637,7 @@ void shape_xres(int v, int ns, ResShape *r) {
     BF ? RTTDA_PREC_MIXED_BF16 : RTTDA_PREC_FP32, CfgR<BF, JB, KS, NCBM, PK>::OMAX, KS, 16 * NWAVE * NCBM, NAME,   \
         &launch_xres<BF, JB, KS, NCBM, PK>, LDS_MAX, &prepare_xres<BF, JB, KS, NCBM, PK>,                          \
         CfgR<BF, JB, KS, NCBM, PK>::GV, 1, 1, JB > 1 ? 8 : 4, false, 3, CfgR<BF, JB, KS, NCBM, PK>::VMAX,          \
-        &shape_xres<BF, JB, KS, NCBM, PK>                                                                          \
+        &shape_xres<BF, JB, KS, NCBM, PK>, &launch_xres_ranges<BF, JB, KS, NCBM, PK>                               \
   }
 #define XRES(BF, JB, KS, NCBM, NAME) XRES_(BF, JB, KS, NCBM, false, NAME)
 

@@ -441,11 +441,12 @@ __global__ __launch_bounds__(256) void k_scalar(int R, int nbf, int stage, int m
 // apart.  (Slabs past a quarter read its last one again and are left out of the sum: a condition on the
 // load would make each wait for the one before it.)
 template <int NP>
-__device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t slab, size_t plane, int nslab, size_t e,
+__device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t slab, size_t plane, Slabs sb, size_t e,
                                          bool live, double (&out)[NP]) {
   __shared__ double quarter[4][NP][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int a = wave * nslab / 4, b = (wave + 1) * nslab / 4;
+  const int a = wave * sb.n / 4, b = (wave + 1) * sb.n / 4;
+  auto first = [&](int k) { return k < sb.nc ? k : sb.nc + (k - sb.nc) * sb.grp; };  // a slab's place in memory
   double t[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) t[p] = 0.0;
@@ -456,7 +457,20 @@ __device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t sla
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int p = 0; p < NP; ++p) x[p][u] = P[(size_t)min(sl + u, b - 1) * slab + p * plane + e];
+        for (int p = 0; p < NP; ++p) x[p][u] = P[(size_t)first(min(sl + u, b - 1)) * slab + p * plane + e];
+      for (int g = 1; g < sb.grp; ++g) {  // (a slab that stands alone reads itself again)
+        float y[NP][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = min(sl + u, b - 1);
+#pragma unroll
+          for (int p = 0; p < NP; ++p) y[p][u] = P[(size_t)(first(k) + (k < sb.nc ? 0 : g)) * slab + p * plane + e];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) x[p][u] = min(sl + u, b - 1) < sb.nc ? x[p][u] : x[p][u] + y[p][u];
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -484,7 +498,7 @@ __device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t sla
 // element of RHS r by the thread with ia == 0.
 // ------------------------------------------------------------------------------------------------
 template <int PREC>
-__global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, int nslab, int mode, int use_field, double dt,
+__global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, Slabs slabs, int mode, int use_field, double dt,
                                                     const double *__restrict__ D, const float *__restrict__ P,
                                                     const double *__restrict__ F, const double *__restrict__ sc,
                                                     double *__restrict__ c, double *__restrict__ c0,
@@ -498,7 +512,7 @@ __global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, int nsl
   for (size_t e0 = blockIdx.x * (size_t)64; e0 < total; e0 += (size_t)gridDim.x * 64) {
     const size_t e = e0 + (threadIdx.x & 63);
     double psum[1];
-    slab_sum<1>(P, slab, 0, nslab, e, e < total, psum);
+    slab_sum<1>(P, slab, 0, slabs, e, e < total, psum);
     if (threadIdx.x >= 64 || e >= total) continue;
     const size_t r = e / ov, ia = e - r * ov;
     const size_t iq = r * 2 * ov + ia, ip = iq + ov;
@@ -615,7 +629,7 @@ __global__ __launch_bounds__(256) void k_lz_apply(long long n, int nslab, const 
   for (long long e0 = blockIdx.x * 64LL; e0 < n; e0 += (long long)gridDim.x * 64) {
     const long long e = e0 + (threadIdx.x & 63);
     double p[1];
-    slab_sum<1>(P, (size_t)n, 0, nslab, (size_t)e, e < n, p);
+    slab_sum<1>(P, (size_t)n, 0, Slabs{nslab, 0, 1}, (size_t)e, e < n, p);
     if (threadIdx.x >= 64 || e >= n) continue;
     const double s = D[e] * v[e] + p[0] - beta * vprev[e];
     w[e] = s;
@@ -674,7 +688,7 @@ __global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__re
 // scalars' own launch 4.1 us.
 // ------------------------------------------------------------------------------------------------
 template <int PREC>
-__global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab, int stage, int mode, int use_field,
+__global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, Slabs slabs, int stage, int mode, int use_field,
                                                   double dt, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ F,
                                                   double *__restrict__ sc, const double *Xin, double *c,
@@ -712,7 +726,7 @@ __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, int nslab
       ya = stage == 0 ? 0.0 : acc[ip];
     }
     double ps[2];
-    slab_sum<2>(P, slab, ov, nslab, im, ia < ov, ps);
+    slab_sum<2>(P, slab, ov, slabs, im, ia < ov, ps);
     if (wave >= 2 || ia >= ov) continue;
     double sg = d * x + ps[q];
     if (epart) en += x * sg;
@@ -998,7 +1012,7 @@ hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, dou
   return hipGetLastError();
 }
 
-hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, int nslab, int stage, int mode,
+hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, Slabs slabs, int stage, int mode,
                            int use_field, double dt, const double *D, const float *P, const double *F, double *sc,
                            const double *Xin, double *c, double *acc, double *xs64, float *x32, __hip_bfloat16 *xhi,
                            __hip_bfloat16 *xlo, double *s_out, double *epart, const StageScalars *scalars) {
@@ -1007,27 +1021,27 @@ hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, int nsl
   const int nbe = epilogue_blocks((long long)o * v);
   dim3 grid(nbe + (es.mode ? 1 : 0), R);
   if (prec == RTTDA_PREC_MIXED_BF16)
-    hipLaunchKernelGGL((k_epilogue<1>), grid, dim3(256), 0, s, R, o, v, nslab, stage, mode, use_field, dt, D, P, F,
+    hipLaunchKernelGGL((k_epilogue<1>), grid, dim3(256), 0, s, R, o, v, slabs, stage, mode, use_field, dt, D, P, F,
                        sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
   else
-    hipLaunchKernelGGL((k_epilogue<0>), grid, dim3(256), 0, s, R, o, v, nslab, stage, mode, use_field, dt, D, P, F,
+    hipLaunchKernelGGL((k_epilogue<0>), grid, dim3(256), 0, s, R, o, v, slabs, stage, mode, use_field, dt, D, P, F,
                        sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
   return hipGetLastError();
 }
 
 int epilogue_blocks(long long ov) { return (int)std::min<long long>((ov + 63) / 64, EP_BX_MAX); }
 
-hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, int nslab, int mode, int use_field,
+hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, Slabs slabs, int mode, int use_field,
                              double dt, const double *D, const float *P, const double *F, const double *sc, double *c,
                              double *c0, double *W, double *W0, float *x32, __hip_bfloat16 *xhi,
                              __hip_bfloat16 *xlo) {
   const long long n = (long long)R * o * v;
   dim3 grid(grid_for(n, 64, 65536));
   if (prec == RTTDA_PREC_MIXED_BF16)
-    hipLaunchKernelGGL((k_sso_update<1>), grid, dim3(256), 0, s, R, o, v, nslab, mode, use_field, dt, D, P, F, sc, c,
+    hipLaunchKernelGGL((k_sso_update<1>), grid, dim3(256), 0, s, R, o, v, slabs, mode, use_field, dt, D, P, F, sc, c,
                        c0, W, W0, x32, xhi, xlo);
   else
-    hipLaunchKernelGGL((k_sso_update<0>), grid, dim3(256), 0, s, R, o, v, nslab, mode, use_field, dt, D, P, F, sc, c,
+    hipLaunchKernelGGL((k_sso_update<0>), grid, dim3(256), 0, s, R, o, v, slabs, mode, use_field, dt, D, P, F, sc, c,
                        c0, W, W0, x32, xhi, xlo);
   return hipGetLastError();
 }

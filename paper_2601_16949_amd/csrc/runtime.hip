@@ -55,6 +55,10 @@ rttda_status fail(rttda_status st, const char *fmt, ...) {
 constexpr int MAX_RHS = 4096;
 constexpr int SJ_MAX = 8;    // Coulomb second-product Q splits
 constexpr int SK_MAX = 768;  // exchange Q splits
+// X-resident exchange: ranges of Q per split, and the cycles that one after the first costs: all workgroups come
+// to its end together and read and write their slabs (25 to 50 MB: 5 to 12 us)
+constexpr int RES_RANGES_MAX = 32;
+constexpr double RES_RANGE_CYCLES = 20e3;
 // exchange flops per stage (at the largest RHS count) from which the Coulomb pair gets its own stream
 constexpr double OVERLAP_MIN_FLOPS = 5e10;
 constexpr int SMALL_BLOCKS = 512;  // workgroups of the small path's partial-sum launch: two per CU
@@ -259,6 +263,8 @@ struct rttda_ctx {
   // X-resident variant's workgroups fill the CUs in whole rounds, so fewer slices take more splits.
   // Equal to sk for the other variants and once a tile or split count has been chosen by the caller.
   int sk_real = 0, sk_one = 0;
+  // ranges of Q whose FP32 sum each of those splits is (see resident_ranges); 1 for the other variants
+  int sub = 1, sub_real = 1, sub_one = 1;
   int use_graph = 1, steps_per_graph = 8;
   int qchunk = 0;  // Q per chunk of the GEMM exchange path, 0 = gemm_chunk's choice
   // second stream for the Coulomb pair, which then runs alongside the exchange (HBM-bound next to
@@ -354,21 +360,79 @@ rttda_status validate_desc(const rttda_desc *d, bool need_ptrs) {
   return RTTDA_OK;
 }
 
-// Split count of an X-resident variant (one workgroup per CU at a time): the least time in whole
-// rounds of workgroups, plus the epilogue's read of the slabs (about 1900 bytes a cycle over the chip,
-// and 60 cycles a slab for the chain of its loads).  *cycles receives that time.
-int resident_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap, double *cycles) {
+// Cycles of an X-resident launch (one workgroup per CU at a time) of `slabs` splits of m ranges each: whole
+// rounds of workgroups, plus the stage update's read of the slabs (about 1900 bytes a cycle over the chip,
+// and 60 cycles a slab for the chain of its loads).
+double resident_cycles(const ResShape &r, int o, int ns, int v, int nq, int slabs, int m) {
+  const long long rounds = ((long long)r.tiles * slabs + 255) / 256;
+  const int per = slabs * m, q = ((nq + per - 1) / per + r.qs - 1) / r.qs;
+  return rounds * (m * q * r.q_cycles + (m - 1) * RES_RANGE_CYCLES + r.start_cycles) +
+         slabs * (60.0 + 2.0 * 4 * ns * o * v / 1900.0);
+}
+
+// the least count with fewer Q in its longest split than s (a count between the two is slower than s)
+int next_split(int nq, int s) {
+  const int q = (nq + s - 1) / s;
+  return q > 1 ? (nq + q - 2) / (q - 1) : nq + 1;
+}
+
+// Split count of an X-resident variant: the least of those times, which *cycles receives.  Where its waves share
+// the Q of a split (narrow v, whose slabs are small), a count that takes up to 6 % more and makes a launch of
+// `few` slices, one right-hand side's, fastest (o24 v168 N_Q600 FP32, 32 RHS: 32 splits for 8, 742 for 732 us
+// per launch, one of them alone 0.81 for 2.6 ms per step); elsewhere the splits' ranges serve that
+// (resident_ranges).
+int resident_splits(const ExchangeVariant *x, int o, int ns, int few, int v, int nq, int cap, double *cycles) {
   ResShape r;
   x->res(v, ns, &r);
   int best = 1;
   *cycles = 1e300;
-  for (int s = 1; s <= std::min(cap, nq); ++s) {
-    const double rounds = std::ceil((double)r.tiles * s / 256.0);
-    const double q = std::ceil(std::ceil((double)nq / s) / r.qs);
-    const double t = rounds * (q * r.q_cycles + r.start_cycles) + s * (60.0 + 2.0 * 4 * ns * o * v / 1900.0);
+  for (int s = 1; s <= std::min(cap, nq); s = next_split(nq, s)) {
+    const double t = resident_cycles(r, o, ns, v, nq, s, 1);
     if (t < *cycles) {
       *cycles = t;
       best = s;
+    }
+  }
+  if (few >= ns || r.qs == 1) return best;
+  ResShape r1;
+  x->res(v, few, &r1);
+  // (over several rounds a split's Q count on average but in the last; a round's start as it measures there)
+  auto full = [&](int s) {
+    const long long rounds = ((long long)r.tiles * s + 255) / 256;
+    const int q = ((nq + s - 1) / s + r.qs - 1) / r.qs;
+    return ((rounds - 1) * ((double)nq / s / r.qs) + q) * r.q_cycles + rounds * (r.start_cycles + 7e3) +
+           s * (60.0 + 2.0 * 4 * ns * o * v / 1900.0);
+  };
+  const double limit = 1.06 * full(best);
+  double least = 1e300;
+  for (int s = best; s <= std::min(cap, nq); s = next_split(nq, s)) {
+    if (full(s) > limit) continue;
+    const double t = resident_cycles(r1, o, few, v, nq, s, 1);
+    if (t < least) {
+      least = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// Ranges of Q per split of an X-resident variant whose sk splits fill the CUs with the context's ns slices: as
+// many as make a launch of `few` slices (one right-hand side's) fastest with a workgroup per range, while
+// their sums' way to the slab and back takes at most 3 % of the full launch.
+int resident_ranges(const ExchangeVariant *x, int o, int ns, int few, int v, int nq, int sk) {
+  ResShape r, r1;
+  x->res(v, ns, &r);
+  if (r.qs > 1) return 1;
+  x->res(v, few, &r1);
+  const double cycles = (nq + sk - 1) / sk * r.q_cycles;  // of a split
+  const int most = (int)std::min({1.0 + 0.03 * cycles / RES_RANGE_CYCLES, (double)nq / sk, (double)RES_RANGES_MAX});
+  int best = 1;
+  double best_t = 1e300;
+  for (int g = 1; g <= most; ++g) {
+    const double t = resident_cycles(r1, o, few, v, nq, sk * g, 1);
+    if (t < best_t * (1 - 1e-12)) {
+      best_t = t;
+      best = g;
     }
   }
   return best;
@@ -402,7 +466,7 @@ int auto_variant(int prec, int o, int ns, int v, int nq, const Layout &L) {
     const ExchangeVariant *x = variant_of(prec, k);
     if (!x->res || !x->applies(o, v)) continue;
     double t;
-    resident_splits(x, o, ns, v, nq, L.sk_max, &t);
+    resident_splits(x, o, ns, ns, v, nq, L.sk_max, &t);
     if (t < res_cycles) {
       res_cycles = t;
       res = k;
@@ -458,7 +522,7 @@ int gemm_chunk(const ExchangeVariant *x, int o, int ns, int v, int nq, int qmax)
   return best;
 }
 
-int auto_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap, const Layout &L) {
+int auto_splits(const ExchangeVariant *x, int o, int ns, int few, int v, int nq, int cap, const Layout &L) {
   if (x->scratch) {
     // GEMM path: splits of each chunk's Q range for the B_oo product, so that its workgroups fill whole
     // rounds of the 256 CUs: a workgroup takes about 1.3 us per Q and 32 j, and a split adds a slab that
@@ -481,7 +545,7 @@ int auto_splits(const ExchangeVariant *x, int o, int ns, int v, int nq, int cap,
   }
   if (x->res) {
     double t;
-    return resident_splits(x, o, ns, v, nq, cap, &t);
+    return resident_splits(x, o, ns, few, v, nq, cap, &t);
   }
   const int tiles = ((ns + x->ks - 1) / x->ks) * ((v + x->nt - 1) / x->nt);
   const int cus = 256;
@@ -539,6 +603,29 @@ enum Slices { SL_COMPLEX, SL_REAL, SL_ONE };
 int exchange_splits(const rttda_ctx *ctx, Slices k) {
   return k == SL_COMPLEX ? ctx->sk : k == SL_REAL ? ctx->sk_real : ctx->sk_one;
 }
+int exchange_subranges(const rttda_ctx *ctx, Slices k) {
+  return k == SL_COMPLEX ? ctx->sub : k == SL_REAL ? ctx->sub_real : ctx->sub_one;
+}
+
+// How a launch of ns slices divides the exchange: `slabs` splits of Q, each the sum of `m` ranges in its
+// workgroup, and `grp` of them to be added in FP32 by the stage update (m grp = the ranges of a split).
+// Many slices take a workgroup per split and slice group, which stages X once for all its ranges and writes
+// one slab; a call with few of the context's right-hand sides a workgroup per range, or most CUs would idle.
+// Both add the same sums in the same order, so a batch and one of its right-hand sides alone agree bit by bit.
+struct ExchangePlan {
+  int slabs, m, grp;
+};
+ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
+  const int sk = exchange_splits(ctx, k), sub = exchange_subranges(ctx, k);
+  const size_t room = (size_t)(ctx->L.sj_max + ctx->L.sk_max) * 2 * ctx->R;  // slabs of one slice
+  if (sub == 1 || ((size_t)ctx->sj + (size_t)sk * sub) * ns > room) return {sk, sub, 1};
+  const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  ResShape r;
+  x->res(ctx->v, ns, &r);
+  const double one = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk, sub);
+  const double all = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk * sub, 1);
+  return one <= all ? ExchangePlan{sk, sub, 1} : ExchangePlan{sk * sub, 1, sub};
+}
 
 // Default splits of the current variant, and whether the Coulomb pair runs alongside it: only where
 // the exchange is long enough to cover the cost of the fork and join (small problems and many
@@ -547,12 +634,22 @@ int exchange_splits(const rttda_ctx *ctx, Slices k) {
 // of Q (in order instead: o72 v256 N_Q960, one RHS 1480 -> 1366 us, o184 v1384 N_Q600, three RHS 56.1 ->
 // 53.5 ms, o240 v1800 N_Q1000, three RHS 167 -> 164 ms per two steps, 1.5 % faster over fifteen shapes,
 // the least of them, o160 v1200 with one RHS, 2 % slower).
+void set_subranges(rttda_ctx *ctx) {
+  const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  auto n = [&](int ns, int few, int sk) {
+    return x->res ? resident_ranges(x, ctx->o, ns, few, ctx->v, ctx->nq, sk) : 1;
+  };
+  ctx->sub = n(2 * ctx->R, 2, ctx->sk);
+  ctx->sub_real = n(ctx->R, 1, ctx->sk_real);
+  ctx->sub_one = n(1, 1, ctx->sk_one);
+}
 void default_launch(rttda_ctx *ctx) {
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
   const int cap = ctx->L.sk_max;
-  ctx->sk = auto_splits(x, ctx->o, 2 * ctx->R, ctx->v, ctx->nq, cap, ctx->L);
-  ctx->sk_real = x->res ? auto_splits(x, ctx->o, ctx->R, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
-  ctx->sk_one = x->res ? auto_splits(x, ctx->o, 1, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
+  ctx->sk = auto_splits(x, ctx->o, 2 * ctx->R, 2, ctx->v, ctx->nq, cap, ctx->L);
+  ctx->sk_real = x->res ? auto_splits(x, ctx->o, ctx->R, 1, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
+  ctx->sk_one = x->res ? auto_splits(x, ctx->o, 1, 1, ctx->v, ctx->nq, cap, ctx->L) : ctx->sk;
+  set_subranges(ctx);
 }
 void default_overlap(rttda_ctx *ctx) {
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
@@ -602,15 +699,29 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   const void *X = ctx->prec == RTTDA_PREC_FP32 ? (const void *)ctx->x32() : (const void *)ctx->xhi();
   const void *Xlo = ctx->prec == RTTDA_PREC_FP32 ? nullptr : (const void *)ctx->xlo();
   if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
-  HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, exchange_splits(ctx, kind),
-                    (float)(-ctx->d.cx), Pk, ctx->scratch(), scratch_for(ctx, ns)));
+  const ExchangePlan pl = exchange_plan(ctx, kind, ns);
+  if (x->res)
+    HIP_TRY(x->launch_ranges(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.slabs,
+                             exchange_subranges(ctx, kind), pl.m > 1, (float)(-ctx->d.cx), Pk));
+  else
+    HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.slabs,
+                      (float)(-ctx->d.cx), Pk, ctx->scratch(), scratch_for(ctx, ns)));
   if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
   if (fork) HIP_TRY(hipStreamWaitEvent(s, ctx->ev_join, 0));  // join before any reader of the slabs
   return RTTDA_OK;
 }
 
-int nslab(const rttda_ctx *ctx, Slices kind = SL_COMPLEX) {
-  return ctx->nq > 0 ? (ctx->small ? ctx->small_splits : ctx->sj + exchange_splits(ctx, kind)) : 0;
+// the slabs that launch leaves
+Slabs slabs_of(const rttda_ctx *ctx, Slices kind, int ns) {
+  if (ctx->nq == 0) return {0, 0, 1};
+  if (ctx->small) return {ctx->small_splits, ctx->small_splits, 1};
+  const ExchangePlan pl = exchange_plan(ctx, kind, ns);
+  return {ctx->sj + pl.slabs / pl.grp, ctx->sj, pl.grp};
+}
+// their number in memory, for a reader that adds them all in one row
+int nslab(const rttda_ctx *ctx, Slices kind, int ns) {
+  const Slabs sb = slabs_of(ctx, kind, ns);
+  return sb.nc + (sb.n - sb.nc) * sb.grp;
 }
 
 // the small path applies to the shape (o v and the RHS count within its single-workgroup limits)
@@ -638,7 +749,7 @@ rttda_status enqueue_step(rttda_ctx *ctx, int nrhs, double dt, bool has_field, b
                           c0,           ctx->acc0(), ctx->xs0(),   ctx->normref()};
     if (corr && stage == 0) HIP_TRY(launch_corr(s, nrhs, ctx->ov, c, c0, ctx->xref(), ctx->xref0(), ctx->state()));
     if (pops && stage == 0) HIP_TRY(launch_pop(s, nrhs, ctx->ov, c, ctx->state()));
-    HIP_TRY(launch_epilogue(s, ctx->prec, nrhs, o, v, nslab(ctx), stage, EP_RK4, has_field ? 1 : 0, dt, ctx->D(),
+    HIP_TRY(launch_epilogue(s, ctx->prec, nrhs, o, v, slabs_of(ctx, SL_COMPLEX, 2 * nrhs), stage, EP_RK4, has_field ? 1 : 0, dt, ctx->D(),
                             ctx->P(), ctx->F(), ctx->sc(), Xin, c, ctx->acc(), ctx->xs64(), ctx->x32(), ctx->xhi(),
                             ctx->xlo(), nullptr, energy && stage == 0 ? ctx->epart() : nullptr, &es));
     if (pr) HIP_TRY(ctx->prof.end(PC_EPILOGUE, s));
@@ -670,7 +781,7 @@ rttda_status enqueue_sso_step(rttda_ctx *ctx, int nrhs, double dt, bool has_fiel
       HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, half == 0 ? 1 : 3,
                             (has_field ? SM_EFIELD : 0) | (half == 1 ? SM_INC : 0), dt, ctx->pulses(), ctx->state(),
                             ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
-    HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, o, v, nslab(ctx, SL_REAL), half == 0 ? SSO_DRIFT : SSO_KICK,
+    HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, o, v, slabs_of(ctx, SL_REAL, nrhs), half == 0 ? SSO_DRIFT : SSO_KICK,
                               has_field ? 1 : 0, dt, ctx->D(), ctx->P(), ctx->F(), ctx->sc(), c, c0, W, W0, ctx->x32(),
                               ctx->xhi(), ctx->xlo()));
     if (pr) HIP_TRY(ctx->prof.end(PC_EPILOGUE, s));
@@ -687,7 +798,7 @@ rttda_status enqueue_sso_start(rttda_ctx *ctx, int nrhs, double dt, bool has_fie
   if (st != RTTDA_OK) return st;
   HIP_TRY(launch_scalar(s, nrhs, ctx->L.nbf, 0, has_field ? SM_EFIELD : 0, dt, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), c0, ctx->acc0(), ctx->xs0(), nullptr, ctx->normref(), nullptr));
-  HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx, SL_REAL), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
+  HIP_TRY(launch_sso_update(s, ctx->prec, nrhs, ctx->o, ctx->v, slabs_of(ctx, SL_REAL, nrhs), SSO_KICK_FIRST, has_field ? 1 : 0, dt,
                             ctx->D(), ctx->P(), ctx->F(), ctx->sc(), c, c0, ctx->xs64(), ctx->xs0(), ctx->x32(),
                             ctx->xhi(), ctx->xlo()));
   return RTTDA_OK;
@@ -865,7 +976,7 @@ rttda_status sigma_enqueue(rttda_ctx *ctx, int nrhs, const double *c0, const dou
   HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_SIGMA0 | SM_KEEP_E, 0.0, ctx->pulses(), ctx->state(),
                         ctx->part(), ctx->sc(), const_cast<double *>(c0), ctx->acc0(), ctx->xs0(), nullptr,
                         ctx->normref(), s0));
-  HIP_TRY(launch_epilogue(hs, ctx->prec, nrhs, ctx->o, ctx->v, nslab(ctx), 0, EP_SIGMA, 1, 0.0, ctx->D(), ctx->P(),
+  HIP_TRY(launch_epilogue(hs, ctx->prec, nrhs, ctx->o, ctx->v, slabs_of(ctx, SL_COMPLEX, 2 * nrhs), 0, EP_SIGMA, 1, 0.0, ctx->D(), ctx->P(),
                           ctx->F(), ctx->sc(), c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, s));
   return RTTDA_OK;
 }
@@ -1028,7 +1139,14 @@ rttda_status rttda_set_tuning(rttda_ctx *ctx, const rttda_tuning *t) {
   if (t->exchange_chunk < -1) return fail(RTTDA_E_INVAL, "exchange_chunk must be -1, 0 or positive");
   if (ctx->nq > 0) {
     ctx->xvar = xv;
-    if (t->exchange_variant || t->exchange_splits) ctx->sk = ctx->sk_real = ctx->sk_one = sk;
+    if (t->exchange_variant || t->exchange_splits) {
+      // (the library's own count leaves the other kinds of launch theirs)
+      default_launch(ctx);
+      if (sk != ctx->sk) {
+        ctx->sk = ctx->sk_real = ctx->sk_one = sk;
+        set_subranges(ctx);
+      }
+    }
     ctx->sj = sj;
     if (!ctx->overlap_set) default_overlap(ctx);
   }
@@ -1340,7 +1458,7 @@ rttda_status propagate_impl(rttda_ctx *ctx, int32_t nrhs, const rttda_pulse *pul
   if (energy) {  // the final energy sample needs one more product A c
     if ((st = to_stage_copy(ctx, c, nrhs)) != RTTDA_OK) return st;
     if ((st = enqueue_two_electron(ctx, 2 * nrhs)) != RTTDA_OK) return st;
-    HIP_TRY(launch_epilogue(hs, ctx->prec, nrhs, o, v, nslab(ctx), 0, EP_ENERGY, 0, dt, ctx->D(), ctx->P(), ctx->F(),
+    HIP_TRY(launch_epilogue(hs, ctx->prec, nrhs, o, v, slabs_of(ctx, SL_COMPLEX, 2 * nrhs), 0, EP_ENERGY, 0, dt, ctx->D(), ctx->P(), ctx->F(),
                             ctx->sc(), c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                             ctx->epart()));
     HIP_TRY(launch_scalar(hs, nrhs, ctx->L.nbf, 0, SM_ENERGY, dt, ctx->pulses(), ctx->state(), ctx->part(), ctx->sc(),
@@ -1416,7 +1534,7 @@ rttda_status rttda_spectral_radius(rttda_ctx *ctx, int32_t n_iter, double *rho, 
   const int kmax = (int)std::min<long long>(n_iter, n);
   for (int j = 0; j < kmax; ++j) {
     if (ctx->nq > 0 && (st = enqueue_two_electron(ctx, 1, SL_ONE)) != RTTDA_OK) return st;
-    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx, SL_ONE), ctx->D(), ctx->P(), v, vprev, j ? db + j - 1 : nullptr, w, pa));
+    HIP_TRY(launch_lz_apply(hs, n, nslab(ctx, SL_ONE, 1), ctx->D(), ctx->P(), v, vprev, j ? db + j - 1 : nullptr, w, pa));
     HIP_TRY(launch_lz_orth(hs, n, v, pa, da + j, w, pb));
     HIP_TRY(launch_lz_next(hs, ctx->prec, n, pb, db + j, w, v, vprev, ctx->x32(), ctx->xhi(), ctx->xlo(), 1));
   }
@@ -1497,7 +1615,7 @@ rttda_status rttda_eigen_lowest(rttda_ctx *ctx, int32_t k, int32_t m_max, int32_
       rttda_status s2 = to_stage_copy_n(ctx, V + (size_t)b0 * n, (long long)nb * n);
       if (s2 != RTTDA_OK) return s2;
       if (ctx->nq > 0 && (s2 = enqueue_two_electron(ctx, nb)) != RTTDA_OK) return s2;
-      HIP_TRY(launch_dv_apply(hs, n, nb, nslab(ctx), ctx->D(), ctx->P(), V + (size_t)b0 * n, W + (size_t)b0 * n));
+      HIP_TRY(launch_dv_apply(hs, n, nb, nslab(ctx, SL_COMPLEX, nb), ctx->D(), ctx->P(), V + (size_t)b0 * n, W + (size_t)b0 * n));
     }
     return RTTDA_OK;
   };

@@ -1,0 +1,100 @@
+"""A split of the X-resident exchange as the FP32 sum of several ranges of Q: added in a workgroup's slab where a
+launch has slices for every CU, by the stage update where a call has few of its context's right-hand sides and
+takes a workgroup per range.  The two leave the same bits, follow the oracle, and a small call is short."""
+import time
+
+import numpy as np
+import pytest
+from conftest import say
+
+from oracle import rttda64 as O
+from paper_2601_16949_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# as for the other X-resident launches: about 30 roundings of 2^-24 (FP32) or twice 2^-16 (split BF16) per product
+TOL = {"fp32": 2e-6, "mixed": 2e-5}
+
+# (o, v, nq, max_rhs): every tile, columns with and without a second phase, full launches of one and more rounds
+SHAPES = {"fp32": [(60, 257, 60, 40), (48, 277, 45, 40), (33, 203, 90, 64), (40, 250, 67, 33), (24, 290, 80, 64),
+                   (30, 330, 50, 64), (16, 340, 90, 64), (57, 400, 31, 22)],
+          "mixed": [(60, 257, 130, 40), (64, 400, 85, 33), (48, 277, 150, 40), (33, 330, 133, 40), (24, 340, 200, 64),
+                    (16, 370, 300, 64)]}
+
+
+@pytest.mark.parametrize("prec,o,v,nq,R", [(p, *s) for p in SHAPES for s in SHAPES[p]])
+def test_batch_and_single_calls_agree_bit_by_bit(gpu_lib, prec, o, v, nq, R):
+    import torch
+
+    prob = I.make_problem(I.Shape(o, v, nq, 0.05, cx=1.0, storage="f32" if prec == "fp32" else "bf16"), 3 * o + v)
+    op = O.Operator.from_problem(prob)
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, prec), max_rhs=R)
+    tun = ctx.get_tuning()
+    say(f"[ranges] {prec} o={o} v={v} nq={nq} max_rhs={R}: {ctx.variant_name(tun['exchange_variant'])} "
+        f"{tun['exchange_splits']} splits")
+    c0, c = I.random_state(o, v, R, seed=o + v)
+    dirs, field = np.tile([[0.0, 0.0, 1.0]], (R, 1)), np.zeros(R)
+    c0d, cd = gpu_lib.to_planes(c0, c)
+    _, full = ctx.sigma(field, dirs, c0d, cd)
+    torch.cuda.synchronize()
+    got = gpu_lib.from_planes(torch.zeros_like(c0d), full)[1]
+    for r in (0, R - 1):
+        ref = O.apply_H(op, O.dipole_blocks(op, dirs[r]), 0.0, c0[r], c[r])[1]
+        assert np.linalg.norm(got[r] - ref) <= TOL[prec] * np.linalg.norm(ref), r
+    for n in (1, 2, 5):
+        _, few = ctx.sigma(field[-n:], dirs[-n:], c0d[-n:].contiguous(), cd[-n:].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(few, full[-n:]), n
+    # steps under a field, from graphs and directly, and the split operator (one plane per state)
+    pulses = [I.Pulse(kind=I.PULSE_CW, e0=0.02, omega=0.5, phase=0.1 * r, direction=I.AXES[r % 3]) for r in range(R)]
+    for integ in ("rk4", "sso"):
+        g0, g = gpu_lib.ground_state(R, o, v)
+        tr = ctx.propagate(pulses, 0.01, 2, g0, g, integrator=integ)
+        h0, h = gpu_lib.ground_state(1, o, v)
+        one = ctx.propagate(pulses[-1:], 0.01, 2, h0, h, integrator=integ)
+        torch.cuda.synchronize()
+        assert torch.equal(h[0], g[-1]) and torch.equal(one[:, 0], tr[:, -1]), integ
+
+
+def _seconds(fn, n=5):
+    import torch
+
+    fn()
+    torch.cuda.synchronize()
+    t = []
+    for _ in range(n):
+        a = time.perf_counter()
+        fn()
+        torch.cuda.synchronize()
+        t.append(time.perf_counter() - a)
+    return min(t)
+
+
+@pytest.mark.parametrize("prec,o,v,nq,R,part", [("fp32", 40, 300, 200, 64, 0.25), ("mixed", 40, 300, 400, 64, 0.35),
+                                                ("fp32", 60, 400, 300, 3, 0.65), ("fp32", 24, 168, 600, 32, 0.5)])
+def test_one_state_of_a_large_context_takes_less_than_the_batch(gpu_lib, prec, o, v, nq, R, part):
+    prob = I.make_problem(I.Shape(o, v, nq, 0.03, storage="f32" if prec == "fp32" else "bf16"), 9)
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, prec), max_rhs=R)
+    pulses = I.gauss_cos_scan(0.39, 0.05, n=R)
+    c0, c = gpu_lib.ground_state(R, o, v)
+    full = _seconds(lambda: ctx.propagate(pulses, 0.01, 2, c0, c))
+    one = _seconds(lambda: ctx.propagate(pulses[:1], 0.01, 2, c0[:1], c[:1]))
+    say(f"[ranges] {prec} o={o} v={v} nq={nq}: {R} RHS {full * 1e3:.2f} ms, one {one * 1e3:.2f} ms")
+    assert one < part * full
+
+
+def test_other_calls_keep_their_speed_once_splits_are_chosen(gpu_lib):
+    """Naming the library's own split count leaves the time-step check and the split operator their own; naming
+    another cuts their splits into ranges."""
+    o, v, nq, R = 40, 300, 400, 64
+    prob = I.make_problem(I.Shape(o, v, nq, 0.03), 9)
+    dev = gpu_lib.DeviceProblem(prob, "fp32")
+    ctx = gpu_lib.Context(dev, max_rhs=R)
+    base = _seconds(lambda: ctx.spectral_radius(20))
+    tun = ctx.get_tuning()
+    for splits, slack in ((tun["exchange_splits"], 1.3), (2 * tun["exchange_splits"], 4.0)):
+        ctx.set_tuning(exchange_variant=tun["exchange_variant"], exchange_splits=splits)
+        assert ctx.get_tuning()["exchange_splits"] == splits
+        t = _seconds(lambda: ctx.spectral_radius(20))
+        say(f"[ranges] time-step check {base * 1e3:.2f} ms, with {splits} splits chosen {t * 1e3:.2f} ms")
+        assert t < slack * base
