@@ -118,7 +118,7 @@ inline bool small_shape_ok(int o, int v) {
 }
 hipError_t prepare_small();  // one-time kernel attributes (dynamic LDS); call outside graph capture
 hipError_t launch_small_2e(hipStream_t s, int b_dtype, const void *Bov, const void *Boo, const void *Bvv,
-                           const float *X, int o, int v, int nq, int ns, int nsplit, float cx, float *P,
+                           const float *X, int o, int v, int nq, int ns, int nsplit, int m, float cx, float *P,
                            const FieldArgs &f);
 // Epilogue grid: blocks per RHS along ia (the energy partial sums come one per block)
 constexpr int EP_BX_MAX = 2048;

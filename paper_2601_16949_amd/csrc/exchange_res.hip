@@ -140,8 +140,9 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
 // them, with the same bits.  So a context whose full batch fills the CUs with long splits (few slabs, X staged
 // once) keeps short ones for a call with few of its right-hand sides, which would else run on a few CUs, and the
 // FP32 chains stay short in both: o40 v300 N_Q1000 FP32, max_rhs 64, 4 splits of 32 ranges: one RHS 1.6 ms per
-// step (34.9 without ranges), all 64 36.0 (35.6); o60 v400 N_Q1500, max_rhs 3, one RHS: 5.7 ms (13.9) in FP32, 42
-// splits of 3, and 2.0 (3.6) in split BF16, 42 of 2; all three 14.05 (13.98) and 3.83 (3.78).  (The second
+// step (34.9 without ranges), all 64 36.0 (35.6); o60 v400 N_Q1500, max_rhs 3, per two steps, one RHS: 5.7 ms
+// (13.9) in FP32, 42 splits of 3, and 2.3 (3.7) in split BF16, 42 of 2; all three 14.05 (13.98) and 3.83 (3.78).
+// (The second
 // phase's blocks, whose waves share the split's Q in eighths, are left out of that: the workgroup of a split's
 // first range takes them, the others' slabs hold zeros there.)
 template <bool BF, int JB, int KS, int NCBM, bool PK, bool RNG>

@@ -435,46 +435,55 @@ __global__ __launch_bounds__(256) void k_scalar(int R, int nbf, int stage, int m
   if ((mode & SM_INC) && blockIdx.x == 0 && threadIdx.x == 0) st->pend = 1;
 }
 
-// Sum of nslab partial slabs at element e of a block of 256 threads that holds 64 elements: each wave
-// adds a quarter of the slabs (eight loads per plane in flight, in slab order), and the quarters meet in
+// Sum of the partial slabs `sb` at element e of a block of 256 threads that holds 64 elements: each wave
+// adds a quarter of the sums (eight loads per plane in flight, in memory order), and the quarters meet in
 // LDS in wave order.  Every thread of lane l receives the sum of element l.  NP planes, `plane` floats
 // apart.  (Slabs past a quarter read its last one again and are left out of the sum: a condition on the
-// load would make each wait for the one before it.)
-template <int NP>
+// load would make each wait for the one before it.)  GRP: some sums are of several slabs.
+template <int NP, bool GRP>
 __device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t slab, size_t plane, Slabs sb, size_t e,
                                          bool live, double (&out)[NP]) {
   __shared__ double quarter[4][NP][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int a = wave * sb.n / 4, b = (wave + 1) * sb.n / 4;
-  auto first = [&](int k) { return k < sb.nc ? k : sb.nc + (k - sb.nc) * sb.grp; };  // a slab's place in memory
+  auto first = [&](int k) { return !GRP || k < sb.nc ? k : sb.nc + (k - sb.nc) * sb.grp; };  // its place in memory
+  const int a = first(wave * sb.n / 4), b = first((wave + 1) * sb.n / 4);
   double t[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) t[p] = 0.0;
   if (live) {
     constexpr int U = 8;
-    for (int sl = a; sl < b; sl += U) {
-      float x[NP][U];
+    auto load = [&](int sl, float (&x)[NP][U]) {
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int p = 0; p < NP; ++p) x[p][u] = P[(size_t)first(min(sl + u, b - 1)) * slab + p * plane + e];
-      for (int g = 1; g < sb.grp; ++g) {  // (a slab that stands alone reads itself again)
-        float y[NP][U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int k = min(sl + u, b - 1);
-#pragma unroll
-          for (int p = 0; p < NP; ++p) y[p][u] = P[(size_t)(first(k) + (k < sb.nc ? 0 : g)) * slab + p * plane + e];
-        }
+        for (int p = 0; p < NP; ++p) x[p][u] = P[(size_t)min(sl + u, b - 1) * slab + p * plane + e];
+    };
+    if constexpr (!GRP) {
+      for (int sl = a; sl < b; sl += U) {
+        float x[NP][U];
+        load(sl, x);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int p = 0; p < NP; ++p) x[p][u] = min(sl + u, b - 1) < sb.nc ? x[p][u] : x[p][u] + y[p][u];
+          for (int p = 0; p < NP; ++p) t[p] += sl + u < b ? (double)x[p][u] : 0.0;
       }
+    } else {  // f: the sum of the g slabs of a group so far (without a branch between the slabs)
+      int g = 0;
+      float f[NP] = {};
+      for (int sl = a; sl < b; sl += U) {
+        float x[NP][U];
+        load(sl, x);
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+          const bool last = g + 1 == sb.grp || sl + u < sb.nc, ok = sl + u < b;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) t[p] += sl + u < b ? (double)x[p][u] : 0.0;
+          for (int p = 0; p < NP; ++p) {
+            f[p] = g == 0 ? x[p][u] : f[p] + x[p][u];
+            t[p] += last && ok ? (double)f[p] : 0.0;
+          }
+          g = last ? 0 : g + 1;
+        }
+      }
     }
   }
 #pragma unroll
@@ -497,7 +506,7 @@ __device__ __forceinline__ void slab_sum(const float *__restrict__ P, size_t sla
 // A block of 256 threads holds 64 (r, i, a): its waves share the slabs, the first updates; the ground
 // element of RHS r by the thread with ia == 0.
 // ------------------------------------------------------------------------------------------------
-template <int PREC>
+template <int PREC, bool GRP>
 __global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, Slabs slabs, int mode, int use_field, double dt,
                                                     const double *__restrict__ D, const float *__restrict__ P,
                                                     const double *__restrict__ F, const double *__restrict__ sc,
@@ -512,7 +521,7 @@ __global__ __launch_bounds__(256) void k_sso_update(int R, int o, int v, Slabs s
   for (size_t e0 = blockIdx.x * (size_t)64; e0 < total; e0 += (size_t)gridDim.x * 64) {
     const size_t e = e0 + (threadIdx.x & 63);
     double psum[1];
-    slab_sum<1>(P, slab, 0, slabs, e, e < total, psum);
+    slab_sum<1, GRP>(P, slab, 0, slabs, e, e < total, psum);
     if (threadIdx.x >= 64 || e >= total) continue;
     const size_t r = e / ov, ia = e - r * ov;
     const size_t iq = r * 2 * ov + ia, ip = iq + ov;
@@ -629,7 +638,7 @@ __global__ __launch_bounds__(256) void k_lz_apply(long long n, int nslab, const 
   for (long long e0 = blockIdx.x * 64LL; e0 < n; e0 += (long long)gridDim.x * 64) {
     const long long e = e0 + (threadIdx.x & 63);
     double p[1];
-    slab_sum<1>(P, (size_t)n, 0, Slabs{nslab, 0, 1}, (size_t)e, e < n, p);
+    slab_sum<1, false>(P, (size_t)n, 0, Slabs{nslab, 0, 1}, (size_t)e, e < n, p);
     if (threadIdx.x >= 64 || e >= n) continue;
     const double s = D[e] * v[e] + p[0] - beta * vprev[e];
     w[e] = s;
@@ -687,7 +696,7 @@ __global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__re
 // o24 v184 N_Q480, one RHS: 6.4 us; one thread per (i, a) summing every slab took 10.9 us, and the
 // scalars' own launch 4.1 us.
 // ------------------------------------------------------------------------------------------------
-template <int PREC>
+template <int PREC, bool GRP>
 __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, Slabs slabs, int stage, int mode, int use_field,
                                                   double dt, const double *__restrict__ D,
                                                   const float *__restrict__ P, const double *__restrict__ F,
@@ -726,7 +735,7 @@ __global__ __launch_bounds__(256) void k_epilogue(int R, int o, int v, Slabs sla
       ya = stage == 0 ? 0.0 : acc[ip];
     }
     double ps[2];
-    slab_sum<2>(P, slab, ov, slabs, im, ia < ov, ps);
+    slab_sum<2, GRP>(P, slab, ov, slabs, im, ia < ov, ps);
     if (wave >= 2 || ia >= ov) continue;
     double sg = d * x + ps[q];
     if (epart) en += x * sg;
@@ -1012,6 +1021,17 @@ hipError_t launch_scalar(hipStream_t s, int R, int nbf, int stage, int mode, dou
   return hipGetLastError();
 }
 
+// go(PREC, GRP) for a launch's precision and slabs
+template <typename F>
+static void by_prec_and_groups(int prec, const Slabs &slabs, F go) {
+  auto pick = [&](auto pr) {
+    if (slabs.grp > 1) go(pr, std::true_type{});
+    else go(pr, std::false_type{});
+  };
+  if (prec == RTTDA_PREC_MIXED_BF16) pick(std::integral_constant<int, 1>{});
+  else pick(std::integral_constant<int, 0>{});
+}
+
 hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, Slabs slabs, int stage, int mode,
                            int use_field, double dt, const double *D, const float *P, const double *F, double *sc,
                            const double *Xin, double *c, double *acc, double *xs64, float *x32, __hip_bfloat16 *xhi,
@@ -1020,12 +1040,11 @@ hipError_t launch_epilogue(hipStream_t s, int prec, int R, int o, int v, Slabs s
   if (scalars) es = *scalars;
   const int nbe = epilogue_blocks((long long)o * v);
   dim3 grid(nbe + (es.mode ? 1 : 0), R);
-  if (prec == RTTDA_PREC_MIXED_BF16)
-    hipLaunchKernelGGL((k_epilogue<1>), grid, dim3(256), 0, s, R, o, v, slabs, stage, mode, use_field, dt, D, P, F,
-                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
-  else
-    hipLaunchKernelGGL((k_epilogue<0>), grid, dim3(256), 0, s, R, o, v, slabs, stage, mode, use_field, dt, D, P, F,
-                       sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
+  auto go = [&](auto pr, auto grp) {
+    hipLaunchKernelGGL((k_epilogue<decltype(pr)::value, decltype(grp)::value>), grid, dim3(256), 0, s, R, o, v, slabs,
+                       stage, mode, use_field, dt, D, P, F, sc, Xin, c, acc, xs64, x32, xhi, xlo, s_out, epart, nbe, es);
+  };
+  by_prec_and_groups(prec, slabs, go);
   return hipGetLastError();
 }
 
@@ -1037,12 +1056,11 @@ hipError_t launch_sso_update(hipStream_t s, int prec, int R, int o, int v, Slabs
                              __hip_bfloat16 *xlo) {
   const long long n = (long long)R * o * v;
   dim3 grid(grid_for(n, 64, 65536));
-  if (prec == RTTDA_PREC_MIXED_BF16)
-    hipLaunchKernelGGL((k_sso_update<1>), grid, dim3(256), 0, s, R, o, v, slabs, mode, use_field, dt, D, P, F, sc, c,
-                       c0, W, W0, x32, xhi, xlo);
-  else
-    hipLaunchKernelGGL((k_sso_update<0>), grid, dim3(256), 0, s, R, o, v, slabs, mode, use_field, dt, D, P, F, sc, c,
-                       c0, W, W0, x32, xhi, xlo);
+  auto go = [&](auto pr, auto grp) {
+    hipLaunchKernelGGL((k_sso_update<decltype(pr)::value, decltype(grp)::value>), grid, dim3(256), 0, s, R, o, v, slabs,
+                       mode, use_field, dt, D, P, F, sc, c, c0, W, W0, x32, xhi, xlo);
+  };
+  by_prec_and_groups(prec, slabs, go);
   return hipGetLastError();
 }
 

@@ -275,7 +275,8 @@ struct rttda_ctx {
   bool overlap_set = false;  // chosen by the caller (else it follows the exchange variant)
   // small problems: the stage's Coulomb + exchange slabs (small_splits of them) and field product in one
   // launch
-  int small = 0, small_splits = 0;
+  // (each the FP32 sum of small_sub ranges of Q)
+  int small = 0, small_splits = 0, small_sub = 1;
   // Coulomb pair on the matrix cores (batches of many slices) instead of the vector-unit GEMVs
   int coul_mfma = 0;
   double *corr_next = nullptr;  // time-correlation output of the next propagate call
@@ -616,8 +617,12 @@ struct ExchangePlan {
   int slabs, m, grp;
 };
 ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
-  const int sk = exchange_splits(ctx, k), sub = exchange_subranges(ctx, k);
   const size_t room = (size_t)(ctx->L.sj_max + ctx->L.sk_max) * 2 * ctx->R;  // slabs of one slice
+  if (ctx->small) {  // (both parts of sigma: a workgroup per range where one per split would not reach every CU)
+    const int sk = ctx->small_splits, sub = ctx->small_sub;
+    return ns * sk <= 256 && (size_t)sk * sub * ns <= room ? ExchangePlan{sk * sub, 1, sub} : ExchangePlan{sk, sub, 1};
+  }
+  const int sk = exchange_splits(ctx, k), sub = exchange_subranges(ctx, k);
   if (sub == 1 || ((size_t)ctx->sj + (size_t)sk * sub) * ns > room) return {sk, sub, 1};
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
   ResShape r;
@@ -669,10 +674,11 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
     if (pr) HIP_TRY(ctx->prof.end(PC_FIELD, s));
   }
   if (ctx->nq == 0) return RTTDA_OK;
+  const ExchangePlan pl = exchange_plan(ctx, kind, ns);
   if (ctx->small) {
     if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
     HIP_TRY(launch_small_2e(s, ctx->d.b_dtype, ctx->d.b_ov, ctx->d.b_oo, ctx->d.b_vv, ctx->x32(), ctx->o, ctx->v,
-                            ctx->nq, ns, ctx->small_splits, (float)ctx->d.cx, ctx->P(), f));
+                            ctx->nq, ns, pl.slabs, pl.m, (float)ctx->d.cx, ctx->P(), f));
     if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
     return RTTDA_OK;
   }
@@ -699,7 +705,6 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   const void *X = ctx->prec == RTTDA_PREC_FP32 ? (const void *)ctx->x32() : (const void *)ctx->xhi();
   const void *Xlo = ctx->prec == RTTDA_PREC_FP32 ? nullptr : (const void *)ctx->xlo();
   if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
-  const ExchangePlan pl = exchange_plan(ctx, kind, ns);
   if (x->res)
     HIP_TRY(x->launch_ranges(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.slabs,
                              exchange_subranges(ctx, kind), pl.m > 1, (float)(-ctx->d.cx), Pk));
@@ -714,9 +719,9 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
 // the slabs that launch leaves
 Slabs slabs_of(const rttda_ctx *ctx, Slices kind, int ns) {
   if (ctx->nq == 0) return {0, 0, 1};
-  if (ctx->small) return {ctx->small_splits, ctx->small_splits, 1};
   const ExchangePlan pl = exchange_plan(ctx, kind, ns);
-  return {ctx->sj + pl.slabs / pl.grp, ctx->sj, pl.grp};
+  const int nc = ctx->small ? 0 : ctx->sj;  // the Coulomb pair's
+  return {nc + pl.slabs / pl.grp, nc, pl.grp};
 }
 // their number in memory, for a reader that adds them all in one row
 int nslab(const rttda_ctx *ctx, Slices kind, int ns) {
@@ -1042,8 +1047,10 @@ rttda_status rttda_create(const rttda_desc *desc, rttda_ctx **out) {
     default_overlap(ctx);
     // the small path's Q ranges (the update adds one slab per range): one Q each where that takes no more than
     // SMALL_BLOCKS workgroups (o10 v40 N_Q120, one RHS, 16 steps: 120 ranges 0.90 ms, 64 1.02 ms; with
-    // eight RHS 64 ranges, 1024 workgroups, 1.70 ms and 120 2.02 ms)
+    // eight RHS 64 ranges, 1024 workgroups, 1.70 ms and 120 2.02 ms).  Where a full batch leaves them several
+    // Q each, they are cut into ranges for the calls with few slices
     ctx->small_splits = std::max(1, std::min({SMALL_BLOCKS / (2 * ctx->R), ctx->nq, L.sj_max + L.sk_max}));
+    ctx->small_sub = std::max(1, std::min(SMALL_BLOCKS / 2, ctx->nq) / ctx->small_splits);
     ctx->coul_mfma = 2 * ctx->R >= COUL_MFMA_MIN_SLICES ? 1 : 0;
     // the default only for the smallest problems (see SMALL_DEFAULT_FLOPS)
     ctx->small = small_fits(ctx->o, ctx->v, ctx->R) &&

@@ -5,8 +5,11 @@
 //    workgroup.  Every Q term of J = 2 sum_Q B^Q <B^Q, X> needs only its own d_Q, so no grid-wide
 //    step separates the two Coulomb products here; the exchange term B_oo^Q X B_vv^Q goes through
 //    the workgroup's LDS (FP32 FMA: at these sizes the matrix cores would idle on latency anyway).
-//    Each workgroup writes one partial slab J - c_x K for its Q range.  Further workgroups of the launch
-//    form the field product.
+//    Each workgroup writes one partial slab J - c_x K, the FP32 sum of those of its m ranges of Q; a call with
+//    few of the context's right-hand sides takes a workgroup per range, and the stage update adds the ranges
+//    so, with the same bits.  Further workgroups of the launch form the field product.
+#include <type_traits>
+
 #include "common.h"
 #include "field.h"
 
@@ -44,10 +47,10 @@ __device__ __forceinline__ float dot4(const float *x, int sx, const float *y, in
 // dynamic LDS: X slice, W, B_vv^Q and B_oo^Q (floats).  All of a Q's factors are loaded together (from
 // clamped places), and the next Q's while this one is multiplied: a loop of loads and LDS writes waits for
 // each load in turn.
-template <typename TB>
+template <typename TB, bool RNG>
 __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, const TB *__restrict__ Boo,
                                                   const TB *__restrict__ Bvv, const float *__restrict__ X, int o,
-                                                  int v, int nq, int ns, int nsplit, float cx,
+                                                  int v, int nq, int ns, int nsplit, int m, float cx,
                                                   float *__restrict__ P, FieldArgs f) {
   if ((int)blockIdx.x < f.blocks) {
     field_block(f, blockIdx.x);
@@ -62,6 +65,16 @@ __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, co
   float *Xs = sm2, *W = sm2 + ov, *Vs = W + ov, *Os = Vs + vv;
   const float *Xg = X + (size_t)s * ov;
   const int qa = (int)((long long)sp * nq / nsplit), qb = (int)((long long)(sp + 1) * nq / nsplit);
+  // RNG: range k of the m in each split begins at Q = floor(k nq / nrg), k = sp m, ...; qf is where the next one
+  // begins, and part the numerator's rest there
+  const int nrg = RNG ? nsplit * m : 1, step = nq / nrg, rest = nq % nrg;
+  int qf = qa, part = RNG ? (int)((long long)sp * m * nq % nrg) : 0;
+  auto next = [&]() {
+    part += rest;
+    qf += step + (part >= nrg ? 1 : 0);
+    part -= part >= nrg ? nrg : 0;
+  };
+  if (RNG) next();
   float tv[UV], to[UO], bq[EPT2];
   auto load_q = [&](int q) {
     const TB *Bq = Bov + (size_t)q * ov, *Vq = Bvv + (size_t)q * vv, *Oq = Boo + (size_t)q * oo;
@@ -81,9 +94,10 @@ __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, co
     for (int u = 0; u < EPT2; ++u)
       if (tid + 256 * u < ov) Xs[tid + 256 * u] = xs[u];
   }
-  float J[EPT2], K[EPT2];
+  float J[EPT2], K[EPT2], T[EPT2];  // a range's sums, and the ranges before it
 #pragma unroll
-  for (int k = 0; k < EPT2; ++k) J[k] = K[k] = 0.f;
+  for (int k = 0; k < EPT2; ++k) J[k] = K[k] = T[k] = 0.f;
+  bool first = true;
   for (int q = qa; q < qb; ++q) {
     float bk[EPT2];
 #pragma unroll
@@ -125,12 +139,23 @@ __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, co
       }
     }
     __syncthreads();  // W, red and the staged factors are rewritten by the next Q
+    if (RNG && q + 1 == qf && q + 1 < qb) {
+#pragma unroll
+      for (int k = 0; k < EPT2; ++k) {
+        const float x = J[k] - cx * K[k];
+        T[k] = first ? x : T[k] + x;
+        J[k] = K[k] = 0.f;
+      }
+      first = false;
+      next();
+    }
   }
   float *Pp = P + ((size_t)sp * ns + s) * ov;
 #pragma unroll
   for (int k = 0; k < EPT2; ++k) {
     const int e = tid + 256 * k;
-    if (e < ov) Pp[e] = J[k] - cx * K[k];
+    const float x = J[k] - cx * K[k];
+    if (e < ov) Pp[e] = RNG && !first ? T[k] + x : x;
   }
 }
 
@@ -138,8 +163,10 @@ __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, co
 
 hipError_t prepare_small() {
   const int bytes = SMALL_LDS_DOUBLES * (int)sizeof(double);
-  const void *fn[] = {reinterpret_cast<const void *>(&k_small_2e<float>),
-                      reinterpret_cast<const void *>(&k_small_2e<__hip_bfloat16>)};
+  const void *fn[] = {reinterpret_cast<const void *>(&k_small_2e<float, false>),
+                      reinterpret_cast<const void *>(&k_small_2e<float, true>),
+                      reinterpret_cast<const void *>(&k_small_2e<__hip_bfloat16, false>),
+                      reinterpret_cast<const void *>(&k_small_2e<__hip_bfloat16, true>)};
   for (const void *f : fn) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
@@ -148,20 +175,24 @@ hipError_t prepare_small() {
 }
 
 hipError_t launch_small_2e(hipStream_t s, int b_dtype, const void *Bov, const void *Boo, const void *Bvv,
-                           const float *X, int o, int v, int nq, int ns, int nsplit, float cx, float *P,
+                           const float *X, int o, int v, int nq, int ns, int nsplit, int m, float cx, float *P,
                            const FieldArgs &f) {
   const int ov = o * v;
-  if (ov > SMALL_OV_MAX || nsplit < 1) return hipErrorInvalidValue;
+  if (ov > SMALL_OV_MAX || nsplit < 1 || m < 1 || (long long)nsplit * m > nq) return hipErrorInvalidValue;
   const dim3 grid(f.blocks + nsplit * ns);
   const size_t lds = ((size_t)2 * ov + (size_t)v * v + (size_t)o * o) * sizeof(float);
-  if (b_dtype == RTTDA_BF16)
-    hipLaunchKernelGGL(k_small_2e<__hip_bfloat16>, grid, dim3(256), lds, s,
-                       static_cast<const __hip_bfloat16 *>(Bov), static_cast<const __hip_bfloat16 *>(Boo),
-                       static_cast<const __hip_bfloat16 *>(Bvv), X, o, v, nq, ns, nsplit, cx, P, f);
-  else
-    hipLaunchKernelGGL(k_small_2e<float>, grid, dim3(256), lds, s, static_cast<const float *>(Bov),
-                       static_cast<const float *>(Boo), static_cast<const float *>(Bvv), X, o, v, nq, ns, nsplit, cx,
-                       P, f);
+  auto go = [&](auto b, auto rng) {
+    using TB = decltype(b);
+    hipLaunchKernelGGL((k_small_2e<TB, decltype(rng)::value>), grid, dim3(256), lds, s, static_cast<const TB *>(Bov),
+                       static_cast<const TB *>(Boo), static_cast<const TB *>(Bvv), X, o, v, nq, ns, nsplit, m, cx, P,
+                       f);
+  };
+  auto pick = [&](auto b) {
+    if (m > 1) go(b, std::true_type{});
+    else go(b, std::false_type{});
+  };
+  if (b_dtype == RTTDA_BF16) pick(__hip_bfloat16{});
+  else pick(0.f);
   return hipGetLastError();
 }
 

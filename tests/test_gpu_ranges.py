@@ -98,3 +98,55 @@ def test_other_calls_keep_their_speed_once_splits_are_chosen(gpu_lib):
         t = _seconds(lambda: ctx.spectral_radius(20))
         say(f"[ranges] time-step check {base * 1e3:.2f} ms, with {splits} splits chosen {t * 1e3:.2f} ms")
         assert t < slack * base
+
+
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+@pytest.mark.parametrize("o,v,nq,R", [(4, 16, 50, 64), (7, 9, 33, 40), (10, 40, 120, 24), (16, 64, 200, 64), (5, 11, 7, 64),
+                                      (20, 80, 131, 9)])
+def test_small_path_batch_and_single_calls_agree_bit_by_bit(gpu_lib, o, v, nq, R, prec):
+    import torch
+
+    prob = I.make_problem(I.Shape(o, v, nq, 0.05, cx=1.0, storage="f32" if prec == "fp32" else "bf16"), 3 * o + v)
+    op = O.Operator.from_problem(prob)
+    ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, prec), max_rhs=R)
+    ctx.set_tuning(small_path=1)
+    say(f"[ranges, small] {prec} o={o} v={v} nq={nq} max_rhs={R}")
+    c0, c = I.random_state(o, v, R, seed=o + v)
+    dirs, field = np.tile([[0.0, 0.0, 1.0]], (R, 1)), np.zeros(R)
+    c0d, cd = gpu_lib.to_planes(c0, c)
+    _, full = ctx.sigma(field, dirs, c0d, cd)
+    torch.cuda.synchronize()
+    got = gpu_lib.from_planes(torch.zeros_like(c0d), full)[1]
+    for r in (0, R - 1):
+        ref = O.apply_H(op, O.dipole_blocks(op, dirs[r]), 0.0, c0[r], c[r])[1]
+        assert np.linalg.norm(got[r] - ref) <= 2e-6 * np.linalg.norm(ref), r  # (FP32 sums in both precisions)
+    pulses = [I.Pulse(kind=I.PULSE_CW, e0=0.02, omega=0.5, phase=0.1 * r, direction=I.AXES[r % 3]) for r in range(R)]
+    batch = {}
+    for integ in ("rk4", "sso"):
+        g0, g = gpu_lib.ground_state(R, o, v)
+        batch[integ] = (ctx.propagate(pulses, 0.01, 3, g0, g, integrator=integ), g)
+    for n in (1, 2, 5):
+        _, few = ctx.sigma(field[-n:], dirs[-n:], c0d[-n:].contiguous(), cd[-n:].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(few, full[-n:]), n
+        for integ, (tr, g) in batch.items():
+            h0, h = gpu_lib.ground_state(n, o, v)
+            t = ctx.propagate(pulses[-n:], 0.01, 3, h0, h, integrator=integ)
+            torch.cuda.synchronize()
+            assert torch.equal(h, g[-n:]) and torch.equal(t, tr[:, -n:]), (integ, n)
+
+
+def test_small_path_one_state_of_a_large_context(gpu_lib):
+    o, v, nq = 16, 64, 200
+    dev = gpu_lib.DeviceProblem(I.make_problem(I.Shape(o, v, nq, 0.03), 9), "fp32")
+    t = {}
+    for R in (1, 64):
+        ctx = gpu_lib.Context(dev, max_rhs=R)
+        ctx.set_tuning(small_path=1)
+        c0, c = gpu_lib.ground_state(1, o, v)
+        pulses = I.gauss_cos_scan(0.39, 0.05, n=1)
+        t[R] = _seconds(lambda: ctx.propagate(pulses, 0.01, 4, c0, c))
+        t[-R] = _seconds(lambda: ctx.spectral_radius(20))
+    say(f"[ranges, small] one RHS: max_rhs 1 {t[1] * 1e3:.2f} ms, 64 {t[64] * 1e3:.2f} ms; time-step check "
+        f"{t[-1] * 1e3:.2f}, {t[-64] * 1e3:.2f} ms")
+    assert t[64] < 2.5 * t[1] and t[-64] < 2.5 * t[-1]

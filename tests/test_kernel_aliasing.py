@@ -21,7 +21,7 @@ def test_stage_update_buffers_may_alias(tmp_path):
     subprocess.run([B.HIPCC, *B.FLAGS, "-O0", "--cuda-device-only", "-S", "-emit-llvm", "-Xclang",
                     "-disable-llvm-passes", "-o", ir, SRC], check=True, capture_output=True)
     kernels = [ln for ln in open(ir) if ln.startswith("define") and "amdgpu_kernel" in ln and "k_epilogue" in ln]
-    assert len(kernels) == 2  # FP32 and split BF16
+    assert len(kernels) >= 2  # FP32 and split BF16
     for ln in kernels:
         params = re.sub(r"\([^()]*\)", "", ln[ln.index("(") + 1:])  # (attributes' own arguments)
         params = params[:params.index(")")].split(",")
