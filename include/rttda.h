@@ -316,7 +316,8 @@ typedef struct rttda_tuning {
   int32_t exchange_splits;  /* number of partial sums over Q of a full launch (2 max_rhs
                                slices); the library's own count of a variant leaves the
                                launches on fewer slices theirs (split operator, time-step
-                               check).  An X-resident variant may add a sum from shorter
+                               check), and a variant named alone brings its own unless a
+                               caller has chosen another.  An X-resident variant may add a sum from shorter
                                ranges, which a call with few right-hand sides spreads over
                                the CUs: the bits are the same either way               */
   int32_t coulomb_splits;   /* number of Q ranges the second Coulomb product is split into */

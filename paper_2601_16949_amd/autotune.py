@@ -67,8 +67,8 @@ GEMM_CHUNKS = (0, 6, 12)  # Q per chunk tried for the large-o GEMM path (0 = as 
 
 def candidates(ctx, max_per_variant: int = 5) -> List[tuple]:
     """(variant, splits, Q chunk) triples: every variant holding o, with splits from half to four
-    times the library's default (at most what the workspace holds); the GEMM path also over a
-    few chunk lengths (0 elsewhere)."""
+    times the library's default for it (at most what the workspace holds); the GEMM path also over a
+    few chunk lengths (0 elsewhere).  The context's own tile and splits are in force again afterwards."""
     lib = ctx.lib
     prec = ctx.desc.precision
     n = lib.rttda_exchange_variants(prec)
@@ -76,7 +76,7 @@ def candidates(ctx, max_per_variant: int = 5) -> List[tuple]:
     out = []
     for k in range(1, n + 1):
         try:
-            ctx.set_tuning(exchange_variant=k)
+            ctx.set_tuning(exchange_variant=k)  # with its own split count
         except Exception:
             continue  # variant does not hold o
         s0 = ctx.get_tuning()["exchange_splits"]

@@ -263,6 +263,7 @@ struct rttda_ctx {
   // X-resident variant's workgroups fill the CUs in whole rounds, so fewer slices take more splits.
   // Equal to sk for the other variants and once a tile or split count has been chosen by the caller.
   int sk_real = 0, sk_one = 0;
+  bool sk_set = false;  // sk is a count that a caller chose, not the variant's own
   // ranges of Q whose FP32 sum each of those splits is (see resident_ranges); 1 for the other variants
   int sub = 1, sub_real = 1, sub_one = 1;
   int use_graph = 1, steps_per_graph = 8;
@@ -1147,9 +1148,11 @@ rttda_status rttda_set_tuning(rttda_ctx *ctx, const rttda_tuning *t) {
   if (ctx->nq > 0) {
     ctx->xvar = xv;
     if (t->exchange_variant || t->exchange_splits) {
-      // (the library's own count leaves the other kinds of launch theirs)
+      // a variant alone brings its own count, or keeps the one a caller has chosen; the library's own count
+      // leaves the other kinds of launch theirs
       default_launch(ctx);
-      if (sk != ctx->sk) {
+      ctx->sk_set = (t->exchange_splits || ctx->sk_set) && sk != ctx->sk;
+      if (ctx->sk_set) {
         ctx->sk = ctx->sk_real = ctx->sk_one = sk;
         set_subranges(ctx);
       }
