@@ -1131,32 +1131,37 @@ hipError_t launch_set_state(hipStream_t s, DevState *st, long long step0, double
 //   S_s(w) = w Re sum_n h_n R_n exp(i w t_n) dt,
 // with h_n = (1 + cos(pi n / N)) / 2, t_n = n dt, n = 0..N.
 //
-// Bound by FP64 arithmetic: one block per SPW frequencies, its threads over the samples n = t,
-// t + 256, ..., so that every frequency has 256 sums in flight (one thread per frequency left most of
+// Bound by FP64 arithmetic: one block of NT threads per SPW frequencies, its threads over the samples n = t,
+// t + NT, ..., so that every frequency has NT sums in flight (one thread per frequency left most of
 // the chip idle behind a serial chain of sincos: 24.9 ms for 20001 samples, three signals and 2001
-// frequencies, 0.043 ms now).  A thread's phases advance by a rotation through 256 w dt (and the
-// window's by 256 pi / N), set afresh from sincos every SPREF samples, so that the rotation's
+// frequencies, 0.043 ms now).  A thread's phases advance by a rotation through NT w dt (and the
+// window's by NT pi / N), set afresh from sincos every SPREF samples, so that the rotation's
 // rounding stays near that of the arguments themselves.  Signals are taken SPS at a time; the block
-// sum runs in a fixed order.
+// sum runs in a fixed order.  A record of up to SPEC_SHORT samples takes blocks of one wave: where there are
+// many frequencies a thread's first sincos cost more than its few samples (100000 frequencies, one signal: 50
+// samples 230 -> 129 us, 1000 samples 266 -> 139 us, the binding's own 120 us a call included; 2000 samples of
+// one frequency would take 15 us for 11).
 // average: out[w] = the mean over the signals (eq. spectrum_average) instead of out[s][w].
 constexpr int SPW = 4, SPS = 3, SPREF = 32;
+constexpr int SPEC_SHORT = 1024;
 
-template <int KIND>
-__global__ __launch_bounds__(256) void k_spectrum(const double *__restrict__ sig, int n_t, int nsig, double dt,
+template <int KIND, int NT>
+__global__ __launch_bounds__(NT) void k_spectrum(const double *__restrict__ sig, int n_t, int nsig, double dt,
                                                   double kappa, int n_w, double w0, double dw, int average,
                                                   double *__restrict__ out) {
-  __shared__ double red[4][SPW][SPS];
+  __shared__ double red[NT / 64][SPW][SPS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int w_base = blockIdx.x * SPW;
   const int N = n_t - 1;
-  double w[SPW], rc[SPW], rs[SPW];  // frequencies and the rotations through 256 samples
+  double w[SPW], rc[SPW], rs[SPW];  // frequencies and the rotations through NT samples
 #pragma unroll
   for (int k = 0; k < SPW; ++k) {
     w[k] = w0 + dw * (w_base + k);
-    sincos(w[k] * (256 * dt), &rs[k], &rc[k]);
+    rs[k] = 0.0, rc[k] = 1.0;
+    if (n_t > NT) sincos(w[k] * (NT * dt), &rs[k], &rc[k]);
   }
   double hrs = 0.0, hrc = 1.0;
-  if (N > 0) sincos(M_PI * 256.0 / N, &hrs, &hrc);
+  if (n_t > NT) sincos(M_PI * (double)NT / N, &hrs, &hrc);
   double mean = 0.0;  // thread k < SPW: frequency w_base + k
   for (int s0 = 0; s0 < nsig; s0 += SPS) {
     const int ns = min(SPS, nsig - s0);
@@ -1167,13 +1172,13 @@ __global__ __launch_bounds__(256) void k_spectrum(const double *__restrict__ sig
 #pragma unroll
       for (int k = 0; k < SPW; ++k) acc[k][s] = 0.0;
     }
-    for (long long n0 = tid; n0 < n_t; n0 += 256 * SPREF) {
+    for (long long n0 = tid; n0 < n_t; n0 += NT * SPREF) {
       double sn[SPW], cs[SPW], hs = 0.0, hc = 1.0;
 #pragma unroll
       for (int k = 0; k < SPW; ++k) sincos(w[k] * (n0 * dt), &sn[k], &cs[k]);
       if (N > 0) sincos(M_PI * (double)n0 / N, &hs, &hc);
-      const long long n1 = min((long long)n_t, n0 + 256 * SPREF);
-      for (long long n = n0; n < n1; n += 256) {
+      const long long n1 = min((long long)n_t, n0 + NT * SPREF);
+      for (long long n = n0; n < n1; n += NT) {
         const double h = 0.5 * (1.0 + hc);
         double a[SPS], b[SPS];  // windowed sample: the trace, or the real and imaginary correlation
 #pragma unroll
@@ -1219,7 +1224,8 @@ __global__ __launch_bounds__(256) void k_spectrum(const double *__restrict__ sig
     if (tid < SPW && w_base + tid < n_w) {
       const double wk = w0 + dw * (w_base + tid);
       for (int s = 0; s < ns; ++s) {
-        const double sum = (red[0][tid][s] + red[1][tid][s]) + (red[2][tid][s] + red[3][tid][s]);
+        double sum = red[0][tid][s];
+        if constexpr (NT == 256) sum = (sum + red[1][tid][s]) + (red[2][tid][s] + red[3][tid][s]);
         const double val = KIND == 0 ? wk * sum * dt / kappa : wk * sum * dt;
         if (average)
           mean += val;
@@ -1234,10 +1240,17 @@ __global__ __launch_bounds__(256) void k_spectrum(const double *__restrict__ sig
 hipError_t launch_spectrum(hipStream_t s, int kind, const double *sig, int n_t, int nsig, double dt, double kappa,
                            int n_w, double w0, double dw, int average, double *out) {
   const dim3 grid((n_w + SPW - 1) / SPW);
-  if (kind == 0)
-    hipLaunchKernelGGL(k_spectrum<0>, grid, dim3(256), 0, s, sig, n_t, nsig, dt, kappa, n_w, w0, dw, average, out);
-  else
-    hipLaunchKernelGGL(k_spectrum<1>, grid, dim3(256), 0, s, sig, n_t, nsig, dt, kappa, n_w, w0, dw, average, out);
+  auto go = [&](auto k, auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((k_spectrum<decltype(k)::value, NT>), grid, dim3(NT), 0, s, sig, n_t, nsig, dt, kappa, n_w, w0,
+                       dw, average, out);
+  };
+  auto pick = [&](auto k) {
+    if (n_t <= SPEC_SHORT) go(k, std::integral_constant<int, 64>{});
+    else go(k, std::integral_constant<int, 256>{});
+  };
+  if (kind == 0) pick(std::integral_constant<int, 0>{});
+  else pick(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 
