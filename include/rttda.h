@@ -353,7 +353,9 @@ rttda_status rttda_exchange_splits_max(const rttda_ctx *ctx, int32_t *out);
  * on, rttda_propagate launches kernels directly (no graph replay) and brackets each
  * launch group with an event pair; rttda_get_profile synchronises and returns the
  * launch counts and summed durations since profiling was last switched on.
- * Classes: 0 exchange, 1 Coulomb pair, 2 field/trace, 3 RK4 epilogue + stage scalars. */
+ * Classes: 0 exchange, 1 Coulomb pair, 2 field/trace, 3 RK4 epilogue + stage scalars.  A
+ * field product that a stage's first Coulomb (small path: partial-sum) launch carries counts
+ * there. */
 typedef struct rttda_profile {
   int64_t launches[4];
   double ms[4];

@@ -112,9 +112,9 @@ constexpr int SMALL_R_MAX = 64;
 constexpr double SMALL_DEFAULT_FLOPS = 2e7;
 // (with the partial-sum kernel's LDS, a slice's X and W and one Q's B_vv and B_oo in FP32, the shapes that
 // the path takes)
-constexpr int SMALL_LDS_DOUBLES = 12288;
+constexpr int SMALL_LDS_FLOATS = 12288;
 inline bool small_shape_ok(int o, int v) {
-  return (long long)o * v <= SMALL_OV_MAX && 2LL * o * v + (long long)v * v + (long long)o * o <= SMALL_LDS_DOUBLES;
+  return (long long)o * v <= SMALL_OV_MAX && 2LL * o * v + (long long)v * v + (long long)o * o <= SMALL_LDS_FLOATS;
 }
 hipError_t prepare_small();  // one-time kernel attributes (dynamic LDS); call outside graph capture
 hipError_t launch_small_2e(hipStream_t s, int b_dtype, const void *Bov, const void *Boo, const void *Bvv,

@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * NWC * NWR, 1) void k_xgemm_w(const __bf16 *__r
   // every load and barrier.  Per chunk, after the barrier that publishes it: read K step 0's fragments
   // (F0), run K step 1 of the chunk before (F1, read before the barrier) while they arrive, then the X_hi
   // half of K step 0, then read K step 1's fragments into F1 while the X_lo half runs.  The loads of the
-  // chunk two ahead go into the buffer of the chunk before; past the last tile they load the zero page,
+  // chunk two ahead go into the buffer of the chunk before; past the last tile they load that tile again,
   // which keeps the loop free of branches around the loads.
   int rbuf = 0;
   bool stored = false;  // exactly NS stores of the tile before may be in flight behind the loads
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(64 * NWC * NWR, 1) void k_xgemm_w(const __bf16 *__r
 }
 
 // ---------------------------------------------------------------------------------------------
-// (B) P[ks][s][i][c] (+)= scale * sum_{qq in split ks} sum_j B_oo^(q0+qq)[i][j] W^T[qq][c][s*o + j]
+// (B) P[ks][s][i][c] (+)= scale * sum_{qq in split ks} sum_j B_oo^(q0+qq)[i][j] W^T[qq][c][s*op + j]
 // over the flattened columns n = (s, c).
 // Waves: NWM along i x NWN along n; each wave MB x NB blocks.  Reduction chunks run over (qq, j).
 // ---------------------------------------------------------------------------------------------

@@ -28,7 +28,9 @@
 // What bounds it: in FP32 the matrix cores (busy about 89 % of the time at o60 v400 N_Q1500, 3 RHS: 1660
 // us per launch, where the best LDS-staged tile takes 1870).  In split BF16, whose products are eight
 // times shorter, the L1's lookups of B_vv and B_oo rows and the waits of two waves per SIMD (matrix
-// cores busy about 48 %: 386 us against 536-600).  The Q ranges of a workgroup are long (42 slabs there
+// cores busy about 48 %: 386 us against 536-600); the 64-row and the two-slice 32-row tiles also spill
+// (51 and 27 registers, 80 and 48 bytes a lane: K accumulators that are read and written once per Q, in
+// order behind the ring's loads).  The Q ranges of a workgroup are long (42 slabs there
 // against 220-357), which the stage epilogue feels: 18 us for 38-51.
 // Odd sizes run like even ones: o37 v277 N_Q743, 2 RHS, split BF16: 86 us (320 for the register-staged
 // tile); o27 v203 N_Q541, 3 RHS, FP32: 124 us (192).
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
                                                                 float *__restrict__ P) {
   using C = CfgR<BF, JB, KS, NCBM, PK>;
   constexpr int RB = C::RB, KB = C::KB, PL = C::PL, GV = C::GV, SZ = C::SZ;
-  constexpr int D = 2;                       // double steps of B_vv in flight (three measure the same)
+  constexpr int D = 2;                       // double steps of B_vv in flight (of every other one, see the loop below)
   constexpr int HA = (RB + 1) / 2;           // row blocks of the first half of a step
   // K-product steps: pairs of row blocks (the last may be a single one); packed: each slice's JB
   constexpr int NP = BF ? (JB + 1) / 2 : PK ? 2 * JB : JB;
@@ -491,8 +493,10 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
           if ((q ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
         }
       };
-      // (the exits between the slots leave the loop at once: a path on which a slot is skipped would
-      // make the compiler wait for every load in flight)
+      // (an exit after each slot.  The compiler makes the first one part of the loop's end, sees a path on which
+      // slot 0 has just been loaded, and waits for every load in flight before slot 0's products, with slot
+      // 1's two loads per block still in flight before its own: every second double step starts on an empty
+      // ring)
       for (;;) {
         step(ring[0]);
         if (q >= qb) break;

@@ -581,7 +581,7 @@ __global__ void k_plane_copy(int R, size_t ov, int plane, const double *__restri
 // ------------------------------------------------------------------------------------------------
 // Lanczos iteration on A (stability guard: the RK4 step is stable for rho(A) dt below ~2.8).
 // Vectors of length ov in FP64; A v = D v + (Coulomb + exchange partials of v) for one real
-// slice.  Block partial sums go to part[blockIdx.x] and are added in a fixed order on the host.
+// slice.  Block partial sums go to part[blockIdx.x] and are added in a fixed order by the next launch.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ double block_sum(double x, double *sh) {
   x = wave_sum(x);
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(256) void k_lz_orth(long long n, const double *__re
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// vprev = v; v = w * scale; FP32 (+ BF16 hi/lo) copy of v for the next product
+// beta = sqrt(sum dots), vprev = v (shift), v = w / beta; FP32 (+ BF16 hi/lo) copy of v for the next product
 template <int PREC>
 __global__ __launch_bounds__(256) void k_lz_next(long long n, const double *__restrict__ dots,
                                                  double *__restrict__ beta_out, const double *__restrict__ w,

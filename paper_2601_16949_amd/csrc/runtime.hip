@@ -730,7 +730,7 @@ int nslab(const rttda_ctx *ctx, Slices kind, int ns) {
   return sb.nc + (sb.n - sb.nc) * sb.grp;
 }
 
-// the small path applies to the shape (o v and the RHS count within its single-workgroup limits)
+// the small path applies to the shape (o v, the RHS count and a workgroup's LDS within its limits)
 bool small_fits(int o, int v, int R) { return small_shape_ok(o, v) && R <= SMALL_R_MAX; }
 
 // One RK4 step (4 stages) on the context's stream.

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void k_small_2e(const TB *__restrict__ Bov, co
 }  // namespace
 
 hipError_t prepare_small() {
-  const int bytes = SMALL_LDS_DOUBLES * (int)sizeof(double);
+  const int bytes = SMALL_LDS_FLOATS * (int)sizeof(float);
   const void *fn[] = {reinterpret_cast<const void *>(&k_small_2e<float, false>),
                       reinterpret_cast<const void *>(&k_small_2e<float, true>),
                       reinterpret_cast<const void *>(&k_small_2e<__hip_bfloat16, false>),
