@@ -260,10 +260,11 @@ struct ExchangeVariant {
   int rank = 0;          // preference among variants of equal tile waste (higher first)
   int v_max = 1 << 30;
   void (*res)(int v, int ns, struct ResShape *) = nullptr;  // X resident in LDS (one workgroup fills a CU)
-  // X-resident variants, of whose splits each is cut into m ranges of Q: nsplit slabs, either each the FP32 sum
-  // of its m ranges in order (in_slab) or one range each, every m of them to be added so by the reader
+  // X-resident variants, of whose nsplit splits each is cut into m ranges of Q: a workgroup per split (whole), which
+  // leaves their FP32 sum (FP32) or each (split BF16), or a workgroup per range, which leaves that.  A slab per
+  // range left, every m of them to be added in FP32, in order, by the reader
   hipError_t (*launch_ranges)(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o,
-                              int v, int nq, int ns, int nsplit, int m, bool in_slab, float scale, float *P) = nullptr;
+                              int v, int nq, int ns, int nsplit, int m, bool whole, float scale, float *P) = nullptr;
   int rows = 0;  // scratch variants: stacked rows per tile of the first GEMM (nt: its columns)
   int cols = 0;  //                   columns per tile of the second
   bool applies(int o, int v) const {

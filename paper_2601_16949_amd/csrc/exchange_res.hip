@@ -137,9 +137,9 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
   return j0 < o && j >= j0 ? j : -1;
 }
 
-// Each of a launch's splits is cut into m ranges of Q, whose sums are added in FP32, in order.  RNG: a workgroup
-// takes a split and adds them in its slab; else one takes a range, leaves its sum, and the stage update adds
-// them, with the same bits.  So a context whose full batch fills the CUs with long splits (few slabs, X staged
+// RANGES: 0, a workgroup per split of Q.  Else each split is cut into m ranges of Q, whose sums are added in FP32, in
+// order: 2 (RNG), a workgroup takes a split and adds them in its slab (FP32) or leaves each (split BF16); 1 (EACH),
+// one takes a range and leaves its sum.  The stage update adds what is left, with the same bits.  So a context whose full batch fills the CUs with long splits (few slabs, X staged
 // once) keeps short ones for a call with few of its right-hand sides, which would else run on a few CUs, and the
 // FP32 chains stay short in both: o40 v300 N_Q1000 FP32, max_rhs 64, 4 splits of 32 ranges: one RHS 1.6 ms per
 // step (34.9 without ranges), all 64 36.0 (35.6); o60 v400 N_Q1500, max_rhs 3, per two steps, one RHS: 5.7 ms
@@ -147,7 +147,7 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
 // (The second
 // phase's blocks, whose waves share the split's Q in eighths, are left out of that: the workgroup of a split's
 // first range takes them, the others' slabs hold zeros there.)
-template <bool BF, int JB, int KS, int NCBM, bool PK, bool RNG>
+template <bool BF, int JB, int KS, int NCBM, bool PK, int RANGES>
 __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__restrict__ Boo,
                                                                 const char *__restrict__ Bvv,
                                                                 const char *__restrict__ X,
@@ -215,7 +215,10 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
 
   const int nblk = (v + 15) / 16;
   const int t0 = tile_block(nblk, nct, ct), t1 = tile_block(nblk, nct, ct + 1);
-  const int n_split = RNG ? nsplit : nsplit / m, split = RNG ? sp : sp / m, range = RNG ? 0 : sp % m;
+  // ADD: in the slab, which all workgroups read and write at once (o60 v400, 3 RHS: 4 us a range in FP32, whose
+  // ranges are long; 13 us in split BF16, where leaving them costs the launch 2 us and the stage update 5)
+  constexpr bool EACH = RANGES == 1, RNG = RANGES == 2, ADD = !BF;
+  const int n_split = EACH ? nsplit / m : nsplit, split = EACH ? sp / m : sp, range = EACH ? sp - split * m : 0;
   const int Qa = (int)((long long)split * nq / n_split), Qb = (int)((long long)(split + 1) * nq / n_split);
   auto bound = [&](int k) { return Qa + k * (Qb - Qa) / m; };  // the split's ranges
 
@@ -243,15 +246,17 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
     const unsigned row_bytes = (unsigned)(v * SZ), row_last = (unsigned)(v - 1) * row_bytes;
 #pragma unroll
     for (int c = 0; c < NCB; ++c) roff[c] = (unsigned)min((b0 + c) * 16 + (n & ~1), v - 1) * row_bytes;
-    // RNG: K to the slab; ranges after a split's first are added to what it holds
-    auto flush = [&](bool add) __attribute__((always_inline)) {
+    // RNG: K, the sum of the split's range rg, to its slab, or added to what the split's holds
+    auto flush = [&](int rg) __attribute__((always_inline)) {
+      const bool add = ADD && rg > 0;
+      const int to = ADD ? sp : sp * m + rg;
       int ln = lane;  // (opaque here: addresses made from it would be held in registers through the loop)
       asm volatile("" : "+v"(ln));
       unsigned col[NCB];  // byte offsets, from clamped places
 #pragma unroll
       for (int c = 0; c < NCB; ++c) col[c] = 4u * min((b0 + c) * 16 + (ln & 15), v - 1);
       auto slab = [&](int a) __attribute__((always_inline)) {
-        return reinterpret_cast<char *>(P + ((size_t)sp * ns + min(s_base + a / JB, ns - 1)) * o * v);
+        return reinterpret_cast<char *>(P + ((size_t)to * ns + min(s_base + a / JB, ns - 1)) * o * v);
       };
       auto row = [&](int a, int t) __attribute__((always_inline)) {
         return 4u * (unsigned)v * min((a % JB) * 16 + 4 * (ln >> 4) + t, o - 1);
@@ -473,7 +478,7 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
           }
           if constexpr (RNG) {
             if (q + 1 == qf && q + 1 < qb) {
-              flush(rg > 0);
+              flush(rg);
 #pragma unroll
               for (int a = 0; a < KB; ++a)
 #pragma unroll
@@ -506,7 +511,7 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
     }
     if constexpr (RNG) {
       if (nparts == 1) {
-        flush(rg > 0);
+        flush(rg);
         return;
       }
     }
@@ -517,7 +522,14 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int i = (a % JB) * 16 + 4 * (ln >> 4) + t;
-        if (sl < ns && i < o && col < v) P[(((size_t)sp * ns + sl) * o + i) * v + col] = scale * k[t];
+        if (sl < ns && i < o && col < v) {
+          if constexpr (RNG && !ADD) {  // (the whole split's sum with its first range, zeros with the others)
+            for (int r = 0; r < m; ++r)
+              P[(((size_t)(sp * m + r) * ns + sl) * o + i) * v + col] = r ? 0.f : scale * k[t];
+          } else {
+            P[(((size_t)sp * ns + sl) * o + i) * v + col] = scale * k[t];
+          }
+        }
       }
     };
     if (nparts == 1) {
@@ -561,12 +573,12 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   };
   for (int phase = 0; phase < (rem ? 2 : 1); ++phase) {
     int cg = wave % ncg, part = wave / ncg, nparts = qs, pstride = ncg, b0 = 0, w = 0;
-    int qa0 = RNG ? Qa : bound(range), qb0 = RNG ? Qb : bound(range + 1);
+    int qa0 = EACH ? bound(range) : Qa, qb0 = EACH ? bound(range + 1) : Qb;
     if (phase == 0) {
       if (part < qs) group_blocks(t1 - t0, rem, ncg, cg, b0, w);
     } else {
       cg = 0, part = wave, nparts = NWAVE, pstride = 1, b0 = t1 - t0 - rem, w = rem;
-      qa0 = Qa, qb0 = RNG || range == 0 ? Qb : Qa;
+      if (EACH) qa0 = Qa, qb0 = range == 0 ? Qb : Qa;
     }
     const int qa = qa0 + (int)((long long)part * (qb0 - qa0) / nparts);
     const int qb = qa0 + (int)((long long)(part + 1) * (qb0 - qa0) / nparts);
@@ -574,43 +586,45 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
   }
 }
 
-// nsplit slabs, each the sum of its own m ranges (RNG) or every m of them to be added by the reader
+// nsplit splits of m ranges: a workgroup per split (whole), which leaves one slab (FP32) or m, or a workgroup and a
+// slab per range
 template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t launch_xres_ranges(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o,
-                              int v, int nq, int ns, int nsplit, int m, bool in_slab, float scale, float *P) {
+                              int v, int nq, int ns, int nsplit, int m, bool whole, float scale, float *P) {
   using C = CfgR<BF, JB, KS, NCBM, PK>;
   const Split sp = choose_split(v, NCBM);
-  const long long ranges = in_slab ? (long long)nsplit * m : nsplit;
   if (o > C::OMAX || o < 4 || (BF && JB > 1 && o < 8) || v < C::GV || v > C::VMAX || nsplit < 1 || m < 1 ||
-      ranges > nq || ranges % m != 0 || (m > 1 && sp.qs > 1))
+      (long long)nsplit * m > nq || (m > 1 && sp.qs > 1))
     return hipErrorInvalidValue;
   const int nst = ((v + C::GV - 1) / C::GV + 3) / 4;  // K steps
   const size_t lds = std::max((size_t)nst * C::STEP_LDS, sp.qs > 1 || sp.rem ? (size_t)NWAVE * C::KB * NCBM * 1024 : (size_t)0);
   if (lds > LDS_MAX) return hipErrorInvalidValue;
   const int n_sg = (ns + KS - 1) / KS;
-  const int total = n_sg * sp.nct * nsplit;
+  const int per_tile = whole ? nsplit : nsplit * m, total = n_sg * sp.nct * per_tile;  // workgroups
   const dim3 grid((total + 7) / 8 * 8);
   auto go = [&](auto rng) {
     hipLaunchKernelGGL((k_exchange_res<BF, JB, KS, NCBM, PK, decltype(rng)::value>), grid, dim3(64 * NWAVE), lds, s,
                        static_cast<const char *>(Boo), static_cast<const char *>(Bvv), static_cast<const char *>(X),
-                       static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, nsplit, m,
-                       scale, P);
+                       static_cast<const char *>(Xlo), o, v, nq, ns, n_sg, sp.nct, sp.ncg, sp.qs, sp.rem, per_tile,
+                       m, scale, P);
   };
-  if (in_slab && m > 1) go(std::true_type{});
-  else go(std::false_type{});
+  if (m == 1) go(std::integral_constant<int, 0>{});
+  else if (whole) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 
 template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t launch_xres(hipStream_t s, const void *Boo, const void *Bvv, const void *X, const void *Xlo, int o, int v,
                        int nq, int ns, int nsplit, float scale, float *P, void *, size_t) {
-  return launch_xres_ranges<BF, JB, KS, NCBM, PK>(s, Boo, Bvv, X, Xlo, o, v, nq, ns, nsplit, 1, false, scale, P);
+  return launch_xres_ranges<BF, JB, KS, NCBM, PK>(s, Boo, Bvv, X, Xlo, o, v, nq, ns, nsplit, 1, true, scale, P);
 }
 
 template <bool BF, int JB, int KS, int NCBM, bool PK>
 hipError_t prepare_xres() {
-  const void *fn[] = {reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, false>),
-                      reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, true>)};
+  const void *fn[] = {reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, 0>),
+                      reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, 1>),
+                      reinterpret_cast<const void *>(&k_exchange_res<BF, JB, KS, NCBM, PK, 2>)};
   for (const void *f : fn) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
     if (e != hipSuccess) return e;

@@ -609,28 +609,32 @@ int exchange_subranges(const rttda_ctx *ctx, Slices k) {
   return k == SL_COMPLEX ? ctx->sub : k == SL_REAL ? ctx->sub_real : ctx->sub_one;
 }
 
-// How a launch of ns slices divides the exchange: `slabs` splits of Q, each the sum of `m` ranges in its
-// workgroup, and `grp` of them to be added in FP32 by the stage update (m grp = the ranges of a split).
-// Many slices take a workgroup per split and slice group, which stages X once for all its ranges and writes
-// one slab; a call with few of the context's right-hand sides a workgroup per range, or most CUs would idle.
-// Both add the same sums in the same order, so a batch and one of its right-hand sides alone agree bit by bit.
+// How a launch of ns slices divides the exchange (small path: both parts of sigma): `splits` splits of Q of m ranges
+// each, by a workgroup per split and slice group (whole), which stages X once for all its ranges, or by one per
+// range, where a call has few of the context's right-hand sides and most CUs would idle.  It leaves `slabs`, of
+// which the stage update adds every grp in FP32, as a workgroup adds its ranges where it leaves their sum: both
+// ways add the same sums in the same order, so a batch and one of its right-hand sides alone agree bit by bit.
 struct ExchangePlan {
-  int slabs, m, grp;
+  int splits, m;
+  bool whole;
+  int slabs, grp;
 };
 ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
+  const int sk = ctx->small ? ctx->small_splits : exchange_splits(ctx, k);
+  const int m = ctx->small ? ctx->small_sub : exchange_subranges(ctx, k);
+  const ExchangePlan sums{sk, m, true, sk, 1}, parts{sk, m, true, sk * m, m}, each{sk, m, false, sk * m, m};
+  if (m == 1) return sums;
   const size_t room = (size_t)(ctx->L.sj_max + ctx->L.sk_max) * 2 * ctx->R;  // slabs of one slice
-  if (ctx->small) {  // (both parts of sigma: a workgroup per range where one per split would not reach every CU)
-    const int sk = ctx->small_splits, sub = ctx->small_sub;
-    return ns * sk <= 256 && (size_t)sk * sub * ns <= room ? ExchangePlan{sk * sub, 1, sub} : ExchangePlan{sk, sub, 1};
-  }
-  const int sk = exchange_splits(ctx, k), sub = exchange_subranges(ctx, k);
-  if (sub == 1 || ((size_t)ctx->sj + (size_t)sk * sub) * ns > room) return {sk, sub, 1};
+  const bool fits = ((size_t)(ctx->small ? 0 : ctx->sj) + (size_t)sk * m) * ns <= room;
+  if (ctx->small) return fits && ns * sk <= 256 ? each : sums;  // (each where a workgroup per split leaves CUs)
+  const ExchangePlan whole = ctx->prec == RTTDA_PREC_FP32 ? sums : parts;
+  if (!fits) return whole;  // (parts always fit, see set_subranges)
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
   ResShape r;
   x->res(ctx->v, ns, &r);
-  const double one = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk, sub);
-  const double all = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk * sub, 1);
-  return one <= all ? ExchangePlan{sk, sub, 1} : ExchangePlan{sk * sub, 1, sub};
+  const double t1 = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk, m);
+  const double t = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk * m, 1);
+  return t1 <= t ? whole : each;
 }
 
 // Default splits of the current variant, and whether the Coulomb pair runs alongside it: only where
@@ -642,8 +646,10 @@ ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
 // the least of them, o160 v1200 with one RHS, 2 % slower).
 void set_subranges(rttda_ctx *ctx) {
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
+  // (split BF16 leaves every range's slab, so the workspace's slabs bound them)
+  const int cap = ctx->prec == RTTDA_PREC_FP32 ? ctx->nq : ctx->L.sk_max;
   auto n = [&](int ns, int few, int sk) {
-    return x->res ? resident_ranges(x, ctx->o, ns, few, ctx->v, ctx->nq, sk) : 1;
+    return x->res ? std::max(1, std::min(resident_ranges(x, ctx->o, ns, few, ctx->v, ctx->nq, sk), cap / sk)) : 1;
   };
   ctx->sub = n(2 * ctx->R, 2, ctx->sk);
   ctx->sub_real = n(ctx->R, 1, ctx->sk_real);
@@ -679,7 +685,7 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   if (ctx->small) {
     if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
     HIP_TRY(launch_small_2e(s, ctx->d.b_dtype, ctx->d.b_ov, ctx->d.b_oo, ctx->d.b_vv, ctx->x32(), ctx->o, ctx->v,
-                            ctx->nq, ns, pl.slabs, pl.m, (float)ctx->d.cx, ctx->P(), f));
+                            ctx->nq, ns, pl.whole ? pl.splits : pl.slabs, pl.whole ? pl.m : 1, (float)ctx->d.cx, ctx->P(), f));
     if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
     return RTTDA_OK;
   }
@@ -707,10 +713,10 @@ rttda_status enqueue_two_electron(rttda_ctx *ctx, int ns, Slices kind = SL_COMPL
   const void *Xlo = ctx->prec == RTTDA_PREC_FP32 ? nullptr : (const void *)ctx->xlo();
   if (pr) HIP_TRY(ctx->prof.begin(PC_EXCHANGE, s));
   if (x->res)
-    HIP_TRY(x->launch_ranges(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.slabs,
-                             exchange_subranges(ctx, kind), pl.m > 1, (float)(-ctx->d.cx), Pk));
+    HIP_TRY(x->launch_ranges(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.splits, pl.m,
+                             pl.whole, (float)(-ctx->d.cx), Pk));
   else
-    HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.slabs,
+    HIP_TRY(x->launch(s, ctx->d.b_oo, ctx->d.b_vv, X, Xlo, ctx->o, ctx->v, ctx->nq, ns, pl.splits,
                       (float)(-ctx->d.cx), Pk, ctx->scratch(), scratch_for(ctx, ns)));
   if (pr) HIP_TRY(ctx->prof.end(PC_EXCHANGE, s));
   if (fork) HIP_TRY(hipStreamWaitEvent(s, ctx->ev_join, 0));  // join before any reader of the slabs
