@@ -137,16 +137,16 @@ __device__ __forceinline__ int slot_row(int rs, int o) {
   return j0 < o && j >= j0 ? j : -1;
 }
 
-// RANGES: 0, a workgroup per split of Q.  Else each split is cut into m ranges of Q, whose sums are added in FP32, in
-// order: 2 (RNG), a workgroup takes a split and adds them in its slab (FP32) or leaves each (split BF16); 1 (EACH),
-// one takes a range and leaves its sum.  The stage update adds what is left, with the same bits.  So a context whose full batch fills the CUs with long splits (few slabs, X staged
-// once) keeps short ones for a call with few of its right-hand sides, which would else run on a few CUs, and the
-// FP32 chains stay short in both: o40 v300 N_Q1000 FP32, max_rhs 64, 4 splits of 32 ranges: one RHS 1.6 ms per
-// step (34.9 without ranges), all 64 36.0 (35.6); o60 v400 N_Q1500, max_rhs 3, per two steps, one RHS: 5.7 ms
-// (13.9) in FP32, 42 splits of 3, and 2.3 (3.7) in split BF16, 42 of 2; all three 14.05 (13.98) and 3.83 (3.78).
-// (The second
-// phase's blocks, whose waves share the split's Q in eighths, are left out of that: the workgroup of a split's
-// first range takes them, the others' slabs hold zeros there.)
+// RANGES: 0, a workgroup per split of Q.  Else each split is cut into m ranges of Q, whose sums are added in FP32,
+// in order: 2 (RNG), a workgroup takes a split and adds them in its slab (FP32) or leaves each (split BF16); 1
+// (EACH), one takes a range and leaves its sum.  The stage update adds what is left, with the same bits.  So a
+// context whose full batch fills the CUs with long splits (few slabs, X staged once) has short ranges for a call
+// with few of its right-hand sides, which would else run on a few CUs, and the FP32 chains stay short in both.
+// o40 v300 N_Q1000 FP32, max_rhs 64, 4 splits of 32 ranges, per step: one RHS 1.5 ms (34.9 without ranges), all
+// 64 35.6 (35.3).  o60 v400 N_Q1500, max_rhs 3, per two steps: one RHS 5.7 ms (13.9) in FP32, 42 splits of 3, and
+// 2.3 (3.7) in split BF16, 42 of 2; all three 13.98 (13.92) and 3.69 (3.59).
+// (The second phase's blocks, whose waves share the split's Q in eighths, are left out of that: the workgroup of
+// a split's first range takes them, the others' slabs hold zeros there.)
 template <bool BF, int JB, int KS, int NCBM, bool PK, int RANGES>
 __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__restrict__ Boo,
                                                                 const char *__restrict__ Bvv,
