@@ -1138,12 +1138,51 @@ hipError_t launch_set_state(hipStream_t s, DevState *st, long long step0, double
 // window's by NT pi / N), set afresh from sincos every SPREF samples, so that the rotation's
 // rounding stays near that of the arguments themselves.  Signals are taken SPS at a time; the block
 // sum runs in a fixed order.  A record of up to SPEC_SHORT samples takes blocks of one wave: where there are
-// many frequencies a thread's first sincos cost more than its few samples (100000 frequencies, one signal: 50
-// samples 230 -> 129 us, 1000 samples 266 -> 139 us, the binding's own 120 us a call included; 2000 samples of
-// one frequency would take 15 us for 11).
+// many frequencies a thread's first sincos cost more than its few samples (100000 frequencies, one signal: 200
+// samples 211 -> 66 us, 1000 samples 236 -> 97 us; 2000 samples of one frequency would take 15 us for 11).  Still
+// shorter records of many frequencies take a thread per frequency, which has its samples' sincos and no others
+// (100000 frequencies: 1 sample 5 us, 10 samples 10, 64 samples 47, where a wave each takes 48; 2000
+// frequencies of 30 samples would take 15 for 7).
 // average: out[w] = the mean over the signals (eq. spectrum_average) instead of out[s][w].
 constexpr int SPW = 4, SPS = 3, SPREF = 32;
 constexpr int SPEC_SHORT = 1024;
+inline bool spec_each(int n_t, int n_w) { return n_t <= 128 && n_w >= 1024 * n_t; }
+
+// one thread per frequency
+template <int KIND>
+__global__ __launch_bounds__(256) void k_spectrum_each(const double *__restrict__ sig, int n_t, int nsig, double dt,
+                                                       double kappa, int n_w, double w0, double dw, int average,
+                                                       double *__restrict__ out) {
+  const int wi = blockIdx.x * 256 + threadIdx.x;
+  if (wi >= n_w) return;
+  const double w = w0 + dw * wi;
+  const int N = n_t - 1;
+  double mean = 0.0;
+  for (int s0 = 0; s0 < nsig; s0 += SPS) {
+    double acc[SPS] = {};
+    for (int n = 0; n < n_t; ++n) {
+      const double h = N > 0 ? 0.5 * (1.0 + cos(M_PI * (double)n / N)) : 1.0;
+      double sn, cs;
+      sincos(w * (n * dt), &sn, &cs);
+#pragma unroll
+      for (int s = 0; s < SPS; ++s) {
+        if (s0 + s >= nsig) break;
+        const size_t e = (size_t)n * nsig + s0 + s;
+        acc[s] += KIND == 0 ? h * (sig[e] - sig[s0 + s]) * sn : h * (sig[2 * e] * cs - sig[2 * e + 1] * sn);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SPS; ++s) {
+      if (s0 + s >= nsig) break;
+      const double val = KIND == 0 ? w * acc[s] * dt / kappa : w * acc[s] * dt;
+      if (average)
+        mean += val;
+      else
+        out[(size_t)(s0 + s) * n_w + wi] = val;
+    }
+  }
+  if (average) out[wi] = mean / nsig;
+}
 
 template <int KIND, int NT>
 __global__ __launch_bounds__(NT) void k_spectrum(const double *__restrict__ sig, int n_t, int nsig, double dt,
@@ -1246,7 +1285,10 @@ hipError_t launch_spectrum(hipStream_t s, int kind, const double *sig, int n_t, 
                        dw, average, out);
   };
   auto pick = [&](auto k) {
-    if (n_t <= SPEC_SHORT) go(k, std::integral_constant<int, 64>{});
+    if (spec_each(n_t, n_w))
+      hipLaunchKernelGGL((k_spectrum_each<decltype(k)::value>), dim3((n_w + 255) / 256), dim3(256), 0, s, sig, n_t, nsig,
+                         dt, kappa, n_w, w0, dw, average, out);
+    else if (n_t <= SPEC_SHORT) go(k, std::integral_constant<int, 64>{});
     else go(k, std::integral_constant<int, 256>{});
   };
   if (kind == 0) pick(std::integral_constant<int, 0>{});
