@@ -62,6 +62,7 @@ constexpr double RES_RANGE_CYCLES = 20e3;
 // exchange flops per stage (at the largest RHS count) from which the Coulomb pair gets its own stream
 constexpr double OVERLAP_MIN_FLOPS = 5e10;
 constexpr int SMALL_BLOCKS = 512;  // workgroups of the small path's partial-sum launch: two per CU
+constexpr int SMALL_RANGES = 64;   // ranges of Q that its splits are cut into for calls with few slices
 // slices (2 max_rhs) from which the Coulomb pair runs on the matrix cores
 constexpr int COUL_MFMA_MIN_SLICES = 32;
 // the exchange's partial K slabs (one per split) take at most this much workspace, or 32 slabs
@@ -379,10 +380,9 @@ int next_split(int nq, int s) {
 }
 
 // Split count of an X-resident variant: the least of those times, which *cycles receives.  Where its waves share
-// the Q of a split (narrow v, whose slabs are small), a count that takes up to 6 % more and makes a launch of
-// `few` slices, one right-hand side's, fastest (o24 v168 N_Q600 FP32, 32 RHS: 32 splits for 8, 742 for 732 us
-// per launch, one of them alone 0.81 for 2.6 ms per step); elsewhere the splits' ranges serve that
-// (resident_ranges).
+// the Q of a split (narrow v, whose slabs are small), a count that takes up to 8 % more and makes a launch of
+// `few` slices, one right-hand side's, fastest (o24 v168 N_Q600 FP32, 32 RHS: 32 splits for 8, 2.80 for 2.73 ms
+// per step, one of them alone 0.80 for 2.57); elsewhere the splits' ranges serve that (resident_ranges).
 int resident_splits(const ExchangeVariant *x, int o, int ns, int few, int v, int nq, int cap, double *cycles) {
   ResShape r;
   x->res(v, ns, &r);
@@ -402,10 +402,10 @@ int resident_splits(const ExchangeVariant *x, int o, int ns, int few, int v, int
   auto full = [&](int s) {
     const long long rounds = ((long long)r.tiles * s + 255) / 256;
     const int q = ((nq + s - 1) / s + r.qs - 1) / r.qs;
-    return ((rounds - 1) * ((double)nq / s / r.qs) + q) * r.q_cycles + rounds * (r.start_cycles + 7e3) +
+    return ((rounds - 1) * ((double)nq / s / r.qs) + q) * r.q_cycles + rounds * (r.start_cycles + 20e3) +
            s * (60.0 + 2.0 * 4 * ns * o * v / 1900.0);
   };
-  const double limit = 1.06 * full(best);
+  const double limit = 1.08 * full(best);
   double least = 1e300;
   for (int s = best; s <= std::min(cap, nq); s = next_split(nq, s)) {
     if (full(s) > limit) continue;
@@ -626,7 +626,7 @@ ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
   if (m == 1) return sums;
   const size_t room = (size_t)(ctx->L.sj_max + ctx->L.sk_max) * 2 * ctx->R;  // slabs of one slice
   const bool fits = ((size_t)(ctx->small ? 0 : ctx->sj) + (size_t)sk * m) * ns <= room;
-  if (ctx->small) return fits && ns * sk <= 256 ? each : sums;  // (each where a workgroup per split leaves CUs)
+  if (ctx->small) return fits && ns * sk <= 128 ? each : sums;  // (each where a workgroup per split leaves CUs)
   const ExchangePlan whole = ctx->prec == RTTDA_PREC_FP32 ? sums : parts;
   if (!fits) return whole;  // (parts always fit, see set_subranges)
   const ExchangeVariant *x = variant_of(ctx->prec, ctx->xvar);
@@ -634,7 +634,7 @@ ExchangePlan exchange_plan(const rttda_ctx *ctx, Slices k, int ns) {
   x->res(ctx->v, ns, &r);
   const double t1 = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk, m);
   const double t = resident_cycles(r, ctx->o, ns, ctx->v, ctx->nq, sk * m, 1);
-  return t1 <= t ? whole : each;
+  return t < 0.8 * t1 ? each : whole;  // (a split's first range has its second phase's blocks to itself)
 }
 
 // Default splits of the current variant, and whether the Coulomb pair runs alongside it: only where
@@ -1054,10 +1054,11 @@ rttda_status rttda_create(const rttda_desc *desc, rttda_ctx **out) {
     default_overlap(ctx);
     // the small path's Q ranges (the update adds one slab per range): one Q each where that takes no more than
     // SMALL_BLOCKS workgroups (o10 v40 N_Q120, one RHS, 16 steps: 120 ranges 0.90 ms, 64 1.02 ms; with
-    // eight RHS 64 ranges, 1024 workgroups, 1.70 ms and 120 2.02 ms).  Where a full batch leaves them several
-    // Q each, they are cut into ranges for the calls with few slices
+    // eight RHS 64 ranges, 1024 workgroups, 1.70 ms and 120 2.02 ms).  Where a full batch leaves fewer than
+    // SMALL_RANGES, they are cut into that many for the calls with few slices (o4 v12 N_Q161, max_rhs 40, two
+    // steps: one RHS 190 us for 465, all 40 630 for 610; with 156 ranges 740)
     ctx->small_splits = std::max(1, std::min({SMALL_BLOCKS / (2 * ctx->R), ctx->nq, L.sj_max + L.sk_max}));
-    ctx->small_sub = std::max(1, std::min(SMALL_BLOCKS / 2, ctx->nq) / ctx->small_splits);
+    ctx->small_sub = std::max(1, std::min(SMALL_RANGES, ctx->nq) / ctx->small_splits);
     ctx->coul_mfma = 2 * ctx->R >= COUL_MFMA_MIN_SLICES ? 1 : 0;
     // the default only for the smallest problems (see SMALL_DEFAULT_FLOPS)
     ctx->small = small_fits(ctx->o, ctx->v, ctx->R) &&
