@@ -71,7 +71,7 @@ def _seconds(fn, n=5):
 
 
 @pytest.mark.parametrize("prec,o,v,nq,R,part", [("fp32", 40, 300, 200, 64, 0.25), ("mixed", 40, 300, 400, 64, 0.35),
-                                                ("fp32", 60, 400, 300, 3, 0.65), ("fp32", 24, 168, 600, 32, 0.5)])
+                                                ("fp32", 60, 400, 300, 3, 0.8), ("fp32", 24, 168, 600, 32, 0.5)])
 def test_one_state_of_a_large_context_takes_less_than_the_batch(gpu_lib, prec, o, v, nq, R, part):
     prob = I.make_problem(I.Shape(o, v, nq, 0.03, storage="f32" if prec == "fp32" else "bf16"), 9)
     ctx = gpu_lib.Context(gpu_lib.DeviceProblem(prob, prec), max_rhs=R)
