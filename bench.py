@@ -57,11 +57,11 @@ TRAFFIC = {
         {"file": "exchange_bf16_dl.hip", "src": "f90b2171f434b93d",
          "fetch_bytes": 264290.89 * 1024 * 2.0, "write_bytes": 125895.47 * 1024 * 1.0},
     ("f32r_o64", "o60_v400_nq1500_kick_xyz", 42, 6):
-        {"file": "exchange_res.hip", "src": "abd22222d86b0adc",
-         "fetch_bytes": 601546.11 * 1024 * 2.0, "write_bytes": 71054.11 * 1024 * 1.0},
+        {"file": "exchange_res.hip", "src": "bc3e8a35c4a1e629",
+         "fetch_bytes": 601509.63 * 1024 * 2.0, "write_bytes": 70858.78 * 1024 * 1.0},
     ("bf16x2r_o64", "o60_v400_nq1500_kick_xyz", 42, 6):
-        {"file": "exchange_res.hip", "src": "abd22222d86b0adc",
-         "fetch_bytes": 280146.22 * 1024 * 2.0, "write_bytes": 49407.64 * 1024 * 1.0},
+        {"file": "exchange_res.hip", "src": "bc3e8a35c4a1e629",
+         "fetch_bytes": 280043.98 * 1024 * 2.0, "write_bytes": 49374.05 * 1024 * 1.0},
 }
 PEAK = {"fp32": 157.3, "mixed": 2516.6}  # dense MFMA TFLOP/s: FP32, BF16
 HBM_PEAK_GBS = 8000.0

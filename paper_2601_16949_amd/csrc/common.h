@@ -239,6 +239,7 @@ inline size_t xgemm_o_bytes(int o, size_t qc) { return o % 8 ? qc * xgemm_op(o) 
 struct ResShape {
   int tiles, qs;
   double q_cycles, start_cycles;
+  bool ranges;  // whether a split may be cut into ranges
 };
 
 struct ExchangeVariant {

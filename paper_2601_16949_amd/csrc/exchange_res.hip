@@ -285,6 +285,20 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
         }
     };
     int rg = 0, qf = RNG && nparts == 1 ? bound(1) : qb;  // RNG: ranges done, and the next one's end
+    auto next_range = [&]() __attribute__((always_inline)) {
+      flush(rg);
+#pragma unroll
+      for (int a = 0; a < KB; ++a)
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) K[a][c] = f4{0.f, 0.f, 0.f, 0.f};
+      ++rg;
+      qf = bound(rg + 1);
+    };
+    // split BF16 leaves the loop over its Q for a range's end: with that inside, the compiler spilled addresses of
+    // the widest waves' loads and waited for every load to read them back (per two steps, 3 RHS of o48 v480 N_Q1500,
+    // three blocks a wave, 4.32 ms, now 4.21, without ranges 4.19; 6 of o64 v440 N_Q1461, four, 13.6, 8.5 and 7.8,
+    // see shape_xres).  FP32 spills more with that outside.
+    constexpr bool NEST = RNG && BF;
     if (qa < qb) {
       const size_t qstride = (size_t)v * v * SZ;
       const char *ql = Bvv + (size_t)qa * qstride;  // Q and double step of the next load
@@ -476,17 +490,8 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
             if (p + 1 < NP) load_o(p & 1 ? of0 : of1, q, p + 1);
             mfma_k(p & 1 ? of1 : of0, p);
           }
-          if constexpr (RNG) {
-            if (q + 1 == qf && q + 1 < qb) {
-              flush(rg);
-#pragma unroll
-              for (int a = 0; a < KB; ++a)
-#pragma unroll
-                for (int c = 0; c < NCB; ++c) K[a][c] = f4{0.f, 0.f, 0.f, 0.f};
-              ++rg;
-              qf = bound(rg + 1);
-            }
-          }
+          if constexpr (RNG && !NEST)
+            if (q + 1 == qf && q + 1 < qb) next_range();
 #pragma unroll
           for (int a = 0; a < RB; ++a)
 #pragma unroll
@@ -503,10 +508,27 @@ __global__ __launch_bounds__(64 * NWAVE, 1) void k_exchange_res(const char *__re
       // 1's two loads per block still in flight before its own: every second double step starts on an empty
       // ring)
       for (;;) {
-        step(ring[0]);
-        if (q >= qb) break;
-        step(ring[1]);
-        if (q >= qb) break;
+        const int qe = NEST ? qf : qb;
+        bool turn = false;  // slot 1 is the next one
+        for (;;) {
+          step(ring[0]);
+          if (NEST) turn = q >= qe;
+          if (q >= qe) break;
+          step(ring[1]);
+          if (q >= qe) break;
+        }
+        if (!NEST || q >= qb) break;
+        next_range();
+        if (turn) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) {
+              const u4 t = ring[0][u][c];
+              ring[0][u][c] = ring[1][u][c];
+              ring[1][u][c] = t;
+            }
+        }
       }
     }
     if constexpr (RNG) {
@@ -643,6 +665,9 @@ void shape_xres(int v, int ns, ResShape *r) {
                            (BF ? 2 * 16 * ((JB + 1) / 2) : 4 * 32 * JB) * (double)C::KB;  // matrix cycles per Q
   const int nb = ((v + 15) / 16 + sp.nct - 1) / sp.nct;
   r->tiles = (ns + KS - 1) / KS * sp.nct;
+  // (split BF16 waves of 16 W and 16 K blocks spill even without ranges, more with them: 6 to 8 % of a full launch
+  // of o64 v440 N_Q1461, 6 RHS, o32 v452 N_Q1461, 16, and o32 v470 N_Q1500, 8)
+  r->ranges = sp.qs == 1 && !(BF && C::RB * ((nb - sp.rem + sp.ncg - 1) / sp.ncg) >= 16);
   r->qs = sp.qs;
   // (a wave of two row blocks waits longer for its operands per product than one of three or four)
   r->q_cycles = per_block * ((nb + sp.ncg - 1) / sp.ncg) * 2 / (BF ? (C::RB > 2 ? 0.45 : 0.35) : 0.85);

@@ -420,14 +420,20 @@ int resident_splits(const ExchangeVariant *x, int o, int ns, int few, int v, int
 
 // Ranges of Q per split of an X-resident variant whose sk splits fill the CUs with the context's ns slices: as
 // many as make a launch of `few` slices (one right-hand side's) fastest with a workgroup per range, while
-// their sums' way to the slab and back takes at most 3 % of the full launch.
+// their sums' way to the slab and back takes at most 3 % of the full launch.  Split BF16 leaves a slab per range,
+// which the stage update reads: a range more costs 4 to 40 us as the slabs are 10 to 30 MB, and at most 2.5 %
+// are spent on that (per two steps, without and with that bound against no ranges: o44 v336 N_Q917, 6 RHS, 2.89
+// and 2.69 ms for 2.69; o64 v452 N_Q1461, 3 RHS, 5.38 and 4.88 for 4.88; o60 v400 N_Q1500, 3 RHS, keeps two).
 int resident_ranges(const ExchangeVariant *x, int o, int ns, int few, int v, int nq, int sk) {
   ResShape r, r1;
   x->res(v, ns, &r);
-  if (r.qs > 1) return 1;
+  if (!r.ranges) return 1;
   x->res(v, few, &r1);
   const double cycles = (nq + sk - 1) / sk * r.q_cycles;  // of a split
-  const int most = (int)std::min({1.0 + 0.03 * cycles / RES_RANGE_CYCLES, (double)nq / sk, (double)RES_RANGES_MAX});
+  const double spend = x->precision == RTTDA_PREC_FP32
+                           ? 0.03 * cycles / RES_RANGE_CYCLES
+                           : 0.025 * cycles / (4e3 + 4.0 * sk * ns * (double)o * v / 950.0);
+  const int most = (int)std::min({1.0 + spend, (double)nq / sk, (double)RES_RANGES_MAX});
   int best = 1;
   double best_t = 1e300;
   for (int g = 1; g <= most; ++g) {

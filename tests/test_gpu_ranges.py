@@ -19,7 +19,7 @@ TOL = {"fp32": 2e-6, "mixed": 2e-5}
 SHAPES = {"fp32": [(60, 257, 60, 40), (48, 277, 45, 40), (33, 203, 90, 64), (40, 250, 67, 33), (24, 290, 80, 64),
                    (30, 330, 50, 64), (16, 340, 90, 64), (57, 400, 31, 22)],
           "mixed": [(60, 257, 130, 40), (64, 400, 85, 33), (48, 277, 150, 40), (33, 330, 133, 40), (24, 340, 200, 64),
-                    (16, 370, 300, 64)]}
+                    (16, 370, 300, 64), (40, 440, 203, 40)]}
 
 
 @pytest.mark.parametrize("prec,o,v,nq,R", [(p, *s) for p in SHAPES for s in SHAPES[p]])
